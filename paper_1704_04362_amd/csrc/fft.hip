@@ -18,17 +18,17 @@
 //   3. the half spectrum of the real tube is separated from Z by conjugate
 //      symmetry, X[k] = (Z[k] + conj Z[M-k])/2 + W_n3^k (Z[k] - conj Z[M-k])/2i,
 //      and each slice k is written with one coalesced store per wavefront.
-// The inverse kernel runs these steps backwards. Long tubes (n3 above 256
-// without a specialised kernel, prime factors up to 13) use a
-// workgroup-per-tube mixed-radix transform in LDS; even ones beyond its LDS
-// budget (up to 2^19) a four-step transform through HBM; lengths from 257
-// with a larger prime factor, up to 2048 (float32) / 1024 (float64),
-// Bluestein's chirp-z transform in LDS; the rest a direct O(n3^2) transform.
+// The inverse kernel runs these steps backwards. Short lengths without a
+// packed kernel run one tube per thread (rfft_small_kernel); other lengths
+// that LDS holds take the transforms of fft_lds.hip; even ones beyond it (up
+// to 2^19) a four-step transform through HBM; the rest a direct O(n3^2)
+// transform.
 #include <cmath>
 #include <mutex>
 #include <vector>
 
-#include "common.hpp"
+#include "fft_stages.hpp"
+#include "fft_tubes.hpp"
 
 namespace tp {
 namespace {
@@ -196,39 +196,6 @@ struct Vec16<double> {
   static constexpr int n = 2;
 };
 
-struct FwdArgs {
-  int64_t rows, cols, in_cols;
-  int64_t ntubes;  // output slots: major x ld
-  const int32_t* row_idx;
-  const int32_t* col_idx;
-  const double* row_scale;
-  const double* col_scale;
-  const int64_t* count;
-  int64_t ld;    // slots per major index (>= cols, or >= rows when colmajor)
-  int colmajor;  // slot t = col * ld + row instead of row * ld + col
-  // > 0 (column-major spectra with ld a multiple of the tile): workgroup b
-  // takes the tile (b / nmaj) of major index b mod nmaj, so workgroups that
-  // run together read neighbouring tubes of the tube-major input instead of
-  // tubes a whole input row apart
-  int64_t nmaj;
-};
-
-// Input tube offset and scale of output slot t; returns false for a slot
-// that is to be written as zeros (padding, or beyond the live sample count).
-__device__ __forceinline__ bool tube_source(const FwdArgs& a, int64_t t, int64_t& src, double& s) {
-  const int64_t maj = t / a.ld, mn = t - maj * a.ld;
-  const int64_t ra = a.colmajor ? mn : maj, cb = a.colmajor ? maj : mn;
-  if (ra >= a.rows || cb >= a.cols) return false;
-  int64_t lim = a.count ? *a.count : INT64_MAX;
-  if (a.row_idx && ra >= lim) return false;
-  if (a.col_idx && cb >= lim) return false;
-  const int64_t ir = a.row_idx ? a.row_idx[ra] : ra;
-  const int64_t ic = a.col_idx ? a.col_idx[cb] : cb;
-  src = ir * a.in_cols + ic;
-  s = (a.row_scale ? a.row_scale[ra] : 1.0) * (a.col_scale ? a.col_scale[cb] : 1.0);
-  return true;
-}
-
 constexpr int kTile = 64;  // tubes per workgroup (one wavefront)
 
 // Output of one spectrum value: planar float (re, im planes [k][slot]) or,
@@ -351,6 +318,65 @@ __global__ __launch_bounds__(kTile) void rfft_kernel(const T* __restrict__ x, Fw
       emit<T, SPLIT>(ore, oim, K, ks, k, t, er + (orr * wr - oi * wi), ei + (orr * wi + oi * wr));
     }
   }
+}
+
+// Short lengths without a packed kernel: one tube per thread, the length-N
+// transform of fft_stages.hpp in float64 registers with a zero imaginary part
+// (folded away by the compiler), each thread reading its whole tube at once.
+// Bound by HBM: 3e7 values of n = 5 float32 tubes take 40 us forward and 38
+// back (6.6 TB/s; a direct sum per output 86 / 85, the LDS stages 176 / 129).
+template <typename T, int N>
+struct Tube {
+  T v[N];
+};
+constexpr int kSmallNT = 256;
+
+template <typename T, int N>
+__global__ __launch_bounds__(kSmallNT) void rfft_small_kernel(const T* __restrict__ x, FwdArgs a, T* __restrict__ ore,
+                                                              T* __restrict__ oim) {
+  const int64_t t = (int64_t)blockIdx.x * kSmallNT + threadIdx.x, ks = a.ntubes;
+  if (t >= ks) return;
+  int64_t src;
+  double s;
+  double r[N], i[N];
+  const bool live = tube_source(a, t, src, s);
+  Tube<T, N> w = {};
+  if (live) __builtin_memcpy(&w, x + src * N, sizeof(w));
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    r[e] = (!live || s == 1.0) ? (double)w.v[e] : (double)(T)((double)w.v[e] * s);
+    i[e] = 0.0;
+  }
+  lfft::dft<N>(r, i);
+#pragma unroll
+  for (int k = 0; k <= N / 2; ++k) {
+    ore[k * ks + t] = (T)r[k];
+    oim[k * ks + t] = (k == 0 || 2 * k == N) ? T(0) : (T)i[k];
+  }
+}
+
+template <typename T, int N>
+__global__ __launch_bounds__(kSmallNT) void irfft_small_kernel(const T* __restrict__ xre, const T* __restrict__ xim,
+                                                               int64_t ks, T* __restrict__ y) {
+  const int64_t t = (int64_t)blockIdx.x * kSmallNT + threadIdx.x;
+  if (t >= ks) return;
+  // the forward transform of the conjugated Hermitian extension is real
+  double r[N], i[N];
+#pragma unroll
+  for (int k = 0; k <= N / 2; ++k) {
+    const bool real = k == 0 || 2 * k == N;
+    r[k] = (double)xre[k * ks + t];
+    i[k] = real ? 0.0 : -(double)xim[k * ks + t];
+    if (!real) {
+      r[N - k] = r[k];
+      i[N - k] = -i[k];
+    }
+  }
+  lfft::dft<N>(r, i);
+  Tube<T, N> w;
+#pragma unroll
+  for (int e = 0; e < N; ++e) w.v[e] = (T)(r[e] / (double)N);
+  __builtin_memcpy(y + t * N, &w, sizeof(w));
 }
 
 // Output staging of the inverse transform: the 64 tubes of a workgroup are
@@ -551,21 +577,8 @@ __global__ void irdft_direct_kernel(const T* __restrict__ xre, const T* __restri
   }
 }
 
-// --------------------------------------------------------------------------
-// Long tubes (n3 above 256 without a specialised kernel): one workgroup per
-// tube, the whole tube as n3 complex values in LDS, an in-place mixed-radix
-// decimation-in-time FFT. The input is loaded in digit-reversed order for
-// the radix sequence r_0, r_1, ... (4s first, then 2, 3, 5, then primes up
-// to kLongMaxRadix); stage q combines r_q sub-transforms of span m (the
-// product of the earlier radices) into transforms of span m r_q: for the
-// butterfly (group g, offset j < m) the inputs a[g + j + s m] take the
-// twiddle W_{m r_q}^{j s} and go through an r_q-point DFT, written back to
-// the same positions. Twiddles and the small DFTs' roots are evaluated with
-// sincospi in float64.
-// --------------------------------------------------------------------------
 constexpr int kLongMaxStages = 24;
 constexpr int kLongMaxRadix = 13;
-constexpr int kLongNT = 256;
 constexpr int64_t kLongMin = 257;
 
 struct LongPlan {
@@ -583,118 +596,6 @@ __device__ __forceinline__ int long_src(const LongPlan& pl, int pos) {
     pos /= p;
   }
   return out;
-}
-
-template <typename T>
-__device__ void long_stages(const LongPlan& pl, T* ar, T* ai) {
-  const int n = pl.n;
-  int m = 1;
-  for (int q = 0; q < pl.nst; ++q) {
-    const int p = pl.rad[q], span = m * p;
-    // roots of the p-point DFT
-    double cw[kLongMaxRadix], sw[kLongMaxRadix];
-    for (int e = 0; e < p; ++e) sincospi(-2.0 * e / p, &sw[e], &cw[e]);
-    for (int b = threadIdx.x; b < n / p; b += kLongNT) {
-      const int j = b % m, g = (b / m) * span;
-      double vr[kLongMaxRadix], vi[kLongMaxRadix];
-      for (int t = 0; t < p; ++t) {
-        const double xr = (double)ar[g + j + t * m], xi = (double)ai[g + j + t * m];
-        const int e = (j * t) % span;
-        double sn, cs;
-        sincospi(-2.0 * e / span, &sn, &cs);
-        vr[t] = xr * cs - xi * sn;
-        vi[t] = xr * sn + xi * cs;
-      }
-      for (int t = 0; t < p; ++t) {
-        double accr = 0.0, acci = 0.0;
-        for (int u = 0; u < p; ++u) {
-          const int e = (u * t) % p;
-          accr += vr[u] * cw[e] - vi[u] * sw[e];
-          acci += vr[u] * sw[e] + vi[u] * cw[e];
-        }
-        ar[g + j + t * m] = (T)accr;
-        ai[g + j + t * m] = (T)acci;
-      }
-    }
-    __syncthreads();
-    m = span;
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kLongNT) void rfft_long_kernel(const T* __restrict__ x, FwdArgs a, LongPlan pl,
-                                                            T* __restrict__ ore, T* __restrict__ oim) {
-  extern __shared__ unsigned char long_lds[];
-  T* ar = reinterpret_cast<T*>(long_lds);
-  T* ai = ar + pl.n;
-  const int64_t t = blockIdx.x;
-  const int n = pl.n, K = n / 2 + 1;
-  const int64_t ks = a.ntubes;
-  int64_t src = -1;
-  double s = 0.0;
-  const bool live = tube_source(a, t, src, s);
-  for (int pos = threadIdx.x; pos < n; pos += kLongNT) {
-    T v = T(0);
-    if (live) {
-      const T xv = x[src * n + long_src(pl, pos)];
-      v = (s == 1.0) ? xv : (T)((double)xv * s);
-    }
-    ar[pos] = v;
-    ai[pos] = T(0);
-  }
-  __syncthreads();
-  long_stages<T>(pl, ar, ai);
-  for (int k = threadIdx.x; k < K; k += kLongNT) {
-    ore[(int64_t)k * ks + t] = ar[k];
-    oim[(int64_t)k * ks + t] = (k == 0 || 2 * k == n) ? T(0) : ai[k];
-  }
-}
-
-// inverse: the Hermitian extension of the half spectrum, conjugated, goes
-// through the forward stages; y = Re(result) / n
-template <typename T>
-__global__ __launch_bounds__(kLongNT) void irfft_long_kernel(const T* __restrict__ xre, const T* __restrict__ xim,
-                                                             int64_t ntubes, LongPlan pl, T* __restrict__ y) {
-  extern __shared__ unsigned char long_lds[];
-  T* ar = reinterpret_cast<T*>(long_lds);
-  T* ai = ar + pl.n;
-  const int64_t t = blockIdx.x;
-  const int n = pl.n, K = n / 2 + 1;
-  for (int pos = threadIdx.x; pos < n; pos += kLongNT) {
-    const int k = long_src(pl, pos);
-    T vr, vi;
-    if (k < K) {
-      vr = xre[(int64_t)k * ntubes + t];
-      vi = (k == 0 || 2 * k == n) ? T(0) : xim[(int64_t)k * ntubes + t];
-    } else {
-      // X[k] = conj(X[n - k])
-      vr = xre[(int64_t)(n - k) * ntubes + t];
-      vi = -xim[(int64_t)(n - k) * ntubes + t];
-    }
-    ar[pos] = vr;
-    ai[pos] = -vi;
-  }
-  __syncthreads();
-  long_stages<T>(pl, ar, ai);
-  const T inv = T(1) / T(n);
-  for (int e = threadIdx.x; e < n; e += kLongNT) y[t * n + e] = ar[e] * inv;
-}
-
-// Radix plan of a long tube; false when n has a prime factor above
-// kLongMaxRadix, too many stages, or does not fit the LDS budget.
-bool long_plan(int64_t n, int elem_bytes, LongPlan& pl) {
-  if (n < kLongMin || 2 * n * elem_bytes > 64 * 1024) return false;
-  pl.n = (int)n;
-  pl.nst = 0;
-  int64_t r = n;
-  for (int p : {4, 2, 3, 5, 7, 11, 13}) {
-    while (r % p == 0) {
-      if (pl.nst == kLongMaxStages) return false;
-      pl.rad[pl.nst++] = p;
-      r /= p;
-    }
-  }
-  return r == 1;
 }
 
 // --------------------------------------------------------------------------
@@ -1187,157 +1088,6 @@ bool radix_plan(int64_t n, LongPlan& pl) {
   return r == 1;
 }
 
-// --------------------------------------------------------------------------
-// Lengths with a prime factor above 13 (up to kBlueMax): Bluestein's
-// chirp-z transform in LDS, one workgroup per tube. With the chirp
-// w[m] = exp(-i pi m^2 / n), the DFT is X[k] = w[k] sum_m (x[m] w[m])
-// conj(w[k - m]) (from 2 m k = m^2 + k^2 - (k - m)^2), a circular
-// convolution of length L >= 2n - 1 (L without prime factors above 13)
-// evaluated by three mixed-radix transforms of length L: a = x w and the
-// filter b (conj w at m and L - m) forward, then the inverse of A B through
-// the conjugate. The inverse tube transform is the forward one of the
-// conjugated Hermitian extension, conjugated and scaled by 1/n.
-// --------------------------------------------------------------------------
-constexpr int kBlueMax = 2048;  // float32 tubes; float64 up to half of it
-
-struct BluePlan {
-  int n;
-  LongPlan pl;  // length L
-};
-
-// chirp exp(-i pi m^2 / n) in double (m^2 reduced mod 2n, exact in int64)
-__device__ __forceinline__ void blue_chirp(int m, int n, double& c, double& s) {
-  const int64_t e = ((int64_t)m * m) % (2 * (int64_t)n);
-  sincospi(-(double)e / (double)n, &s, &c);
-}
-
-// DFT of n complex values: load(m) gives input m < n, store(k, re, im)
-// takes output k < nout (<= n). LDS: ar | br (2L values, br = ar + L) and
-// ai | bi, so the two forward transforms run as one two-sequence pass.
-constexpr int kBluePer = 2 * kBlueMax / kFsNT;  // L / threads at most
-
-template <typename T, typename Load, typename Store>
-__device__ void bluestein(const BluePlan& bp, T* ar, T* ai, Load load, int nout, Store store) {
-  const int n = bp.n, L = bp.pl.n;
-  T* br = ar + L;
-  T* bi = ai + L;
-  for (int m = threadIdx.x; m < L; m += kFsNT) {
-    T a_r = T(0), a_i = T(0), b_r = T(0), b_i = T(0);
-    if (m < n) {
-      double c, sn, xr, xi;
-      blue_chirp(m, n, c, sn);
-      load(m, xr, xi);
-      a_r = (T)(xr * c - xi * sn);
-      a_i = (T)(xr * sn + xi * c);
-      b_r = (T)c;
-      b_i = (T)(-sn);
-    } else if (m > L - n) {
-      double c, sn;
-      blue_chirp(L - m, n, c, sn);
-      b_r = (T)c;
-      b_i = (T)(-sn);
-    }
-    const int pos = long_dst(bp.pl, m);
-    ar[pos] = a_r;
-    ai[pos] = a_i;
-    br[pos] = b_r;
-    bi[pos] = b_i;
-  }
-  __syncthreads();
-  multi_stages<T>(bp.pl, ar, ai, 2);
-  // conj(A B), through registers, into ar/ai in digit-reversed order
-  T pr[kBluePer], pi[kBluePer];
-#pragma unroll
-  for (int q = 0; q < kBluePer; ++q) {
-    const int m = threadIdx.x + q * kFsNT;
-    if (m < L) {
-      const double xr = (double)ar[m], xi = (double)ai[m], yr = (double)br[m], yi = (double)bi[m];
-      pr[q] = (T)(xr * yr - xi * yi);
-      pi[q] = (T)(-(xr * yi + xi * yr));
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kBluePer; ++q) {
-    const int m = threadIdx.x + q * kFsNT;
-    if (m < L) {
-      const int pos = long_dst(bp.pl, m);
-      ar[pos] = pr[q];
-      ai[pos] = pi[q];
-    }
-  }
-  __syncthreads();
-  multi_stages<T>(bp.pl, ar, ai, 1);
-  const double inv = 1.0 / (double)L;
-  for (int k = threadIdx.x; k < nout; k += kFsNT) {
-    double c, sn;
-    blue_chirp(k, n, c, sn);
-    const double yr = (double)ar[k] * inv, yi = -(double)ai[k] * inv;  // the convolution at k
-    store(k, yr * c - yi * sn, yr * sn + yi * c);
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kFsNT) void rdft_blue_kernel(const T* __restrict__ x, FwdArgs a, BluePlan bp,
-                                                          T* __restrict__ ore, T* __restrict__ oim) {
-  extern __shared__ unsigned char blue_lds[];
-  const int n = bp.n, L = bp.pl.n, K = n / 2 + 1;
-  T* ar = reinterpret_cast<T*>(blue_lds);
-  T* ai = ar + 2 * L;
-  const int64_t t = blockIdx.x;
-  const int64_t ks = a.ntubes;
-  int64_t src = -1;
-  double sc = 1.0;
-  const bool live = tube_source(a, t, src, sc);
-  auto load = [&](int m, double& xr, double& xi) {
-    xr = live ? (double)x[src * n + m] * sc : 0.0;
-    xi = 0.0;
-  };
-  auto store = [&](int k, double re, double im) {
-    ore[(int64_t)k * ks + t] = (T)re;
-    oim[(int64_t)k * ks + t] = (k == 0 || 2 * k == n) ? T(0) : (T)im;
-  };
-  bluestein<T>(bp, ar, ai, load, K, store);
-}
-
-// inverse: the forward transform of the conjugated Hermitian extension,
-// conjugated (only the real part is kept) and scaled by 1/n
-template <typename T>
-__global__ __launch_bounds__(kFsNT) void irdft_blue_kernel(const T* __restrict__ xre, const T* __restrict__ xim,
-                                                           int64_t ntubes, BluePlan bp, T* __restrict__ y) {
-  extern __shared__ unsigned char blue_lds[];
-  const int n = bp.n, L = bp.pl.n, K = n / 2 + 1;
-  T* ar = reinterpret_cast<T*>(blue_lds);
-  T* ai = ar + 2 * L;
-  const int64_t t = blockIdx.x;
-  auto load = [&](int k, double& re, double& im) {
-    if (k < K) {
-      re = (double)xre[(int64_t)k * ntubes + t];
-      im = (k == 0 || 2 * k == n) ? 0.0 : (double)xim[(int64_t)k * ntubes + t];
-    } else {
-      re = (double)xre[(int64_t)(n - k) * ntubes + t];
-      im = -(double)xim[(int64_t)(n - k) * ntubes + t];
-    }
-    im = -im;
-  };
-  const double inv = 1.0 / (double)n;
-  auto store = [&](int e, double re, double) { y[t * n + e] = (T)(re * inv); };
-  bluestein<T>(bp, ar, ai, load, n, store);
-}
-
-// Bluestein plan: L = the smallest length >= 2n - 1 without prime factors
-// above 13; the four L-long sequences must fit in 64 KB of LDS.
-bool blue_plan(int64_t n, int elem_bytes, BluePlan& bp) {
-  if (n < 2 || n > (elem_bytes == 4 ? kBlueMax : kBlueMax / 2)) return false;
-  for (int64_t L = 2 * n - 1;; ++L) {
-    if (4 * L * elem_bytes > 64 * 1024) return false;
-    if (radix_plan(L, bp.pl)) {
-      bp.n = (int)n;
-      return true;
-    }
-  }
-}
-
 // Four-step plan of an even n: N = n/2 = N1 N2 with N2 the largest divisor
 // <= kFsMaxN2 that leaves N1 <= kFsMaxN1, both without prime factors above 13.
 bool four_step_plan(int64_t n, FourStep& fs) {
@@ -1438,6 +1188,63 @@ InvKernel<T> pick_inv(int64_t n) {
 }
 
 template <typename T>
+FwdKernel<T> pick_small_fwd(int64_t n) {
+  switch (n) {
+    case 3: return rfft_small_kernel<T, 3>;
+    case 5: return rfft_small_kernel<T, 5>;
+    case 6: return rfft_small_kernel<T, 6>;
+    case 7: return rfft_small_kernel<T, 7>;
+    case 9: return rfft_small_kernel<T, 9>;
+    case 11: return rfft_small_kernel<T, 11>;
+    case 12: return rfft_small_kernel<T, 12>;
+    case 13: return rfft_small_kernel<T, 13>;
+    case 14: return rfft_small_kernel<T, 14>;
+    case 15: return rfft_small_kernel<T, 15>;
+    case 17: return rfft_small_kernel<T, 17>;
+    case 19: return rfft_small_kernel<T, 19>;
+    case 23: return rfft_small_kernel<T, 23>;
+    default: return nullptr;
+  }
+}
+
+template <typename T>
+InvKernel<T> pick_small_inv(int64_t n) {
+  switch (n) {
+    case 3: return irfft_small_kernel<T, 3>;
+    case 5: return irfft_small_kernel<T, 5>;
+    case 6: return irfft_small_kernel<T, 6>;
+    case 7: return irfft_small_kernel<T, 7>;
+    case 9: return irfft_small_kernel<T, 9>;
+    case 11: return irfft_small_kernel<T, 11>;
+    case 12: return irfft_small_kernel<T, 12>;
+    case 13: return irfft_small_kernel<T, 13>;
+    case 14: return irfft_small_kernel<T, 14>;
+    case 15: return irfft_small_kernel<T, 15>;
+    case 17: return irfft_small_kernel<T, 17>;
+    case 19: return irfft_small_kernel<T, 19>;
+    case 23: return irfft_small_kernel<T, 23>;
+    default: return nullptr;
+  }
+}
+
+template <typename T>
+struct TypeOf;
+template <>
+struct TypeOf<float> {
+  static constexpr int dtype = TP_F32;
+};
+template <>
+struct TypeOf<double> {
+  static constexpr int dtype = TP_F64;
+};
+
+// longest tube of the LDS transforms (fft_lds.hip)
+template <typename T>
+constexpr int64_t lds_max() {
+  return 32768 / (int64_t)sizeof(T);
+}
+
+template <typename T>
 int fwd_impl(const T* x, int64_t n3, const TubeGather& g, T* re, T* im, hipStream_t st) {
   FwdArgs a{g.rows, g.cols, g.in_cols, g.rows * g.cols, g.row_idx, g.col_idx, g.row_scale, g.col_scale, g.count,
             g.cols, 0, 0};
@@ -1445,17 +1252,16 @@ int fwd_impl(const T* x, int64_t n3, const TubeGather& g, T* re, T* im, hipStrea
   if (auto k = pick_fwd<T>(n3)) {
     const int64_t blocks = (a.ntubes + kTile - 1) / kTile;
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kTile), 0, st, x, a, re, im);
-  } else if (LongPlan pl; long_plan(n3, (int)sizeof(T), pl)) {
-    if (a.ntubes > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many tubes");
-    hipLaunchKernelGGL(rfft_long_kernel<T>, dim3((unsigned)a.ntubes), dim3(kLongNT), 2 * n3 * sizeof(T), st, x, a,
-                       pl, re, im);
-  } else if (FourStep fs; n3 >= kLongMin && four_step_plan(n3, fs)) {
-    return fs_forward<T>(x, a, fs, (T*)re, (T*)im, st);
-  } else if (BluePlan bp; n3 >= kLongMin && blue_plan(n3, (int)sizeof(T), bp)) {
-    if (a.ntubes > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many tubes");
-    hipLaunchKernelGGL(rdft_blue_kernel<T>, dim3((unsigned)a.ntubes), dim3(kFsNT), 4 * bp.pl.n * sizeof(T), st, x, a,
-                       bp, re, im);
+  } else if (auto k = pick_small_fwd<T>(n3)) {
+    const int64_t blocks = (a.ntubes + kSmallNT - 1) / kSmallNT;
+    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kSmallNT), 0, st, x, a, re, im);
   } else {
+    bool handled = false;
+    if (n3 <= lds_max<T>())
+      if (int rc = lds_forward(x, TypeOf<T>::dtype, n3, a, re, im, st, &handled)) return rc;
+    if (handled) return TP_OK;
+    FourStep fs;
+    if (n3 >= kLongMin && four_step_plan(n3, fs)) return fs_forward<T>(x, a, fs, re, im, st);
     const int64_t blocks = (a.ntubes + 127) / 128;
     if (n3 <= kDirectTable)
       hipLaunchKernelGGL((rdft_direct_kernel<T, true>), dim3((unsigned)blocks), dim3(128), 2 * n3 * sizeof(double), st,
@@ -1474,17 +1280,16 @@ int inv_impl(const T* re, const T* im, int64_t n3, int64_t ntubes, T* y, hipStre
   if (auto k = pick_inv<T>(n3)) {
     const int64_t blocks = (ntubes + kTile - 1) / kTile;
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kTile), 0, st, re, im, ntubes, y);
-  } else if (LongPlan pl; long_plan(n3, (int)sizeof(T), pl)) {
-    if (ntubes > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many tubes");
-    hipLaunchKernelGGL(irfft_long_kernel<T>, dim3((unsigned)ntubes), dim3(kLongNT), 2 * n3 * sizeof(T), st, re, im,
-                       ntubes, pl, y);
-  } else if (FourStep fs; n3 >= kLongMin && four_step_plan(n3, fs)) {
-    return fs_inverse<T>(re, im, ntubes, fs, y, st);
-  } else if (BluePlan bp; n3 >= kLongMin && blue_plan(n3, (int)sizeof(T), bp)) {
-    if (ntubes > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many tubes");
-    hipLaunchKernelGGL(irdft_blue_kernel<T>, dim3((unsigned)ntubes), dim3(kFsNT), 4 * bp.pl.n * sizeof(T), st, re, im,
-                       ntubes, bp, y);
+  } else if (auto k = pick_small_inv<T>(n3)) {
+    const int64_t blocks = (ntubes + kSmallNT - 1) / kSmallNT;
+    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kSmallNT), 0, st, re, im, ntubes, y);
   } else {
+    bool handled = false;
+    if (n3 <= lds_max<T>())
+      if (int rc = lds_inverse(re, im, TypeOf<T>::dtype, n3, ntubes, y, st, &handled)) return rc;
+    if (handled) return TP_OK;
+    FourStep fs;
+    if (n3 >= kLongMin && four_step_plan(n3, fs)) return fs_inverse<T>(re, im, ntubes, fs, y, st);
     const int64_t blocks = (ntubes + 127) / 128;
     if (n3 <= kDirectTable)
       hipLaunchKernelGGL((irdft_direct_kernel<T, true>), dim3((unsigned)blocks), dim3(128), 2 * n3 * sizeof(double),

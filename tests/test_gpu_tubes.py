@@ -1,0 +1,56 @@
+"""GPU parity of the tube transforms over the tube lengths where their kernels
+change: one thread per tube (3 to 23), the LDS stages with float64 (up to 256)
+and float32 storage, Bluestein's transform (a prime factor above 13), odd and
+even lengths, and fewer or more tubes than a workgroup takes.
+
+Tolerances: float32 results round 2^-24 once per pass through float32 storage,
+at most 8 passes in a transform (Bluestein: two transforms of at most 3 stages
+and two products), so 8 x 6e-8 = 5e-7 bounds the relative Frobenius error of
+one transform and twice that a round trip; float64 1e-14 (eps_64 times the
+same count and the operations between).
+"""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import decomp as D
+from oracle import sampling as S
+from oracle import tensor as T
+
+pytestmark = pytest.mark.gpu
+
+api = pytest.importorskip("paper_1704_04362_amd.api")
+
+TOL = {np.float32: 5e-7, np.float64: 1e-14}
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n3", [3, 14, 17, 23, 33, 34, 96, 127, 202, 256, 258, 1001, 1023, 2038, 3000, 4096])
+def test_tube_transforms_by_length(n3, dtype):
+    if dtype == np.float64 and n3 == 2038:
+        n3 = 1018
+    for n1, n2 in ((1, 1), (3, 13), (41, 53)):
+        X = W.gaussian((n1, n2, n3), seed=n3, salt=n1).astype(dtype)
+        re, im = api.tfft(dev(X))
+        H = T.half_spectrum(X.astype(np.float64))
+        assert T.rel_fro(re.cpu().numpy() + 1j * im.cpu().numpy(), H) < TOL[dtype]
+        assert not im[0].any() and (n3 % 2 or not im[-1].any())
+        assert T.rel_fro(api.tifft(re, im, n3).cpu().numpy(), X) < 2 * TOL[dtype]
+
+
+@pytest.mark.parametrize("n3", [17, 80, 101, 600])
+def test_tube_transforms_of_picked_slices(n3):
+    """Picked, scaled slices (fewer live picks than slots) through these
+    transforms: the rt-product against the oracle."""
+    A = W.gaussian((9, 70, n3), seed=5)
+    B = W.gaussian((70, 11, n3), seed=6)
+    w = W.lognormal_weights(70, 3)
+    picks = api.tsample("user", 20, mode="bernoulli", seed=2, w=dev(w))
+    Z = api.tprod(dev(A), dev(B), picks=picks, prec="f64").cpu().numpy()
+    idx, sc = S.sample_bernoulli(w, 20, seed=2)
+    assert T.rel_fro(Z, D.rtprod(A, B, idx, sc)) < 1e-12
