@@ -89,10 +89,12 @@ struct TubeGather {
   const int64_t* count = nullptr;
 };
 
-int fft_forward(const void* x, int dtype, int64_t n3, const TubeGather& g, void* re, void* im,
-                hipStream_t st);
+// sums: lengths up to 256 without a packed register kernel keep the direct
+// sums, whose last bits the sweep-capped ADMM needs unchanged (api_svt.cpp).
+int fft_forward(const void* x, int dtype, int64_t n3, const TubeGather& g, void* re, void* im, hipStream_t st,
+                bool sums = false);
 int fft_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t rows, int64_t cols, void* x,
-                hipStream_t st);
+                hipStream_t st, bool sums = false);
 bool fft_supported(int64_t n3);
 // Forward transform of float32 tubes into the split operand format of the
 // matrix-core products: four bf16 planes [hi re, lo re, hi im, lo im][k][slot]

@@ -1245,19 +1245,20 @@ constexpr int64_t lds_max() {
 }
 
 template <typename T>
-int fwd_impl(const T* x, int64_t n3, const TubeGather& g, T* re, T* im, hipStream_t st) {
+int fwd_impl(const T* x, int64_t n3, const TubeGather& g, T* re, T* im, hipStream_t st, bool sums) {
   FwdArgs a{g.rows, g.cols, g.in_cols, g.rows * g.cols, g.row_idx, g.col_idx, g.row_scale, g.col_scale, g.count,
             g.cols, 0, 0};
   if (a.ntubes == 0) return TP_OK;
+  sums = sums && n3 < kLongMin;
   if (auto k = pick_fwd<T>(n3)) {
     const int64_t blocks = (a.ntubes + kTile - 1) / kTile;
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kTile), 0, st, x, a, re, im);
-  } else if (auto k = pick_small_fwd<T>(n3)) {
+  } else if (auto k = pick_small_fwd<T>(n3); k && !sums) {
     const int64_t blocks = (a.ntubes + kSmallNT - 1) / kSmallNT;
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kSmallNT), 0, st, x, a, re, im);
   } else {
     bool handled = false;
-    if (n3 <= lds_max<T>())
+    if (n3 <= lds_max<T>() && !sums)
       if (int rc = lds_forward(x, TypeOf<T>::dtype, n3, a, re, im, st, &handled)) return rc;
     if (handled) return TP_OK;
     FourStep fs;
@@ -1275,17 +1276,18 @@ int fwd_impl(const T* x, int64_t n3, const TubeGather& g, T* re, T* im, hipStrea
 }
 
 template <typename T>
-int inv_impl(const T* re, const T* im, int64_t n3, int64_t ntubes, T* y, hipStream_t st) {
+int inv_impl(const T* re, const T* im, int64_t n3, int64_t ntubes, T* y, hipStream_t st, bool sums) {
   if (ntubes == 0) return TP_OK;
+  sums = sums && n3 < kLongMin;
   if (auto k = pick_inv<T>(n3)) {
     const int64_t blocks = (ntubes + kTile - 1) / kTile;
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kTile), 0, st, re, im, ntubes, y);
-  } else if (auto k = pick_small_inv<T>(n3)) {
+  } else if (auto k = pick_small_inv<T>(n3); k && !sums) {
     const int64_t blocks = (ntubes + kSmallNT - 1) / kSmallNT;
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kSmallNT), 0, st, re, im, ntubes, y);
   } else {
     bool handled = false;
-    if (n3 <= lds_max<T>())
+    if (n3 <= lds_max<T>() && !sums)
       if (int rc = lds_inverse(re, im, TypeOf<T>::dtype, n3, ntubes, y, st, &handled)) return rc;
     if (handled) return TP_OK;
     FourStep fs;
@@ -1343,20 +1345,21 @@ int fft_forward_split(const float* x, int64_t n3, const TubeGather& g, bool colm
   return TP_OK;
 }
 
-int fft_forward(const void* x, int dtype, int64_t n3, const TubeGather& g, void* re, void* im, hipStream_t st) {
+int fft_forward(const void* x, int dtype, int64_t n3, const TubeGather& g, void* re, void* im, hipStream_t st,
+                bool sums) {
   if (int rc = ensure_twiddles()) return rc;
   if ((g.rows * g.cols + kTile - 1) / kTile > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many tubes");
   if (dtype == TP_F64)
-    return fwd_impl<double>((const double*)x, n3, g, (double*)re, (double*)im, st);
-  return fwd_impl<float>((const float*)x, n3, g, (float*)re, (float*)im, st);
+    return fwd_impl<double>((const double*)x, n3, g, (double*)re, (double*)im, st, sums);
+  return fwd_impl<float>((const float*)x, n3, g, (float*)re, (float*)im, st, sums);
 }
 
 int fft_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t rows, int64_t cols, void* x,
-                hipStream_t st) {
+                hipStream_t st, bool sums) {
   if (int rc = ensure_twiddles()) return rc;
   if (dtype == TP_F64)
-    return inv_impl<double>((const double*)re, (const double*)im, n3, rows * cols, (double*)x, st);
-  return inv_impl<float>((const float*)re, (const float*)im, n3, rows * cols, (float*)x, st);
+    return inv_impl<double>((const double*)re, (const double*)im, n3, rows * cols, (double*)x, st, sums);
+  return inv_impl<float>((const float*)re, (const float*)im, n3, rows * cols, (float*)x, st, sums);
 }
 
 }  // namespace tp
