@@ -21,6 +21,7 @@
 
 #include "common.hpp"
 #include "jacobi.hpp"
+#include "jacobi32.hpp"
 #include "svt.hpp"
 
 namespace tp {
@@ -28,13 +29,13 @@ namespace {
 
 constexpr int RB = 16;       // rows per block
 constexpr int PR = 2 * RB;   // rows per pair
-constexpr int CHC = 64;      // columns staged per chunk
 constexpr int NT = 256;
+constexpr int PT = 512;      // threads of a pair step
 // Cyclic Jacobi sweeps on the 32 x 32 Gram matrix of a pair step. The outer
 // sweeps revisit every pair until all of them are orthogonal, so a pair step
 // need not diagonalise its Gram matrix exactly: one inner sweep costs about
 // one more outer sweep in total against a full inner solve, at a fraction of
-// the price per step (the inner solve dominates a step).
+// the price per step.
 constexpr int kInnerSweeps = 1;
 
 struct PairArgs {
@@ -47,7 +48,6 @@ struct PairArgs {
   float* ratio;      // (nb-1) x K x (nb/2) ratios of this sweep, per round
   const int* conv;   // K flags
   double tol;
-  int inner_sweeps;
 };
 
 __device__ __forceinline__ int tournament(int pos, int round, int nb) {
@@ -56,141 +56,273 @@ __device__ __forceinline__ int tournament(int pos, int round, int nb) {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-// Staged rows of a pair step live in LDS as float64 with a row stride chosen
-// per access pattern (in doubles): the Gram products read 16 rows x 4
-// consecutive columns per instruction (stride = 4 mod 32 keeps that 2-way,
-// the minimum for 64 eight-byte lanes), the rotations 4 rows x 16 columns
-// (stride = 16 mod 32).
-constexpr int kGramStride = CHC + 4;
-constexpr int kRotStride = CHC + 16;
-constexpr int kStage = PR * kRotStride;
+// v_mfma_f64_16x16x4f64: A lane l = A[l % 16][l / 16], B lane l =
+// B[l / 16][l % 16], D lane l register v = D[4 v + l / 16][l % 16], as
+// measured on gfx950.
+#define TP_MFMA64(a, b, c) __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0)
 
-// A chunk of the staged rows (columns [c0, c0 + nc) of rows[0..PR), float32
-// planar) as held by one thread between its global loads and its LDS
-// stores: element e = tid + NT q is row e / CHC, column e % CHC; missing rows
-// and columns past nc read as zero. Loading the next chunk into registers
-// before the current one is consumed keeps the global loads in flight
-// during the products.
-constexpr int kChunkPer = PR * CHC / NT;
-constexpr int kGramDepth = 2, kRotDepth = 1;
-struct ChunkRegs {
-  float r[kChunkPer], i[kChunkPer];
+// Gram matrix G_st = sum_j x_s[j] conj(x_t[j]) of the 32 staged rows, straight
+// from global memory into the operand layout: lane (row r, group g) reads the
+// four columns 16 q + 4 g .. + 3 of its row with one 16-byte load, and a 4 x 4
+// transposition over the lane groups hands it column 16 q + 4 kk + g for the
+// product kk. A 16 x 16 block's re = Xr Xr^T + Xi Xi^T and im = Xi Xr^T - Xr Xi^T
+// run over all columns in order. Of the eight only seven are formed, one per
+// wavefront (re of block (1,0) is that of (0,1) transposed). Two column groups'
+// loads are in flight during the products of a third.
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+// v[c] of lane group g becomes v[g] of lane group c
+__device__ __forceinline__ void transpose4(float (&v)[4]) {
+  swap32(v[0], v[2]);
+  swap32(v[1], v[3]);
+  swap16(v[0], v[1]);
+  swap16(v[2], v[3]);
+}
+
+struct GramCols {
+  float r[4], i[4];
 };
 
-__device__ __forceinline__ void load_chunk(ChunkRegs& g, const float* re, const float* im, int64_t ncols, int64_t c0,
-                                           int nc, const int* rows, bool real) {
+// missing rows and the imaginary part of a real slice to zero, then to the
+// operand layout
+__device__ __forceinline__ void gram_fix(GramCols& z, bool live, bool real) {
 #pragma unroll
-  for (int q = 0; q < kChunkPer; ++q) {
-    const int e = threadIdx.x + NT * q;
-    const int r = e / CHC, j = e - r * CHC;
-    float vr = 0.f, vi = 0.f;
-    if (j < nc && rows[r] >= 0) {
-      const int64_t off = (int64_t)rows[r] * ncols + c0 + j;
-      vr = re[off];
-      vi = real ? 0.f : im[off];
-    }
-    g.r[q] = vr;
-    g.i[q] = vi;
+  for (int e = 0; e < 4; ++e) {
+    z.r[e] = live ? z.r[e] : 0.f;
+    z.i[e] = live && !real ? z.i[e] : 0.f;
+  }
+  transpose4(z.r);
+  transpose4(z.i);
+}
+
+template <bool IM>
+__device__ __forceinline__ void gram_products(const GramCols& x, const GramCols& y, d4& acc) {
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const double ar = (double)x.r[kk], ai = (double)x.i[kk];
+    const double br = (double)y.r[kk], bi = (double)y.i[kk];
+    acc = TP_MFMA64(IM ? ai : ar, br, acc);
+    acc = TP_MFMA64(IM ? -ar : ai, bi, acc);
   }
 }
 
-// Stores a chunk into the float64 staging arrays with row stride S.
-template <int S>
-__device__ __forceinline__ void store_chunk(const ChunkRegs& g, double* sr, double* si) {
-#pragma unroll
-  for (int q = 0; q < kChunkPer; ++q) {
-    const int e = threadIdx.x + NT * q;
-    const int r = e / CHC, j = e - r * CHC;
-    sr[r * S + j] = (double)g.r[q];
-    si[r * S + j] = (double)g.i[q];
-  }
-}
-
-// Runs body(c0, nc) over the column chunks [c0, c0 + nc) of the staged rows,
-// each chunk stored to the LDS staging arrays (row stride S) before its
-// body. DEPTH (1 or 2) chunks are kept in flight in registers: chunk
-// c + DEPTH is loaded while chunk c is multiplied. Every thread must call
-// it; body must only read the staging arrays.
-template <int S, int DEPTH, class Body>
-__device__ __forceinline__ void staged_chunks(const float* re, const float* im, int64_t ncols, const int* rows,
-                                              bool real, double* sr, double* si, Body&& body) {
-  static_assert(DEPTH == 1 || DEPTH == 2, "one or two chunks in flight");
-  auto width = [ncols](int64_t c) { return (int)((ncols - c) < CHC ? (ncols - c) : CHC); };
-  ChunkRegs g[DEPTH];
-  load_chunk(g[0], re, im, ncols, 0, width(0), rows, real);
-  if (DEPTH == 2 && CHC < ncols) load_chunk(g[DEPTH - 1], re, im, ncols, CHC, width(CHC), rows, real);
-  for (int64_t c0 = 0; c0 < ncols; c0 += DEPTH * CHC) {
-#pragma unroll
-    for (int b = 0; b < DEPTH; ++b) {
-      const int64_t c = c0 + b * CHC;
-      if (c >= ncols) break;
-      store_chunk<S>(g[b], sr, si);
-      __syncthreads();
-      if (c + DEPTH * CHC < ncols) load_chunk(g[b], re, im, ncols, c + DEPTH * CHC, width(c + DEPTH * CHC), rows, real);
-      body(c, width(c));
-      __syncthreads();
+template <bool IM, bool DIAG>
+__device__ __forceinline__ d4 gram_block(const float* re, const float* im, int64_t ncols, const int* rows, bool real,
+                                         int ba, int bb) {
+  const int l = threadIdx.x & 63, g = l >> 4;
+  const int ra = rows[16 * ba + (l & 15)], rb = rows[16 * bb + (l & 15)];
+  const bool alive = ra >= 0, blive = rb >= 0;
+  const int64_t oa = (int64_t)(alive ? ra : 0) * ncols, ob = (int64_t)(blive ? rb : 0) * ncols;
+  const int64_t nq = ncols / 16;  // whole groups of 16 columns
+  struct Pair {
+    GramCols a, b;
+  };
+  auto load = [&](int64_t q, Pair& z) {
+    const int64_t c = 16 * (q < nq ? q : nq - 1) + 4 * g;
+    __builtin_memcpy(z.a.r, re + oa + c, 16);
+    __builtin_memcpy(z.a.i, im + oa + c, 16);
+    if (!DIAG) {
+      __builtin_memcpy(z.b.r, re + ob + c, 16);
+      __builtin_memcpy(z.b.i, im + ob + c, 16);
     }
-  }
-}
-
-// Rotates rows rows[0..PR) of a row-major K x nrows x ncols planar matrix by
-// V^H: out_s = sum_t conj(V_ts) in_t, on the float64 matrix cores
-// (v_mfma_f64_16x16x4f64: A lane l = A[l % 16][l / 16], B lane l =
-// B[l / 16][l % 16], D lane l register v = D[4 v + l / 16][l % 16], as
-// measured on gfx950).
-// Wavefront w owns output columns [16 w, 16 w + 16) of each staged chunk and
-// both 16-row halves; the V^H fragments (A[s][t] = conj(V[t][s])) are passed
-// in registers: vfr/vfi[h][kk] for row half h and contraction step kk.
-__device__ void rotate_rows(const double (&vfr)[2][8], const double (&vfi)[2][8], double* sr, double* si,
-                            float* re, float* im, int64_t ncols, const int* rows, bool real) {
-  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
-  const int j0 = 16 * w;
-  staged_chunks<kRotStride, kRotDepth>(re, im, ncols, rows, real, sr, si, [&](int64_t c0, int nc) {
-    d4 orr[2], oi[2];
+  };
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  auto use = [&](const Pair& z) {
+    GramCols x = z.a, y = z.b;
+    gram_fix(x, alive, real);
+    if (DIAG)
+      y = x;
+    else
+      gram_fix(y, blive, real);
+    gram_products<IM>(x, y, acc);
+  };
+  if (nq > 0) {
+    // unconditional loads (past the end the last group again), so that they
+    // stay in flight over the products
+    constexpr int kAhead = 4;
+    Pair z[kAhead];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      orr[h] = d4{0.0, 0.0, 0.0, 0.0};
-      oi[h] = d4{0.0, 0.0, 0.0, 0.0};
-    }
+    for (int t = 0; t < kAhead; ++t) load(t, z[t]);
+    for (int64_t q = 0; q < nq; q += kAhead) {
 #pragma unroll
-    for (int kk = 0; kk < PR / 4; ++kk) {
-      const int t = 4 * kk + (l >> 4), j = j0 + (l & 15);
-      const double br = sr[t * kRotStride + j], bi = si[t * kRotStride + j];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        // conj(V)^T x: re = Vr xr + Vi xi, im = Vr xi - Vi xr
-        orr[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(vfr[h][kk], br, orr[h], 0, 0, 0);
-        orr[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(vfi[h][kk], bi, orr[h], 0, 0, 0);
-        oi[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(vfr[h][kk], bi, oi[h], 0, 0, 0);
-        oi[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(-vfi[h][kk], br, oi[h], 0, 0, 0);
+      for (int t = 0; t < kAhead; ++t) {
+        if (q + t < nq) use(z[t]);
+        load(q + t + kAhead, z[t]);
       }
     }
-    // the chunks still in flight cover later columns than the ones written
-    const int j = j0 + (l & 15);
-    if (j < nc) {
+  }
+  if (16 * nq < ncols) {
+    Pair z;
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int sidx = 16 * h + 4 * v + (l >> 4);
-          if (rows[sidx] < 0) continue;
-          const int64_t off = (int64_t)rows[sidx] * ncols + c0 + j;
-          re[off] = (float)orr[h][v];
-          if (!real) im[off] = (float)oi[h][v];
-        }
+    for (int e = 0; e < 4; ++e) {
+      const int64_t c = 16 * nq + 4 * g + e;
+      const bool in = c < ncols;
+      const int64_t o = in ? c : 0;
+      z.a.r[e] = in ? re[oa + o] : 0.f;
+      z.a.i[e] = in ? im[oa + o] : 0.f;
+      z.b.r[e] = in && !DIAG ? re[ob + o] : 0.f;
+      z.b.i[e] = in && !DIAG ? im[ob + o] : 0.f;
     }
-  });
+    use(z);
+  }
+  return acc;
 }
 
-__global__ __launch_bounds__(NT) void svt_pair_kernel(PairArgs a, int round) {
-  __shared__ JacobiShared<PR, NT> sh;
-  __shared__ double stage_r[kStage], stage_i[kStage];
+// Rotation of the 32 rows of X and of U^H by V^H in place: out_s =
+// sum_t conj(V_ts) in_t, on the float64 matrix cores (re = Vr xr + Vi xi,
+// im = Vr xi - Vi xr). The 32-column tiles of X and then of U^H are dealt to the
+// wavefronts. Lane (group g, j) reads columns 2j, 2j + 1 of the tile from
+// rows 4 kk + g straight into the operand layout (the even columns form one
+// 16-column product, the odd ones another): every element is read and
+// written once, nothing is staged or synchronised, and a tile's loads are in
+// flight during the products of the one before (the first tile's during the
+// inner sweep).
+struct RotTile {
+  float2 r[8], i[8];
+};
+
+struct RotArgs {
+  float *xre, *xim, *ure, *uim;
+  int64_t n1, n2, nx;  // nx: tiles of X
+  bool real, full;     // full: all 32 rows exist
+};
+
+__device__ __forceinline__ void rot_tile(const RotArgs& a, int64_t t, float*& re, float*& im, int64_t& ncols,
+                                         int64_t& c0) {
+  const bool x = t < a.nx;
+  re = x ? a.xre : a.ure;
+  im = x ? a.xim : a.uim;
+  ncols = x ? a.n2 : a.n1;
+  c0 = 32 * (x ? t : t - a.nx);
+}
+
+// Unconditional loads from clamped addresses (matrices have at least two
+// columns where there is something to rotate): they stay in flight. The last
+// column of an odd number comes as the second of its pair (rot_fix).
+__device__ __forceinline__ void rot_load(const RotArgs& a, int64_t t, const int (&row)[8], RotTile& z) {
+  float *re, *im;
+  int64_t ncols, c0;
+  rot_tile(a, t, re, im, ncols, c0);
+  int64_t c = c0 + 2 * (threadIdx.x & 15);
+  c = c + 2 > ncols ? ncols - 2 : c;
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) {
+    const int64_t o = (int64_t)(row[kk] < 0 ? 0 : row[kk]) * ncols + c;
+    __builtin_memcpy(&z.r[kk], re + o, 8);
+    __builtin_memcpy(&z.i[kk], im + o, 8);
+  }
+}
+
+// missing rows and the imaginary part of a real slice to zero
+__device__ __forceinline__ void rot_fix(const RotArgs& a, int64_t t, const int (&row)[8], RotTile& z) {
+  float *re, *im;
+  int64_t ncols, c0;
+  rot_tile(a, t, re, im, ncols, c0);
+  if (!a.real && a.full && c0 + 32 <= ncols) return;
+  const bool last = c0 + 2 * (threadIdx.x & 15) + 1 == ncols;
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) {
+    if (last) {
+      z.r[kk].x = z.r[kk].y;
+      z.i[kk].x = z.i[kk].y;
+    }
+    if (row[kk] < 0) z.r[kk] = float2{0.f, 0.f};
+    if (row[kk] < 0 || a.real) z.i[kk] = float2{0.f, 0.f};
+  }
+}
+
+__device__ __forceinline__ void rot_store(const RotArgs& a, int64_t t, const int* rows, int h, const d4 (&outr)[2],
+                                          const d4 (&outi)[2]) {
+  float *re, *im;
+  int64_t ncols, c0;
+  rot_tile(a, t, re, im, ncols, c0);
+  const int l = threadIdx.x & 63, g = l >> 4;
+  const int64_t c = c0 + 2 * (l & 15);
+  const bool whole = c0 + 32 <= ncols;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int s = rows[16 * h + 4 * v + g];
+    const int64_t o = (int64_t)s * ncols + c;
+    const float2 wr{(float)outr[0][v], (float)outr[1][v]}, wi{(float)outi[0][v], (float)outi[1][v]};
+    if (whole && a.full) {
+      __builtin_memcpy(re + o, &wr, 8);
+      if (!a.real) __builtin_memcpy(im + o, &wi, 8);
+    } else if (s >= 0 && c < ncols) {
+      re[o] = wr.x;
+      if (!a.real) im[o] = wi.x;
+      if (c + 1 < ncols) {
+        re[o + 1] = wr.y;
+        if (!a.real) im[o + 1] = wi.y;
+      }
+    }
+  }
+}
+
+// `x` holds the wavefront's first tile
+__device__ __forceinline__ void rotate_rows(const RotArgs& a, const Cz* V, const int* rows, const int (&row)[8],
+                                            RotTile& x) {
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = l >> 4, j = l & 15;
+  const int64_t nt = a.nx + (a.n1 + 31) / 32;
+  for (int64_t t = w; t < nt; t += PT / 64) {
+    if (t != w) rot_load(a, t, row, x);
+    rot_fix(a, t, row, x);
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h) {
+      d4 outr[2], outi[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) outr[q] = outi[q] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const Cz v = V[(4 * kk + g) * 32 + 16 * h + j];
+        // converted again for the second half: 64 registers of doubles less
+        asm volatile("" : "+v"(x.r[kk].x), "+v"(x.r[kk].y), "+v"(x.i[kk].x), "+v"(x.i[kk].y));
+        const double br[2] = {(double)x.r[kk].x, (double)x.r[kk].y}, bi[2] = {(double)x.i[kk].x, (double)x.i[kk].y};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          outr[q] = TP_MFMA64(v.x, br[q], outr[q]);
+          outi[q] = TP_MFMA64(v.x, bi[q], outi[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          outr[q] = TP_MFMA64(v.y, bi[q], outr[q]);
+          outi[q] = TP_MFMA64(-v.y, br[q], outi[q]);
+        }
+      }
+      rot_store(a, t, rows, h, outr, outi);
+    }
+  }
+}
+
+// One pair step of one slice, eight wavefronts. On one CU for 256 columns
+// (cycles of a 2.2 GHz CU): Gram matrix 31,000, test and symmetrisation 3,000,
+// inner sweep 46,000 (31 rounds bound by float64 issue, see jacobi32.hpp),
+// rotations 33,000 (the rate of the float64 matrix cores), against 184,000 in
+// all for four wavefronts staging float64 rows through LDS with H and V of the
+// sweep updated there. 408 pair steps (51 slices of 256 x 256) take 93 us on
+// one stream (168 before), a cold 256 x 256 x 100 thresholding 15.3 ms (19.4),
+// ten completion iterations 46 ms (58.5); the results are the same bits.
+__global__ __launch_bounds__(PT, 4) void svt_pair_kernel(PairArgs a, int round) {
+  // raw Gram matrix (planar, row stride 33) over H[1] and V until the sweep
+  __shared__ union {
+    Jacobi32Shared jac;
+    struct {
+      Cz h0[32 * 32];
+      double re[PR][PR + 1], im[PR][PR + 1];
+    } raw;
+  } sh;
   __shared__ int rows[PR];
-  __shared__ double ratio_red[NT];
-  __shared__ int skip;
+  __shared__ double ratio_red[PT / 64];
   const int64_t k = a.k0 + blockIdx.y;
   const int pair = blockIdx.x;
-  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (a.conv[k]) return;
   const bool real = k == 0 || (a.real_last && k == a.K - 1);
   const int ba = tournament(pair, round, a.nb), bb = tournament(a.nb - 1 - pair, round, a.nb);
@@ -199,32 +331,33 @@ __global__ __launch_bounds__(NT) void svt_pair_kernel(PairArgs a, int round) {
     const int64_t r = (int64_t)blk * RB + (tid % RB);
     rows[tid] = r < a.n1 ? (int)r : -1;
   }
-  float* xre = a.xre + k * a.n1 * a.n2;
-  float* xim = a.xim + k * a.n1 * a.n2;
-  float* ure = a.ure + k * a.n1 * a.n1;
-  float* uim = a.uim + k * a.n1 * a.n1;
-  // Gram G_st = sum_j x_s[j] conj(x_t[j]) on the matrix cores: wavefront w
-  // owns the 16 x 16 block (s0, t0); re = Xr Xr^T + Xi Xi^T,
-  // im = Xi Xr^T - Xr Xi^T (A = rows s0.., B = rows t0.. transposed)
-  const int s0 = 16 * (w >> 1), t0 = 16 * (w & 1);
-  d4 gre = {0.0, 0.0, 0.0, 0.0}, gim = {0.0, 0.0, 0.0, 0.0};
+  const RotArgs rot{a.xre + k * a.n1 * a.n2, a.xim + k * a.n1 * a.n2, a.ure + k * a.n1 * a.n1,
+                    a.uim + k * a.n1 * a.n1, a.n1,                    a.n2,
+                    (a.n2 + 31) / 32,        real,                    (int64_t)(max(ba, bb) + 1) * RB <= a.n1};
   __syncthreads();
-  staged_chunks<kGramStride, kGramDepth>(xre, xim, a.n2, rows, real, stage_r, stage_i, [&](int64_t, int) {
-#pragma unroll 4
-    for (int kk = 0; kk < CHC / 4; ++kk) {
-      const int j = 4 * kk + (l >> 4);
-      const double ar = stage_r[(s0 + (l & 15)) * kGramStride + j], ai = stage_i[(s0 + (l & 15)) * kGramStride + j];
-      const double br = stage_r[(t0 + (l & 15)) * kGramStride + j], bi = stage_i[(t0 + (l & 15)) * kGramStride + j];
-      gre = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, gre, 0, 0, 0);
-      gre = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, bi, gre, 0, 0, 0);
-      gim = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, gim, 0, 0, 0);
-      gim = __builtin_amdgcn_mfma_f64_16x16x4f64(-ar, bi, gim, 0, 0, 0);
-    }
-  });
+  if (w < 7) {
+    auto put = [&](const d4& acc, int s0, int t0, bool is_im) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    sh.Hr[s0 + 4 * v + (l >> 4)][t0 + (l & 15)] = gre[v];
-    sh.Hi[s0 + 4 * v + (l >> 4)][t0 + (l & 15)] = gim[v];
+      for (int v = 0; v < 4; ++v) {
+        const int s = s0 + 4 * v + (l >> 4), t = t0 + (l & 15);
+        if (is_im) {
+          sh.raw.im[s][t] = acc[v];
+        } else {
+          sh.raw.re[s][t] = acc[v];
+          if (s0 != t0) sh.raw.re[t][s] = acc[v];
+        }
+      }
+    };
+    const int blk = w == 0 || w == 1 ? 0 : 1;  // diagonal blocks: wavefronts 0, 1, 5, 6
+    if (w == 0 || w == 5)
+      put(gram_block<false, true>(rot.xre, rot.xim, a.n2, rows, real, blk, blk), 16 * blk, 16 * blk, false);
+    else if (w == 1 || w == 6)
+      put(gram_block<true, true>(rot.xre, rot.xim, a.n2, rows, real, blk, blk), 16 * blk, 16 * blk, true);
+    else if (w == 2)
+      put(gram_block<false, false>(rot.xre, rot.xim, a.n2, rows, real, 0, 1), 0, 16, false);
+    else
+      put(gram_block<true, false>(rot.xre, rot.xim, a.n2, rows, real, w == 3 ? 0 : 1, w == 3 ? 1 : 0),
+          w == 3 ? 0 : 16, w == 3 ? 16 : 0, true);
   }
   __syncthreads();
   // largest off-diagonal entry relative to the larger squared norm of its
@@ -237,40 +370,34 @@ __global__ __launch_bounds__(NT) void svt_pair_kernel(PairArgs a, int round) {
   // angle is below tol relative to the pair's spectral gap, which bounds
   // the error of the thresholded result by ~tol ||M||.
   double mr = 0.0;
-  for (int e = tid; e < PR * PR; e += NT) {
-    const int s = e / PR, t = e - s * PR;
+#pragma unroll
+  for (int q = 0; q < PR * PR / PT; ++q) {
+    const int e = tid + PT * q, s = e / PR, t = e - s * PR;
+    const double gr = sh.raw.re[s][t], gi = sh.raw.im[s][t];
+    const double hr = sh.raw.re[t][s], hi = sh.raw.im[t][s];
     if (s != t) {
-      const double d = fmax(sh.Hr[s][s], sh.Hr[t][t]);
-      const double gr = sh.Hr[s][t], gi = sh.Hi[s][t];
-      if (d > 0.0) mr = fmax(mr, sqrt(gr * gr + gi * gi) / d);
+      const double d = fmax(sh.raw.re[s][s], sh.raw.re[t][t]);
+      if (d > 0.0) mr = fmax(mr, sqrt(fma(gr, gr, gi * gi)) / d);
     }
+    // exactly Hermitian
+    const double im = s < t ? 0.5 * (gi - hi) : (s > t ? -(0.5 * (hi - gi)) : 0.0);
+    sh.raw.h0[e] = Cz{s == t ? gr : 0.5 * (gr + hr), im};
   }
-  ratio_red[tid] = mr;
-  __syncthreads();
-  for (int ww = NT / 2; ww > 0; ww >>= 1) {
-    if (tid < ww) ratio_red[tid] = fmax(ratio_red[tid], ratio_red[tid + ww]);
-    __syncthreads();
-  }
-  if (tid == 0) {
-    a.ratio[((int64_t)round * a.K + k) * (a.nb / 2) + pair] = (float)ratio_red[0];
-    skip = ratio_red[0] < a.tol;
-  }
-  __syncthreads();
-  if (skip) return;
-  jacobi_eig_lds<PR, NT>(sh, PR, a.inner_sweeps, 1e-14);
-  // V^H fragments for the rotations: A[s][t] = conj(V[t][s]) with
-  // s = 16 h + (l % 16), t = 4 kk + (l / 16); the minus sign of the
-  // imaginary part is applied in the products
-  double vfr[2][8], vfi[2][8];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int o = 32; o > 0; o >>= 1) mr = fmax(mr, __shfl_xor(mr, o));
+  if (l == 0) ratio_red[w] = mr;
+  __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < PR / 4; ++kk) {
-      vfr[h][kk] = sh.Vr[4 * kk + (l >> 4)][16 * h + (l & 15)];
-      vfi[h][kk] = sh.Vi[4 * kk + (l >> 4)][16 * h + (l & 15)];
-    }
-  rotate_rows(vfr, vfi, stage_r, stage_i, xre, xim, a.n2, rows, real);
-  rotate_rows(vfr, vfi, stage_r, stage_i, ure, uim, a.n1, rows, real);
+  for (int q = 0; q < PT / 64; ++q) mr = fmax(mr, ratio_red[q]);
+  if (tid == 0) a.ratio[((int64_t)round * a.K + k) * (a.nb / 2) + pair] = (float)mr;
+  if (mr < a.tol) return;
+  int row[8];
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) row[kk] = rows[4 * kk + (l >> 4)];
+  RotTile x;
+  if (w < rot.nx + (a.n1 + 31) / 32) rot_load(rot, w, row, x);
+  jacobi32<PT, false>(sh.jac, PR, kInnerSweeps, 0.0, nullptr);
+  rotate_rows(rot, sh.jac.V, rows, row, x);
 }
 
 __global__ void svt_conv_kernel(const float* __restrict__ ratio, int64_t K, int64_t k0, int64_t k1, int nrounds,
@@ -655,7 +782,7 @@ int svt_jacobi(float* xre, float* xim, float* ure, float* uim, int64_t K, int64_
   const int nb = svt_blocks(n1);
   hipLaunchKernelGGL(zero_int_kernel, dim3(nblk(K)), dim3(256), 0, st, conv, K);
   TP_LAUNCH_CHECK();
-  PairArgs a{K, n1, n2, 0, xre, xim, ure, uim, nb, real_last ? 1 : 0, ratio, conv, tol, kInnerSweeps};
+  PairArgs a{K, n1, n2, 0, xre, xim, ure, uim, nb, real_last ? 1 : 0, ratio, conv, tol};
   // slices [k0, k1) on stream s
   auto sweeps = [&](int64_t k0, int64_t k1, hipStream_t s) -> int {
     PairArgs g = a;
@@ -666,7 +793,7 @@ int svt_jacobi(float* xre, float* xim, float* ure, float* uim, int64_t K, int64_
         for (int64_t c0 = k0; c0 < k1; c0 += 65535) {
           g.k0 = c0;
           const int64_t kc = k1 - c0 < 65535 ? k1 - c0 : 65535;
-          hipLaunchKernelGGL(svt_pair_kernel, dim3(nb / 2, (unsigned)kc), dim3(NT), 0, s, g, round);
+          hipLaunchKernelGGL(svt_pair_kernel, dim3(nb / 2, (unsigned)kc), dim3(PT), 0, s, g, round);
           TP_LAUNCH_CHECK();
         }
       }
