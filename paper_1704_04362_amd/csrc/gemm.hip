@@ -5,10 +5,11 @@
 // is an independent product C_k = op(A_k) op(B_k); slices 0 and, for even
 // tube length, the Nyquist slice are real and skip the imaginary work.
 //
-// This file holds the general kernel (any op, any size, float or double,
-// LDS-tiled on the vector ALUs) and the dispatch. The matrix-core kernels
-// live in gemm_f32.hip (float32 arithmetic), gemm_mfma.hip (split bf16),
-// gemm_short.hip (short contractions) and gemm_tall.hip (narrow results).
+// This file holds the general float32 kernel (any op, any size, LDS-tiled on
+// the vector ALUs) and the dispatch. The matrix-core kernels live in
+// gemm_f64.hip (float64), gemm_f32.hip (float32 arithmetic), gemm_mfma.hip
+// (split bf16), gemm_short.hip (short contractions) and gemm_tall.hip (narrow
+// results).
 #include <algorithm>
 
 #include "common.hpp"
@@ -18,6 +19,7 @@ int cgemm_mfma(const CGemm& p, int prec, hipStream_t st, bool* handled);
 int cgemm_short(const CGemm& p, int split, hipStream_t st, bool* handled);
 int cgemm_tall(const CGemm& p, int split, hipStream_t st, bool* handled);
 int cgemm_f32mfma(const CGemm& p, hipStream_t st, bool* handled);
+int cgemm_f64mfma(const CGemm& p, hipStream_t st);
 
 namespace {
 
@@ -232,7 +234,8 @@ int cgemm(const CGemm& p, int dtype, int prec, hipStream_t st) {
     }
     return TP_OK;
   }
-  if (dtype == TP_F32 && (prec == TP_PREC_F32 || prec == TP_PREC_BF16X3)) {
+  if (dtype == TP_F64) return cgemm_f64mfma(p, st);
+  if (prec == TP_PREC_F32 || prec == TP_PREC_BF16X3) {
     const int split = prec == TP_PREC_BF16X3 ? 1 : 0;
     bool handled = false;
     // narrow results with a long contraction (range-finder products)
@@ -242,13 +245,13 @@ int cgemm(const CGemm& p, int dtype, int prec, hipStream_t st) {
     if (int rc = cgemm_short(p, split, st, &handled)) return rc;
     if (handled) return TP_OK;
   }
-  if (dtype == TP_F32 && prec == TP_PREC_F32) {
+  if (prec == TP_PREC_F32) {
     // large float32 products on the float32 matrix cores
     bool handled = false;
     if (int rc = cgemm_f32mfma(p, st, &handled)) return rc;
     if (handled) return TP_OK;
   }
-  if (dtype == TP_F32 && prec != TP_PREC_F64) {
+  {
     bool handled = false;
     if (int rc = cgemm_mfma(p, prec, st, &handled)) return rc;
     if (handled) return TP_OK;
@@ -259,17 +262,10 @@ int cgemm(const CGemm& p, int dtype, int prec, hipStream_t st) {
   const bool narrow = p.N <= 32;
   const int64_t bm = narrow ? 128 : 64, bn = narrow ? 32 : 64;
   dim3 grid((unsigned)((p.N + bn - 1) / bn), (unsigned)((p.M + bm - 1) / bm), (unsigned)p.K);
-  if (dtype == TP_F64) {
-    if (narrow)
-      hipLaunchKernelGGL((cgemm_simt_kernel<double, 128, 32>), grid, dim3(NT), 0, st, g);
-    else
-      hipLaunchKernelGGL((cgemm_simt_kernel<double, 64, 64>), grid, dim3(NT), 0, st, g);
-  } else {
-    if (narrow)
-      hipLaunchKernelGGL((cgemm_simt_kernel<float, 128, 32>), grid, dim3(NT), 0, st, g);
-    else
-      hipLaunchKernelGGL((cgemm_simt_kernel<float, 64, 64>), grid, dim3(NT), 0, st, g);
-  }
+  if (narrow)
+    hipLaunchKernelGGL((cgemm_simt_kernel<float, 128, 32>), grid, dim3(NT), 0, st, g);
+  else
+    hipLaunchKernelGGL((cgemm_simt_kernel<float, 64, 64>), grid, dim3(NT), 0, st, g);
   TP_LAUNCH_CHECK();
   return TP_OK;
 }
