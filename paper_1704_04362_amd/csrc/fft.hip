@@ -577,570 +577,8 @@ __global__ void irdft_direct_kernel(const T* __restrict__ xre, const T* __restri
   }
 }
 
-constexpr int kLongMaxStages = 24;
-constexpr int kLongMaxRadix = 13;
+// shortest length that the four-step transform takes
 constexpr int64_t kLongMin = 257;
-
-struct LongPlan {
-  int n, nst;
-  int rad[kLongMaxStages];
-};
-
-// source index of the element that the digit-reversed load puts at pos
-__device__ __forceinline__ int long_src(const LongPlan& pl, int pos) {
-  int out = 0, m = pl.n;
-  for (int q = 0; q < pl.nst; ++q) {
-    const int p = pl.rad[q];
-    m /= p;
-    out += (pos % p) * m;
-    pos /= p;
-  }
-  return out;
-}
-
-// --------------------------------------------------------------------------
-// Tubes beyond the LDS budget: a four-step transform through HBM, with the
-// caller's output as the only intermediate storage. The real tube x of even
-// length n is packed as z[m] = x[2m] + i x[2m+1], m < N = n/2, and with
-// N = N1 N2, m = j1 + N1 j2, k = k2 + N2 k1 its DFT factors as
-//   Z[k2 + N2 k1] = sum_j1 W_N1^{j1 k1} W_N^{j1 k2} sum_j2 z[j1 + N1 j2] W_N2^{j2 k2}
-// (W_L = exp(-2 pi i / L)). Forward:
-//   tube pass: per tube and j1 the inner length-N2 transform over j2 and the
-//     twiddle W_N^{j1 k2}, written to spectrum slice k2 + N2 j1 of that
-//     tube's slot;
-//   slice pass: per slot block and pair {k2, N2 - k2} the outer length-N1
-//     transforms over j1 (the partner Z[N - k] of every Z[k] of the pair is
-//     in the pair), then X[k] = E[k] + W_n^k O[k] for k <= N, with
-//     E[k] = (Z[k] + conj Z[N-k]) / 2, O[k] = (Z[k] - conj Z[N-k]) / 2i, written
-//     to slice k: exactly the slices the pair's intermediate values occupy, so
-//     each workgroup overwrites only what it has read.
-// Inverse (the steps reversed, conjugated, into the output tensor):
-//   slice pass: per slot block and k2, Z[k] = E[k] + i O[k] from the half
-//     spectrum (E = (X[k] + conj X[N-k]) / 2, O = (X[k] - conj X[N-k]) W_n^-k / 2),
-//     the inverse transform over k1 and the twiddle W_N^{-j1 k2}, written
-//     into the tube at packed position j1 + N1 k2;
-//   tube pass: per tube and j1 the inverse transform over k2, 1/N, and the
-//     real and imaginary parts as x[2m], x[2m+1] at the positions it read.
-// Both short transforms run in LDS as the mixed-radix stages above, several
-// sequences per workgroup (FsGeom: slots x j1 values of length N2 <= 256 in
-// the tube pass, slots x the pair of length N1 <= 1024 in the slice pass, at
-// most 64 KB of LDS), so tubes up to n = 2 x 256 x 1024 with no prime factor
-// above 13 take this path; longer or other lengths beyond the LDS budget
-// take the direct transform.
-// --------------------------------------------------------------------------
-constexpr int kFsMaxN2 = 256, kFsMaxN1 = 1024, kFsNT = 512;
-constexpr int kFsBatch = 8;  // elements whose loads a thread keeps in flight
-
-template <typename T>
-struct FsGeom;
-template <>
-struct FsGeom<float> {
-  static constexpr int tubes = 8, j1s = 4, stubes = 4;  // tube pass: 8 slots x 4 j1; slice pass: 4 slots
-};
-template <>
-struct FsGeom<double> {
-  static constexpr int tubes = 4, j1s = 4, stubes = 2;
-};
-
-struct FourStep {
-  int N1, N2;
-  LongPlan p1, p2;  // radix plans of lengths N1 and N2
-};
-
-// Launch order. Workgroup L runs on XCD L mod 8, each XCD with its own L2;
-// the logical index (L mod 8) q + L / 8 (q = ceil(total / 8)) gives every XCD
-// a contiguous range of logical work, so the workgroups that share cache
-// lines (neighbouring slots, neighbouring j1) run together on one XCD.
-// Returns false for the padding beyond `total`.
-__device__ __forceinline__ bool fs_logical(int64_t total, int64_t& G) {
-  const int64_t L = blockIdx.x, q = (total + 7) / 8;
-  G = (L % 8) * q + L / 8;
-  return G < total;
-}
-
-// tube passes: 4 x 4 groups of (slot block, j1 block), j1 groups fastest,
-// so that reads (contiguous in j1) and writes (contiguous in slots) both
-// share lines within a group
-__device__ __forceinline__ bool fs_tube_block(int64_t nslot_blocks, int64_t nj_blocks, int64_t& sb, int64_t& jb) {
-  const int64_t ngj = (nj_blocks + 3) / 4, ngs = (nslot_blocks + 3) / 4;
-  int64_t G;
-  if (!fs_logical(ngj * ngs * 16, G)) return false;
-  const int64_t g = G / 16, w = G % 16;
-  jb = (g % ngj) * 4 + (w % 4);
-  sb = (g / ngj) * 4 + (w / 4);
-  return jb < nj_blocks && sb < nslot_blocks;
-}
-
-// sincospi in the arithmetic of the data (float tubes take float roots:
-// their rounding is that of the data)
-__device__ __forceinline__ void fs_sincospi(float x, float* s, float* c) { sincospif(x, s, c); }
-__device__ __forceinline__ void fs_sincospi(double x, double* s, double* c) { sincospi(x, s, c); }
-
-// One radix-P butterfly of a decimation-in-time stage of span m P: the P
-// inputs a[base + t m] take the twiddle W_{mP}^{j t} (j t < m P) and go through
-// a P-point DFT with roots (cw, sw); P is a compile-time constant, so the DFT
-// is fully unrolled with its root indices folded.
-template <int P, typename T>
-__device__ __forceinline__ void fs_bfly(T* ar, T* ai, int base, int m, int j, int span, const T* cw, const T* sw) {
-  T vr[P], vi[P];
-  vr[0] = ar[base];
-  vi[0] = ai[base];
-#pragma unroll
-  for (int t = 1; t < P; ++t) {
-    const T xr = ar[base + t * m], xi = ai[base + t * m];
-    T sn, cs;
-    fs_sincospi(T(-2) * T(j * t) / T(span), &sn, &cs);
-    vr[t] = xr * cs - xi * sn;
-    vi[t] = xr * sn + xi * cs;
-  }
-#pragma unroll
-  for (int t = 0; t < P; ++t) {
-    T accr = vr[0], acci = vi[0];
-#pragma unroll
-    for (int u = 1; u < P; ++u) {
-      const int e = (u * t) % P;
-      accr += vr[u] * cw[e] - vi[u] * sw[e];
-      acci += vr[u] * sw[e] + vi[u] * cw[e];
-    }
-    ar[base + t * m] = accr;
-    ai[base + t * m] = acci;
-  }
-}
-
-// mixed-radix stages of `nseq` sequences of length pl.n, sequence s at
-// offset s * pl.n (loaded in digit-reversed order), in the data's precision
-template <typename T>
-__device__ void multi_stages(const LongPlan& pl, T* ar, T* ai, int nseq) {
-  const int n = pl.n;
-  int m = 1;
-  for (int q = 0; q < pl.nst; ++q) {
-    const int p = pl.rad[q], span = m * p, per = n / p;
-    T cw[kLongMaxRadix], sw[kLongMaxRadix];
-#pragma unroll
-    for (int e = 0; e < kLongMaxRadix; ++e) {
-      cw[e] = T(1);
-      sw[e] = T(0);
-      if (e < p) fs_sincospi(T(-2) * T(e) / T(p), &sw[e], &cw[e]);
-    }
-    for (int b = threadIdx.x; b < nseq * per; b += kFsNT) {
-      const int sq = b / per, bb = b - sq * per;
-      const int bm = bb / m, j = bb - bm * m;
-      const int base = sq * n + bm * span + j;
-      switch (p) {
-        case 2: fs_bfly<2, T>(ar, ai, base, m, j, span, cw, sw); break;
-        case 3: fs_bfly<3, T>(ar, ai, base, m, j, span, cw, sw); break;
-        case 4: fs_bfly<4, T>(ar, ai, base, m, j, span, cw, sw); break;
-        case 5: fs_bfly<5, T>(ar, ai, base, m, j, span, cw, sw); break;
-        case 7: fs_bfly<7, T>(ar, ai, base, m, j, span, cw, sw); break;
-        case 11: fs_bfly<11, T>(ar, ai, base, m, j, span, cw, sw); break;
-        default: fs_bfly<13, T>(ar, ai, base, m, j, span, cw, sw); break;
-      }
-    }
-    __syncthreads();
-    m = span;
-  }
-}
-
-// position at which the digit-reversed load puts source index src (the
-// inverse of long_src)
-__device__ __forceinline__ int long_dst(const LongPlan& pl, int src) {
-  int pos = 0, w = 1;
-  int digits[kLongMaxStages];
-  for (int q = pl.nst - 1; q >= 0; --q) {
-    digits[q] = src % pl.rad[q];
-    src /= pl.rad[q];
-  }
-  for (int q = 0; q < pl.nst; ++q) {
-    pos += digits[q] * w;
-    w *= pl.rad[q];
-  }
-  return pos;
-}
-
-// exp(-2 pi i e / L) for 0 <= e < L
-__device__ __forceinline__ void fs_root(int e, int L, double& c, double& s) {
-  sincospi(-2.0 * (double)e / (double)L, &s, &c);
-}
-
-// forward tube pass: workgroup (slot block, j1 block)
-template <typename T>
-__global__ __launch_bounds__(kFsNT) void fs_fwd_tube_kernel(const T* __restrict__ x, FwdArgs a, FourStep fs,
-                                                            T* __restrict__ ore, T* __restrict__ oim) {
-  constexpr int TB = FsGeom<T>::tubes, JB = FsGeom<T>::j1s;
-  extern __shared__ unsigned char fs_lds[];
-  const int N1 = fs.N1, N2 = fs.N2, N = N1 * N2;
-  T* ar = reinterpret_cast<T*>(fs_lds);
-  T* ai = ar + TB * JB * N2;
-  const int64_t ks = a.ntubes;
-  int64_t sbk, jbk;
-  if (!fs_tube_block((ks + TB - 1) / TB, (N1 + JB - 1) / JB, sbk, jbk)) return;
-  const int64_t t0 = sbk * TB;
-  const int j10 = (int)jbk * JB;
-  // input tube and scale of each slot of the block
-  __shared__ int64_t s_src[TB];
-  __shared__ double s_sc[TB];
-  if (threadIdx.x < TB) {
-    const int64_t t = t0 + threadIdx.x;
-    int64_t src = -1;
-    double sc = 1.0;
-    if (!(t < ks && tube_source(a, t, src, sc))) src = -1;
-    s_src[threadIdx.x] = src;
-    s_sc[threadIdx.x] = sc;
-  }
-  __syncthreads();
-  // sequence (tube u, j1 offset v) at (u JB + v) N2 holds z[j1 + N1 j2] at
-  // the digit-reversed position of j2; threads take consecutive j1 of one
-  // (tube, j2) (contiguous input runs), kFsBatch loads in flight per thread
-  // (indices first, then the batch's loads unconditionally from clamped
-  // addresses so that they all stay in flight, then the LDS stores)
-  const int total = TB * JB * N2;
-  for (int e0 = threadIdx.x; e0 < total; e0 += kFsBatch * kFsNT) {
-    int64_t off[kFsBatch];
-    double sc[kFsBatch];
-    int li[kFsBatch];
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      const int e = e0 + q * kFsNT;
-      off[q] = -1;
-      sc[q] = 1.0;
-      li[q] = -1;
-      if (e < total) {
-        const int v = e % JB, r = e / JB;
-        const int j2 = r % N2, u = r / N2;
-        const int j1 = j10 + v;
-        li[q] = (u * JB + v) * N2 + long_dst(fs.p2, j2);
-        const int64_t src = s_src[u];
-        if (src >= 0 && j1 < N1) {
-          off[q] = src * (int64_t)(2 * N) + 2 * ((int64_t)j1 + (int64_t)N1 * j2);
-          sc[q] = s_sc[u];
-        }
-      }
-    }
-    T vr[kFsBatch], vi[kFsBatch];
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      const int64_t o = off[q] < 0 ? 0 : off[q];
-      vr[q] = x[o];
-      vi[q] = x[o + 1];
-    }
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      if (li[q] < 0) continue;
-      const bool ok = off[q] >= 0;
-      ar[li[q]] = !ok ? T(0) : (sc[q] == 1.0) ? vr[q] : (T)((double)vr[q] * sc[q]);
-      ai[li[q]] = !ok ? T(0) : (sc[q] == 1.0) ? vi[q] : (T)((double)vi[q] * sc[q]);
-    }
-  }
-  __syncthreads();
-  multi_stages<T>(fs.p2, ar, ai, TB * JB);
-  // twiddle W_N^{j1 k2}; value (t, j1, k2) goes to slice k2 + N2 j1 of slot t
-  for (int e = threadIdx.x; e < TB * JB * N2; e += kFsNT) {
-    const int k2 = e / (TB * JB), r = e - k2 * (TB * JB);
-    const int v = r / TB, u = r - v * TB;  // slots fastest: neighbouring stores
-    const int64_t t = t0 + u;
-    const int j1 = j10 + v;
-    if (t >= ks || j1 >= N1) continue;
-    const int li = (u * JB + v) * N2 + k2;
-    double c, sn;
-    fs_root((int)((unsigned)(j1 * k2) % (unsigned)N), N, c, sn);  // j1 k2 < 2^18
-    const double xr = (double)ar[li], xi = (double)ai[li];
-    const int64_t o = ((int64_t)k2 + (int64_t)N2 * j1) * ks + t;
-    ore[o] = (T)(xr * c - xi * sn);
-    oim[o] = (T)(xr * sn + xi * c);
-  }
-}
-
-// forward slice pass: workgroup (slot block, pair {k2, N2 - k2})
-template <typename T>
-__global__ __launch_bounds__(kFsNT) void fs_fwd_slice_kernel(FourStep fs, int64_t ks, T* __restrict__ ore,
-                                                             T* __restrict__ oim) {
-  constexpr int TB = FsGeom<T>::stubes;
-  extern __shared__ unsigned char fs_lds[];
-  const int N1 = fs.N1, N2 = fs.N2, N = N1 * N2;
-  T* ar = reinterpret_cast<T*>(fs_lds);
-  T* ai = ar + 2 * TB * N1;
-  const int64_t nsb = (ks + TB - 1) / TB;
-  int64_t G;
-  if (!fs_logical(nsb * (N2 / 2 + 1), G)) return;
-  const int64_t t0 = (G % nsb) * TB;  // slot blocks fastest
-  const int ka = (int)(G / nsb), kb = (N2 - ka) % N2;
-  const int nk = ka == kb ? 1 : 2;
-  // sequence (h, u) at (h TB + u) N1 holds the values of slice k2 = (ka, kb)[h]
-  // of slot t0 + u, position pos holding j1 = long_src(pos); kFsBatch loads
-  // in flight per thread
-  const int total = nk * TB * N1;
-  for (int e0 = threadIdx.x; e0 < total; e0 += kFsBatch * kFsNT) {
-    int64_t off[kFsBatch];
-    int li[kFsBatch];
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      const int e = e0 + q * kFsNT;
-      off[q] = -1;
-      li[q] = -1;
-      if (e < total) {
-        const int pos = e / (nk * TB), r = e - pos * (nk * TB);
-        const int h = r / TB, u = r - h * TB;
-        const int64_t t = t0 + u;
-        li[q] = (h * TB + u) * N1 + pos;
-        if (t < ks) off[q] = ((int64_t)(h ? kb : ka) + (int64_t)N2 * long_src(fs.p1, pos)) * ks + t;
-      }
-    }
-    T vr[kFsBatch], vi[kFsBatch];
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      const int64_t o = off[q] < 0 ? 0 : off[q];
-      vr[q] = ore[o];
-      vi[q] = oim[o];
-    }
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      if (li[q] < 0) continue;
-      ar[li[q]] = off[q] < 0 ? T(0) : vr[q];
-      ai[li[q]] = off[q] < 0 ? T(0) : vi[q];
-    }
-  }
-  __syncthreads();
-  multi_stages<T>(fs.p1, ar, ai, nk * TB);
-  // X[k] = E[k] + W_n^k O[k] for the k of this pair (and k = N with k2 = 0)
-  const int n = 2 * N;
-  const int nout = nk * N1 + (ka == 0 ? 1 : 0);
-  for (int e = threadIdx.x; e < nout * TB; e += kFsNT) {
-    const int q = e / TB, u = e - q * TB;
-    const int64_t t = t0 + u;
-    if (t >= ks) continue;
-    // the q-th output of the pair: slice (ka, kb)[q / N1] + N2 (q mod N1), or N
-    const int k = q < nk * N1 ? (q < N1 ? ka : kb) + N2 * (q % N1) : N;
-    // Z[k mod N] and Z[(N - k) mod N], both among the pair's sequences
-    const int kk = k % N, km = (N - kk) % N;
-    const int ha = kk % N2 == ka ? 0 : 1, hb = km % N2 == ka ? 0 : 1;
-    const int ia = (ha * TB + u) * N1 + kk / N2, ib = (hb * TB + u) * N1 + km / N2;
-    const double zr = (double)ar[ia], zi = (double)ai[ia];
-    const double wr = (double)ar[ib], wi = -(double)ai[ib];  // conj Z[N - k]
-    const double er = 0.5 * (zr + wr), ei = 0.5 * (zi + wi);
-    const double orr = 0.5 * (zi - wi), oi = -0.5 * (zr - wr);  // (Z - conj Z[N-k]) / 2i
-    double c, sn;
-    fs_root(k, n, c, sn);
-    const double xr = er + (orr * c - oi * sn);
-    const double xi = (k == 0 || k == N) ? 0.0 : ei + (orr * sn + oi * c);
-    const int64_t o = (int64_t)k * ks + t;
-    ore[o] = (T)xr;
-    oim[o] = (T)xi;
-  }
-}
-
-// inverse slice pass: workgroup (slot block, k2)
-template <typename T>
-__global__ __launch_bounds__(kFsNT) void fs_inv_slice_kernel(const T* __restrict__ xre, const T* __restrict__ xim,
-                                                             int64_t ntubes, FourStep fs, T* __restrict__ y) {
-  constexpr int TB = FsGeom<T>::stubes;
-  extern __shared__ unsigned char fs_lds[];
-  const int N1 = fs.N1, N2 = fs.N2, N = N1 * N2, n = 2 * N;
-  T* ar = reinterpret_cast<T*>(fs_lds);
-  T* ai = ar + TB * N1;
-  const int64_t nsb = (ntubes + TB - 1) / TB;
-  int64_t G;
-  if (!fs_logical(nsb * N2, G)) return;
-  const int64_t t0 = (G % nsb) * TB;  // slot blocks fastest
-  const int k2 = (int)(G / nsb);
-  // conj Z[k2 + N2 k1] at position pos of sequence u (k1 = long_src(pos)):
-  // the forward stages of the conjugate give the conjugate of the inverse;
-  // kFsBatch elements' loads in flight per thread
-  const int total = TB * N1;
-  for (int e0 = threadIdx.x; e0 < total; e0 += kFsBatch * kFsNT) {
-    int64_t oa[kFsBatch], ob[kFsBatch];
-    int kq[kFsBatch], li[kFsBatch];
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      const int e = e0 + q * kFsNT;
-      oa[q] = ob[q] = 0;
-      kq[q] = -1;
-      li[q] = -1;
-      if (e < total) {
-        const int pos = e / TB, u = e - pos * TB;
-        const int64_t t = t0 + u;
-        li[q] = u * N1 + pos;
-        if (t < ntubes) {
-          const int k = k2 + N2 * long_src(fs.p1, pos);
-          kq[q] = k;
-          oa[q] = (int64_t)k * ntubes + t;
-          ob[q] = (int64_t)(N - k) * ntubes + t;  // 1 <= N - k <= N
-        }
-      }
-    }
-    T ar0[kFsBatch], ai0[kFsBatch], br0[kFsBatch], bi0[kFsBatch];
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      ar0[q] = xre[oa[q]];
-      ai0[q] = xim[oa[q]];
-      br0[q] = xre[ob[q]];
-      bi0[q] = xim[ob[q]];
-    }
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      if (li[q] < 0) continue;
-      T vr = T(0), vi = T(0);
-      const int k = kq[q];
-      if (k >= 0) {
-        const double xr = (double)ar0[q], xi = k == 0 ? 0.0 : (double)ai0[q];
-        const double yr = (double)br0[q], yi = (N - k) == N ? 0.0 : -(double)bi0[q];  // conj X[N-k]
-        const double er = 0.5 * (xr + yr), ei = 0.5 * (xi + yi);
-        const double dr = 0.5 * (xr - yr), di = 0.5 * (xi - yi);
-        double c, sn;
-        fs_root(k, n, c, sn);  // W_n^k; O = D conj(W_n^k)
-        const double orr = dr * c + di * sn, oi = di * c - dr * sn;
-        // Z = E + i O, conjugated
-        vr = (T)(er - oi);
-        vi = (T)(-(ei + orr));
-      }
-      ar[li[q]] = vr;
-      ai[li[q]] = vi;
-    }
-  }
-  __syncthreads();
-  multi_stages<T>(fs.p1, ar, ai, TB);
-  // u[j1] = conj(stage result) W_N^{-j1 k2}, stored at packed position
-  // j1 + N1 k2 of the slot's tube
-  for (int e = threadIdx.x; e < TB * N1; e += kFsNT) {
-    const int u = e / N1, j1 = e - u * N1;
-    const int64_t t = t0 + u;
-    if (t >= ntubes) continue;
-    const double vr = (double)ar[u * N1 + j1], vi = -(double)ai[u * N1 + j1];
-    double c, sn;
-    fs_root((int)((unsigned)(j1 * k2) % (unsigned)N), N, c, sn);  // W_N^{j1 k2}; times its conjugate
-    const int64_t o = t * (int64_t)n + 2 * ((int64_t)j1 + (int64_t)N1 * k2);
-    y[o] = (T)(vr * c + vi * sn);
-    y[o + 1] = (T)(vi * c - vr * sn);
-  }
-}
-
-// inverse tube pass: workgroup (slot block, j1 block), in place in y
-template <typename T>
-__global__ __launch_bounds__(kFsNT) void fs_inv_tube_kernel(int64_t ntubes, FourStep fs, T* __restrict__ y) {
-  constexpr int TB = FsGeom<T>::tubes, JB = FsGeom<T>::j1s;
-  extern __shared__ unsigned char fs_lds[];
-  const int N1 = fs.N1, N2 = fs.N2, N = N1 * N2, n = 2 * N;
-  T* ar = reinterpret_cast<T*>(fs_lds);
-  T* ai = ar + TB * JB * N2;
-  int64_t sbk, jbk;
-  if (!fs_tube_block((ntubes + TB - 1) / TB, (N1 + JB - 1) / JB, sbk, jbk)) return;
-  const int64_t t0 = sbk * TB;
-  const int j10 = (int)jbk * JB;
-  const int total = TB * JB * N2;
-  for (int e0 = threadIdx.x; e0 < total; e0 += kFsBatch * kFsNT) {
-    int64_t off[kFsBatch];
-    int li[kFsBatch];
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      const int e = e0 + q * kFsNT;
-      off[q] = -1;
-      li[q] = -1;
-      if (e < total) {
-        const int v = e % JB, r = e / JB;
-        const int k2 = r % N2, u = r / N2;
-        const int64_t t = t0 + u;
-        const int j1 = j10 + v;
-        li[q] = (u * JB + v) * N2 + long_dst(fs.p2, k2);
-        if (t < ntubes && j1 < N1) off[q] = t * (int64_t)n + 2 * ((int64_t)j1 + (int64_t)N1 * k2);
-      }
-    }
-    T vr[kFsBatch], vi[kFsBatch];
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      const int64_t o = off[q] < 0 ? 0 : off[q];
-      vr[q] = y[o];
-      vi[q] = y[o + 1];
-    }
-#pragma unroll
-    for (int q = 0; q < kFsBatch; ++q) {
-      if (li[q] < 0) continue;
-      ar[li[q]] = off[q] < 0 ? T(0) : vr[q];
-      ai[li[q]] = off[q] < 0 ? T(0) : -vi[q];  // conjugate in, conjugate out
-    }
-  }
-  __syncthreads();
-  multi_stages<T>(fs.p2, ar, ai, TB * JB);
-  const double inv = 1.0 / (double)N;
-  for (int e = threadIdx.x; e < TB * JB * N2; e += kFsNT) {
-    const int u = e / (JB * N2), r = e - u * (JB * N2);
-    const int j2 = r / JB, v = r - j2 * JB;  // j1 fastest: neighbouring stores
-    const int64_t t = t0 + u;
-    const int j1 = j10 + v;
-    if (t >= ntubes || j1 >= N1) continue;
-    const int li = (u * JB + v) * N2 + j2;
-    const int64_t o = t * (int64_t)n + 2 * ((int64_t)j1 + (int64_t)N1 * j2);
-    y[o] = (T)((double)ar[li] * inv);
-    y[o + 1] = (T)(-(double)ai[li] * inv);
-  }
-}
-
-// radix plan of a short length (factors 4, 2, 3, 5, 7, 11, 13), no size limits
-bool radix_plan(int64_t n, LongPlan& pl) {
-  pl.n = (int)n;
-  pl.nst = 0;
-  int64_t r = n;
-  for (int p : {4, 2, 3, 5, 7, 11, 13}) {
-    while (r % p == 0) {
-      if (pl.nst == kLongMaxStages) return false;
-      pl.rad[pl.nst++] = p;
-      r /= p;
-    }
-  }
-  return r == 1;
-}
-
-// Four-step plan of an even n: N = n/2 = N1 N2 with N2 the largest divisor
-// <= kFsMaxN2 that leaves N1 <= kFsMaxN1, both without prime factors above 13.
-bool four_step_plan(int64_t n, FourStep& fs) {
-  if (n % 2 || n < 4) return false;
-  const int64_t N = n / 2;
-  if (N > (int64_t)kFsMaxN1 * kFsMaxN2) return false;
-  for (int64_t n2 = kFsMaxN2 < N ? kFsMaxN2 : N; n2 >= 1; --n2) {
-    if (N % n2) continue;
-    const int64_t n1 = N / n2;
-    if (n1 > kFsMaxN1) break;
-    if (radix_plan(n1, fs.p1) && radix_plan(n2, fs.p2)) {
-      fs.N1 = (int)n1;
-      fs.N2 = (int)n2;
-      return true;
-    }
-  }
-  return false;
-}
-
-// 1D grid of a launch with `total` logical workgroups (padded to whole
-// rounds over the eight XCDs)
-inline int64_t fs_grid(int64_t total) { return (total + 7) / 8 * 8; }
-inline int64_t fs_tube_grid(int64_t nslot_blocks, int64_t nj_blocks) {
-  return fs_grid(((nj_blocks + 3) / 4) * ((nslot_blocks + 3) / 4) * 16);
-}
-
-template <typename T>
-int fs_forward(const T* x, const FwdArgs& a, const FourStep& fs, T* re, T* im, hipStream_t st) {
-  constexpr int TB = FsGeom<T>::tubes, JB = FsGeom<T>::j1s, SB = FsGeom<T>::stubes;
-  const int64_t gt = fs_tube_grid((a.ntubes + TB - 1) / TB, (fs.N1 + JB - 1) / JB);
-  const int64_t gs = fs_grid((a.ntubes + SB - 1) / SB * (fs.N2 / 2 + 1));
-  if (gt > 0x7fffffffLL || gs > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many tubes");
-  const size_t lt = size_t(2) * TB * JB * fs.N2 * sizeof(T), ls = size_t(2) * 2 * SB * fs.N1 * sizeof(T);
-  hipLaunchKernelGGL(fs_fwd_tube_kernel<T>, dim3((unsigned)gt), dim3(kFsNT), lt, st, x, a, fs, re, im);
-  TP_LAUNCH_CHECK();
-  hipLaunchKernelGGL(fs_fwd_slice_kernel<T>, dim3((unsigned)gs), dim3(kFsNT), ls, st, fs, a.ntubes, re, im);
-  TP_LAUNCH_CHECK();
-  return TP_OK;
-}
-
-template <typename T>
-int fs_inverse(const T* re, const T* im, int64_t ntubes, const FourStep& fs, T* y, hipStream_t st) {
-  constexpr int TB = FsGeom<T>::tubes, JB = FsGeom<T>::j1s, SB = FsGeom<T>::stubes;
-  const int64_t gt = fs_tube_grid((ntubes + TB - 1) / TB, (fs.N1 + JB - 1) / JB);
-  const int64_t gs = fs_grid((ntubes + SB - 1) / SB * fs.N2);
-  if (gt > 0x7fffffffLL || gs > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many tubes");
-  const size_t lt = size_t(2) * TB * JB * fs.N2 * sizeof(T), ls = size_t(2) * SB * fs.N1 * sizeof(T);
-  hipLaunchKernelGGL(fs_inv_slice_kernel<T>, dim3((unsigned)gs), dim3(kFsNT), ls, st, re, im, ntubes, fs, y);
-  TP_LAUNCH_CHECK();
-  hipLaunchKernelGGL(fs_inv_tube_kernel<T>, dim3((unsigned)gt), dim3(kFsNT), lt, st, ntubes, fs, y);
-  TP_LAUNCH_CHECK();
-  return TP_OK;
-}
 
 template <typename T>
 using FwdKernel = void (*)(const T*, FwdArgs, T*, T*);
@@ -1261,8 +699,9 @@ int fwd_impl(const T* x, int64_t n3, const TubeGather& g, T* re, T* im, hipStrea
     if (n3 <= lds_max<T>() && !sums)
       if (int rc = lds_forward(x, TypeOf<T>::dtype, n3, a, re, im, st, &handled)) return rc;
     if (handled) return TP_OK;
-    FourStep fs;
-    if (n3 >= kLongMin && four_step_plan(n3, fs)) return fs_forward<T>(x, a, fs, re, im, st);
+    if (n3 >= kLongMin)
+      if (int rc = four_forward(x, TypeOf<T>::dtype, n3, a, re, im, st, &handled)) return rc;
+    if (handled) return TP_OK;
     const int64_t blocks = (a.ntubes + 127) / 128;
     if (n3 <= kDirectTable)
       hipLaunchKernelGGL((rdft_direct_kernel<T, true>), dim3((unsigned)blocks), dim3(128), 2 * n3 * sizeof(double), st,
@@ -1290,8 +729,9 @@ int inv_impl(const T* re, const T* im, int64_t n3, int64_t ntubes, T* y, hipStre
     if (n3 <= lds_max<T>() && !sums)
       if (int rc = lds_inverse(re, im, TypeOf<T>::dtype, n3, ntubes, y, st, &handled)) return rc;
     if (handled) return TP_OK;
-    FourStep fs;
-    if (n3 >= kLongMin && four_step_plan(n3, fs)) return fs_inverse<T>(re, im, ntubes, fs, y, st);
+    if (n3 >= kLongMin)
+      if (int rc = four_inverse(re, im, TypeOf<T>::dtype, n3, ntubes, y, st, &handled)) return rc;
+    if (handled) return TP_OK;
     const int64_t blocks = (ntubes + 127) / 128;
     if (n3 <= kDirectTable)
       hipLaunchKernelGGL((irdft_direct_kernel<T, true>), dim3((unsigned)blocks), dim3(128), 2 * n3 * sizeof(double),

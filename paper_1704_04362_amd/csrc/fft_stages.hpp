@@ -1,10 +1,10 @@
 // Short complex transforms in registers and the mixed-radix transform of
 // many sequences in LDS built on them (used by the tube transforms of
-// fft_lds.hip and by the four-step transform of fft.hip).
+// fft_lds.hip and by the four-step transform of fft_four.hip).
 //
-// All butterflies run in float64: on gfx950 a float64 multiply-add issues at
-// the rate of a scalar float32 one, so float32 tubes get float64 butterflies
-// at no cost and round only where a stage stores to LDS.
+// The butterflies' type is that of the root table: float64 for the tubes in
+// LDS, also float ones, which then round only where a stage stores; the tube's
+// own type in the four-step passes, whose registers hold the next tile too.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -127,20 +127,22 @@ struct Root<16> {
       0.7071067811865476, 0.3826834323650898, 0.0, -0.3826834323650898, -0.7071067811865476, -0.9238795325112867,
       -1.0, -0.9238795325112867, -0.7071067811865476, -0.3826834323650898};
 };
-template <int P>
-__device__ __forceinline__ void dft(double (&r)[P], double (&i)[P]);
+template <int P, typename R>
+__device__ __forceinline__ void dft(R (&r)[P], R (&i)[P]);
 
-__device__ __forceinline__ void dft2(double& ar, double& ai, double& br, double& bi) {
-  const double xr = ar - br, xi = ai - bi;
+template <typename R>
+__device__ __forceinline__ void dft2(R& ar, R& ai, R& br, R& bi) {
+  const R xr = ar - br, xi = ai - bi;
   ar += br;
   ai += bi;
   br = xr;
   bi = xi;
 }
 
-__device__ __forceinline__ void dft4(double (&r)[4], double (&i)[4]) {
-  const double ar = r[0] + r[2], ai = i[0] + i[2], br = r[0] - r[2], bi = i[0] - i[2];
-  const double cr = r[1] + r[3], ci = i[1] + i[3], dr = i[1] - i[3], di = r[3] - r[1];  // (x1 - x3)(-i)
+template <typename R>
+__device__ __forceinline__ void dft4(R (&r)[4], R (&i)[4]) {
+  const R ar = r[0] + r[2], ai = i[0] + i[2], br = r[0] - r[2], bi = i[0] - i[2];
+  const R cr = r[1] + r[3], ci = i[1] + i[3], dr = i[1] - i[3], di = r[3] - r[1];  // (x1 - x3)(-i)
   r[0] = ar + cr;
   i[0] = ai + ci;
   r[1] = br + dr;
@@ -153,10 +155,10 @@ __device__ __forceinline__ void dft4(double (&r)[4], double (&i)[4]) {
 
 // odd prime P: with t_u = x_u + x_{P-u}, d_u = x_u - x_{P-u},
 // X_{k}, X_{P-k} = (x_0 + sum_u t_u cos) -+ i sum_u d_u sin
-template <int P>
-__device__ __forceinline__ void dft_prime(double (&r)[P], double (&i)[P]) {
+template <int P, typename R>
+__device__ __forceinline__ void dft_prime(R (&r)[P], R (&i)[P]) {
   constexpr int H = (P - 1) / 2;
-  double tr[H], ti[H], dr[H], di[H];
+  R tr[H], ti[H], dr[H], di[H];
 #pragma unroll
   for (int u = 0; u < H; ++u) {
     tr[u] = r[u + 1] + r[P - 1 - u];
@@ -164,7 +166,7 @@ __device__ __forceinline__ void dft_prime(double (&r)[P], double (&i)[P]) {
     dr[u] = r[u + 1] - r[P - 1 - u];
     di[u] = i[u + 1] - i[P - 1 - u];
   }
-  const double x0r = r[0], x0i = i[0];
+  const R x0r = r[0], x0i = i[0];
 #pragma unroll
   for (int u = 0; u < H; ++u) {
     r[0] += tr[u];
@@ -172,14 +174,14 @@ __device__ __forceinline__ void dft_prime(double (&r)[P], double (&i)[P]) {
   }
 #pragma unroll
   for (int k = 1; k <= H; ++k) {
-    double ar = x0r, ai = x0i, br = 0.0, bi = 0.0;
+    R ar = x0r, ai = x0i, br = R(0), bi = R(0);
 #pragma unroll
     for (int u = 0; u < H; ++u) {
       const int e = (k * (u + 1)) % P;
-      ar += Root<P>::c[e] * tr[u];
-      ai += Root<P>::c[e] * ti[u];
-      br += Root<P>::s[e] * di[u];
-      bi += Root<P>::s[e] * dr[u];
+      ar += R(Root<P>::c[e]) * tr[u];
+      ai += R(Root<P>::c[e]) * ti[u];
+      br += R(Root<P>::s[e]) * di[u];
+      bi += R(Root<P>::s[e]) * dr[u];
     }
     r[k] = ar + br;
     i[k] = ai - bi;
@@ -189,10 +191,10 @@ __device__ __forceinline__ void dft_prime(double (&r)[P], double (&i)[P]) {
 }
 
 // P = A B, Cooley-Tukey: A transforms of length B, twiddles, B of length A
-template <int A, int B>
-__device__ __forceinline__ void dft_ct(double (&r)[A * B], double (&i)[A * B]) {
+template <int A, int B, typename R>
+__device__ __forceinline__ void dft_ct(R (&r)[A * B], R (&i)[A * B]) {
   constexpr int P = A * B;
-  double yr[A][B], yi[A][B];
+  R yr[A][B], yi[A][B];
 #pragma unroll
   for (int a = 0; a < A; ++a) {
 #pragma unroll
@@ -204,7 +206,7 @@ __device__ __forceinline__ void dft_ct(double (&r)[A * B], double (&i)[A * B]) {
   }
 #pragma unroll
   for (int k = 0; k < B; ++k) {
-    double tr[A], ti[A];
+    R tr[A], ti[A];
 #pragma unroll
     for (int a = 0; a < A; ++a) {
       const int e = a * k;
@@ -212,7 +214,7 @@ __device__ __forceinline__ void dft_ct(double (&r)[A * B], double (&i)[A * B]) {
         tr[a] = yr[a][k];
         ti[a] = yi[a][k];
       } else {
-        const double c = Root<P>::c[e], s = Root<P>::s[e];
+        const R c = R(Root<P>::c[e]), s = R(Root<P>::s[e]);
         tr[a] = yr[a][k] * c + yi[a][k] * s;
         ti[a] = yi[a][k] * c - yr[a][k] * s;
       }
@@ -228,10 +230,10 @@ __device__ __forceinline__ void dft_ct(double (&r)[A * B], double (&i)[A * B]) {
 
 // P = A B with A, B coprime, no twiddles (Good-Thomas): input B a + A b,
 // output k with k = ka mod A, k = kb mod B
-template <int A, int B>
-__device__ __forceinline__ void dft_pfa(double (&r)[A * B], double (&i)[A * B]) {
+template <int A, int B, typename R>
+__device__ __forceinline__ void dft_pfa(R (&r)[A * B], R (&i)[A * B]) {
   constexpr int P = A * B;
-  double yr[A][B], yi[A][B];
+  R yr[A][B], yi[A][B];
 #pragma unroll
   for (int a = 0; a < A; ++a) {
 #pragma unroll
@@ -243,7 +245,7 @@ __device__ __forceinline__ void dft_pfa(double (&r)[A * B], double (&i)[A * B]) 
   }
 #pragma unroll
   for (int b = 0; b < B; ++b) {
-    double tr[A], ti[A];
+    R tr[A], ti[A];
 #pragma unroll
     for (int a = 0; a < A; ++a) {
       tr[a] = yr[a][b];
@@ -262,8 +264,8 @@ __device__ __forceinline__ void dft_pfa(double (&r)[A * B], double (&i)[A * B]) 
   }
 }
 
-template <int P>
-__device__ __forceinline__ void dft(double (&r)[P], double (&i)[P]) {
+template <int P, typename R>
+__device__ __forceinline__ void dft(R (&r)[P], R (&i)[P]) {
   if constexpr (P == 2)
     dft2(r[0], i[0], r[1], i[1]);
   else if constexpr (P == 4)
@@ -312,50 +314,68 @@ struct alignas(2 * sizeof(S)) Cx {
 
 // exp(-2 pi i e / N), 0 <= e < N, from a table of exp(-2 pi i k / 2N),
 // k <= N / 2, by the symmetries of the circle
-__device__ __forceinline__ void root_at(const Cx<double>* tab, int N, int e, double& c, double& s) {
+template <typename R>
+__device__ __forceinline__ void root_at(const Cx<R>* tab, int N, int e, R& c, R& s) {
   int a = 2 * e;
   const bool neg = a >= N;  // half a turn further
   a = neg ? a - N : a;
   const bool mir = 2 * a > N;  // mirrored on the imaginary axis
   a = mir ? N - a : a;
-  const Cx<double> w = tab[a];
+  const Cx<R> w = tab[a];
   c = neg != mir ? -w.x : w.x;
   s = neg ? -w.y : w.y;
 }
 
+// the same from a table of all exp(-2 pi i e / N)
+template <typename R>
+struct AllRoots {
+  const Cx<R>* w;
+};
+template <typename R>
+__device__ __forceinline__ void root_at(AllRoots<R> tab, int, int e, R& c, R& s) {
+  const Cx<R> w = tab.w[e];
+  c = w.x;
+  s = w.y;
+}
+template <typename R>
+__device__ R root_type(const Cx<R>*);
+template <typename R>
+__device__ R root_type(AllRoots<R>);
+
 // x_t *= W^t, t = 1 .. P-1, W = exp(-2 pi i e1 / N). Float tubes (EXACT false)
 // form the powers by two running products in float64 (odd and even t), far
 // below the rounding of their storage; double ones read every root.
-template <int P, bool EXACT>
-__device__ __forceinline__ void twiddle(const Cx<double>* tab, int N, int e1, double (&r)[P], double (&i)[P]) {
-  double cr[2], ci[2];  // the running powers of odd and even t
+template <int P, bool EXACT, typename Tab, typename R>
+__device__ __forceinline__ void twiddle(Tab tab, int N, int e1, R (&r)[P], R (&i)[P]) {
+  R cr[2], ci[2];  // the running powers of odd and even t
   root_at(tab, N, e1, cr[1], ci[1]);
-  const double sr = cr[1] * cr[1] - ci[1] * ci[1], si = 2.0 * cr[1] * ci[1];
+  const R sr = cr[1] * cr[1] - ci[1] * ci[1], si = R(2) * cr[1] * ci[1];
   cr[0] = sr;
   ci[0] = si;
 #pragma unroll
   for (int t = 1; t < P; ++t) {
-    double &wr = cr[t & 1], &wi = ci[t & 1];
+    R &wr = cr[t & 1], &wi = ci[t & 1];
     if (EXACT ? t > 1 : t > 2) {
       if constexpr (EXACT) {
         root_at(tab, N, e1 * t, wr, wi);
       } else {
-        const double x = wr;
+        const R x = wr;
         wr = x * sr - wi * si;
         wi = x * si + wi * sr;
       }
     }
-    const double x = r[t];
+    const R x = r[t];
     r[t] = x * wr - i[t] * wi;
     i[t] = x * wi + i[t] * wr;
   }
 }
 
 // One stage in place: radix P, butterfly (group g, j < m) over the positions
-// g m P + j + t m. Decimation in time (DIF false): twiddle W_{mP}^{j t}, then the
+// g m P + j + t m, `ld` elements apart. Decimation in time (DIF false): twiddle W_{mP}^{j t}, then the
 // P-point transform; decimation in frequency: the transform, then the twiddle.
-template <typename S, int P, bool DIF, bool EXACT>
-__device__ __forceinline__ void stage(Cx<S>* buf, int lg, int N, int m, uint32_t mag, const Cx<double>* tab) {
+template <typename S, int P, bool DIF, bool EXACT, typename Tab>
+__device__ __forceinline__ void stage(Cx<S>* buf, int lg, int ld, int N, int m, uint32_t mag, Tab tab) {
+  using R = decltype(root_type(tab));
   const int mask = (1 << lg) - 1, per = N / P, total = per << lg;
   for (int b = threadIdx.x; b < total; b += blockDim.x) {
     const int u = b & mask, c = b >> lg;
@@ -364,14 +384,14 @@ __device__ __forceinline__ void stage(Cx<S>* buf, int lg, int N, int m, uint32_t
       g = (int)__umulhi((uint32_t)c, mag);
       j = c - g * m;
     }
-    Cx<S>* p = buf + ((g * (m * P) + j) << lg) + u;
-    const int step = m << lg;
-    double r[P], i[P];
+    Cx<S>* p = buf + (g * (m * P) + j) * ld + u;
+    const int step = m * ld;
+    R r[P], i[P];
 #pragma unroll
     for (int t = 0; t < P; ++t) {
       const Cx<S> v = p[t * step];
-      r[t] = (double)v.x;
-      i[t] = (double)v.y;
+      r[t] = (R)v.x;
+      i[t] = (R)v.y;
     }
     const int e1 = j * (N / (m * P));
     if (!DIF && m > 1) twiddle<P, EXACT>(tab, N, e1, r, i);
@@ -385,30 +405,34 @@ __device__ __forceinline__ void stage(Cx<S>* buf, int lg, int N, int m, uint32_t
 // All stages. DIF: natural order in, element k of the result at position
 // pos(k) (see fill_positions); otherwise input element e at pos(e), natural
 // order out. Ends with a barrier.
-template <typename S, bool DIF, bool EXACT>
-__device__ void stages(const Plan& pl, Cx<S>* buf, int lg, const Cx<double>* tab) {
+template <typename S, bool DIF, bool EXACT, typename Tab>
+__device__ void stages(const Plan& pl, Cx<S>* buf, int lg, int ld, Tab tab) {
   for (int q = 0; q < pl.nst; ++q) {
     const int z = DIF ? pl.nst - 1 - q : q;
     const int m = pl.m[z];
     const uint32_t mag = pl.mag[z];
     switch (pl.rad[z]) {
-      case 2: stage<S, 2, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 3: stage<S, 3, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 4: stage<S, 4, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 5: stage<S, 5, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 6: stage<S, 6, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 7: stage<S, 7, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 8: stage<S, 8, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 9: stage<S, 9, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 10: stage<S, 10, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 11: stage<S, 11, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 12: stage<S, 12, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 13: stage<S, 13, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      case 15: stage<S, 15, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
-      default: stage<S, 16, DIF, EXACT>(buf, lg, pl.n, m, mag, tab); break;
+      case 2: stage<S, 2, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 3: stage<S, 3, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 4: stage<S, 4, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 5: stage<S, 5, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 6: stage<S, 6, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 7: stage<S, 7, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 8: stage<S, 8, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 9: stage<S, 9, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 10: stage<S, 10, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 11: stage<S, 11, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 12: stage<S, 12, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 13: stage<S, 13, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 15: stage<S, 15, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      default: stage<S, 16, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
     }
     __syncthreads();
   }
+}
+template <typename S, bool DIF, bool EXACT>
+__device__ __forceinline__ void stages(const Plan& pl, Cx<S>* buf, int lg, const Cx<double>* tab) {
+  stages<S, DIF, EXACT>(pl, buf, lg, 1 << lg, tab);
 }
 
 // pos[k], k < N: where the in-place stages keep element k of the transform
@@ -430,6 +454,16 @@ __device__ __forceinline__ void fill_roots(int N, Cx<double>* tab) {
     double s, c;
     sincospi(-(double)k / (double)N, &s, &c);
     tab[k] = Cx<double>{c, s};
+  }
+}
+
+// exp(-2 pi i k / N), k < N, rounded once to the butterflies' type
+template <typename R>
+__device__ __forceinline__ void fill_all_roots(int N, Cx<R>* tab) {
+  for (int k = threadIdx.x; k < N; k += blockDim.x) {
+    double s, c;
+    sincospi(-2.0 * (double)k / (double)N, &s, &c);
+    tab[k] = Cx<R>{(R)c, (R)s};
   }
 }
 

@@ -39,18 +39,11 @@ __device__ __forceinline__ bool tube_source(const FwdArgs& a, int64_t t, int64_t
   return true;
 }
 
-// Launch order. Workgroup L runs on XCD L mod 8, each XCD with its own L2;
-// the logical index (L mod 8) q + L / 8 (q = ceil(total / 8)) gives every XCD
-// a contiguous range of logical work, so the workgroups that share cache
-// lines (neighbouring slots) run together on one XCD. The grid is padded to
-// whole rounds over the eight XCDs (xcd_grid); returns false for the padding.
-__device__ __forceinline__ bool xcd_logical(int64_t total, int64_t& G) {
-  const int64_t L = blockIdx.x, q = (total + 7) / 8;
-  G = (L % 8) * q + L / 8;
-  return G < total;
-}
-// The same order for a grid (a multiple of 8) of fewer workgroups than `total`:
-// each XCD's workgroups walk its contiguous range side by side.
+// Launch order. Workgroup L runs on XCD L mod 8, each XCD with its own L2:
+// every XCD takes a contiguous range of ceil(total / 8) logical tiles, so the
+// workgroups that share cache lines (neighbouring slots) run together on one
+// XCD, and the XCD's workgroups (of a grid that is a multiple of 8) walk its
+// range side by side.
 struct XcdWalk {
   int64_t total, q, i, step;
   __device__ XcdWalk(int64_t total_) : total(total_), q((total_ + 7) / 8), i(blockIdx.x / 8), step(gridDim.x / 8) {}
@@ -70,5 +63,12 @@ int lds_forward(const void* x, int dtype, int64_t n3, const FwdArgs& a, void* re
                 bool* handled);
 int lds_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t ntubes, void* y, hipStream_t st,
                 bool* handled);
+
+// Four-step transforms through HBM (fft_four.hip): even lengths up to 2^19 whose
+// half has no prime factor above 13. *handled is false for other lengths.
+int four_forward(const void* x, int dtype, int64_t n3, const FwdArgs& a, void* re, void* im, hipStream_t st,
+                 bool* handled);
+int four_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t ntubes, void* y, hipStream_t st,
+                 bool* handled);
 
 }  // namespace tp

@@ -54,3 +54,33 @@ def test_tube_transforms_of_picked_slices(n3):
     Z = api.tprod(dev(A), dev(B), picks=picks, prec="f64").cpu().numpy()
     idx, sc = S.sample_bernoulli(w, 20, seed=2)
     assert T.rel_fro(Z, D.rtprod(A, B, idx, sc)) < 1e-12
+
+
+@pytest.mark.parametrize("n3, shape, dtype", [
+    (8320, (1, 1), np.float32),      # 4160 = 20 x 208, one tube
+    (10000, (3, 100), np.float32),   # 20 x 250: 256 slots a slice tile, a remainder
+    (57122, (1, 9), np.float32),     # 169 x 169: odd pair count, no self-paired middle slice
+    (262144, (1, 2), np.float32),    # 512 x 256
+    (524288, (1, 1), np.float32),    # 1024 x 256, the longest
+    (4100, (2, 65), np.float64),     # 41 is no radix: the direct kernel
+    (4116, (2, 65), np.float64),     # 14 x 147
+    (524288, (1, 3), np.float64),
+])
+def test_four_step_tiles(n3, shape, dtype):
+    """Tile shapes of the four-step passes against float64 transforms on the
+    host. float32: at most 8 roundings through float storage and float
+    butterflies of at most log2(N) additions, relative error below
+    2^-24 (8 + log2 n3) each way; float64 the same with 2^-53 and twice the
+    count, for the host's own error."""
+    X = W.gaussian((*shape, n3), seed=n3).astype(dtype)
+    tol = 2.0 ** -24 * (8 + np.log2(n3)) if dtype == np.float32 else 2.0 ** -53 * 2 * (8 + np.log2(n3))
+    if n3 == 4100:
+        tol *= 16  # direct sums of 4100 terms
+    re, im = api.tfft(dev(X))
+    H = np.fft.rfft(X.astype(np.float64), axis=2).transpose(2, 0, 1)
+    got = re.cpu().numpy().astype(np.float64) + 1j * im.cpu().numpy()
+    assert got.shape == H.shape
+    assert np.linalg.norm(got - H) < tol * np.linalg.norm(H)
+    assert not im[0].any() and not im[-1].any()
+    Y = api.tifft(re, im, n3).cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(Y - X) < 2 * tol * np.linalg.norm(X)
