@@ -6,12 +6,15 @@
 // Squares are formed and summed in float64 (a float32 square is exact in
 // float64), always in the same order, so results are reproducible run to
 // run. No floating-point atomics.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace tp {
 namespace {
 
-constexpr int LT = 32;      // tubes (lateral slices) per workgroup (64 measured 2% slower in the rt-product)
+constexpr int LT = 32;      // tubes (lateral slices) per workgroup, or a multiple of it for short tubes
+                            // (64 measured 2% slower in the rt-product's 64-long tubes)
 constexpr int LROWS = 16;   // horizontal slices per workgroup
 constexpr int LNT = 256;    // threads per workgroup
 
@@ -28,60 +31,73 @@ struct V16<double> {
   static constexpr int n = 2;
 };
 
-// Workgroup (bx, by) sums rows [by*LROWS, +LROWS) for tubes [bx*LT, +LT).
-// In every row those LT tubes are one contiguous run of LT*n3 values; a
-// thread always owns the same 16-byte pieces of that run, so it accumulates
-// its pieces over all rows with independent coalesced loads, and the pieces
-// of a tube are added in a fixed order at the end through LDS.
-template <typename T>
+// Workgroup (bx, by) sums rows [by*LROWS, +LROWS) for tubes [bx*lt, +lt).
+// In every row those tubes are one contiguous run of lt*n3 values; a thread
+// always owns the same 16-byte pieces of that run, so it accumulates its
+// pieces over all rows with independent coalesced loads (all LROWS in flight:
+// rows past the end re-read the last row and are masked out of the sum), and
+// the sums of a tube are added in a fixed order at the end through LDS: one
+// sum per piece where pieces do not straddle tubes (ALIGNED, n3 a multiple of
+// the piece), otherwise one per value, whose pieces also start on any value.
+// Bound: reading A. 300 x 100000 x 5 float32, 600 MB: 338 us with one value a
+// thread and 32 tubes a workgroup (1.8 TB/s), 112 us (5.3 TB/s) with pieces and 192.
+template <typename T, bool ALIGNED>
 __global__ __launch_bounds__(LNT) void lateral_partial_kernel(const T* __restrict__ a, int64_t n1, int64_t n2,
-                                                               int64_t n3, double* __restrict__ partial) {
+                                                               int64_t n3, int64_t lt, double* __restrict__ partial) {
   using V = typename V16<T>::type;
-  constexpr int VN = V16<T>::n;
-  extern __shared__ double piece[];  // [LT][CH]
+  constexpr int VN = V16<T>::n, SN = ALIGNED ? 1 : VN;  // sums of a piece
+  extern __shared__ double piece[];                     // [lt][n3 / (VN / SN)], rounded up to a piece
   const int tid = threadIdx.x;
-  const int64_t j0 = (int64_t)blockIdx.x * LT;
+  const int64_t j0 = (int64_t)blockIdx.x * lt;
   const int64_t i0 = (int64_t)blockIdx.y * LROWS;
-  const int64_t ntub = (n2 - j0) < LT ? (n2 - j0) : LT;
-  const bool vec = (n3 % VN) == 0;
-  const int64_t CH = vec ? n3 / VN : n3;
-  const int64_t npieces = ntub * CH;
-  const int64_t rows = (n1 - i0) < LROWS ? (n1 - i0) : LROWS;
-  for (int64_t f0 = 0; f0 < LT * CH; f0 += LNT) {
-    const int64_t f = f0 + tid;
-    double s = 0.0;
-    if (f < npieces) {
-      if (vec) {
-        // all LROWS loads in flight at once: rows past the end re-read the
-        // last row and are masked out of the sum
-        V w[LROWS];
+  const int64_t ntub = (n2 - j0) < lt ? (n2 - j0) : lt;
+  const int64_t len = ntub * n3, rows = (n1 - i0) < LROWS ? (n1 - i0) : LROWS;
+  const T* run = a + (i0 * n2 + j0) * n3;
+  for (int64_t f = tid; f * VN < len; f += LNT) {
+    double s[SN] = {};
+    if (ALIGNED || f * VN + VN <= len) {
+      V w[LROWS];
 #pragma unroll
-        for (int r = 0; r < LROWS; ++r) {
-          const int64_t rr = r < rows ? r : rows - 1;
-          w[r] = *reinterpret_cast<const V*>(a + ((i0 + rr) * n2 + j0) * n3 + f * VN);
-        }
+      for (int r = 0; r < LROWS; ++r) {
+        const int64_t rr = r < rows ? r : rows - 1;
+        const T* p = run + rr * n2 * n3 + f * VN;
+        if constexpr (ALIGNED)
+          w[r] = *reinterpret_cast<const V*>(p);
+        else
+          __builtin_memcpy(&w[r], p, sizeof(V));
+      }
 #pragma unroll
-        for (int r = 0; r < LROWS; ++r) {
-          const T* wp = reinterpret_cast<const T*>(&w[r]);
+      for (int r = 0; r < LROWS; ++r) {
+        const T* wp = reinterpret_cast<const T*>(&w[r]);
+        if constexpr (ALIGNED) {
           double q = 0.0;
 #pragma unroll
           for (int e = 0; e < VN; ++e) q += (double)wp[e] * (double)wp[e];
-          s += r < rows ? q : 0.0;
-        }
-      } else {
-        for (int64_t r = 0; r < rows; ++r) {
-          const double v = (double)a[((i0 + r) * n2 + j0) * n3 + f];
-          s += v * v;
+          s[0] += r < rows ? q : 0.0;
+        } else {
+#pragma unroll
+          for (int e = 0; e < VN; ++e) {
+            const double v = r < rows ? (double)wp[e] : 0.0;
+            s[e] = fma(v, v, s[e]);
+          }
         }
       }
+    } else if constexpr (!ALIGNED) {  // the run's last values
+      for (int e = 0; e < len - f * VN; ++e)
+        for (int64_t r = 0; r < rows; ++r) {
+          const double v = (double)run[r * n2 * n3 + f * VN + e];
+          s[e] = fma(v, v, s[e]);
+        }
     }
-    if (f < LT * CH) piece[f] = s;
+#pragma unroll
+    for (int e = 0; e < SN; ++e) piece[f * SN + e] = s[e];
   }
   __syncthreads();
-  if (tid < ntub) {
+  const int64_t CH = ALIGNED ? n3 / VN : n3;
+  for (int64_t j = tid; j < ntub; j += LNT) {
     double t = 0.0;
-    for (int64_t p = 0; p < CH; ++p) t += piece[tid * CH + p];
-    partial[(int64_t)blockIdx.y * n2 + j0 + tid] = t;
+    for (int64_t p = 0; p < CH; ++p) t += piece[j * CH + p];
+    partial[(int64_t)blockIdx.y * n2 + j0 + j] = t;
   }
 }
 
@@ -187,14 +203,16 @@ int lateral_norms(const void* a, int dtype, int64_t n1, int64_t n2, int64_t n3, 
   if (n2 == 0) return TP_OK;
   const int64_t nb = lateral_blocks(n1);
   const int vn = dtype == TP_F64 ? 2 : 4;
-  const int64_t CH = (n3 % vn == 0) ? n3 / vn : n3;
-  const size_t lds = size_t(LT) * CH * sizeof(double);
+  const bool aligned = n3 % vn == 0;
+  // tubes a workgroup: enough for a piece a thread
+  const int64_t lt = LT * std::max<int64_t>(1, LNT * vn / (LT * n3));
+  const size_t lds = sizeof(double) * ((aligned ? lt * (n3 / vn) : lt * n3) + vn);
   if (n1 == 0) {
     hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, out, n2);
     TP_LAUNCH_CHECK();
     return TP_OK;
   }
-  if (lds > 64 * 1024) {
+  if (lds > 64 * 1024 + vn * sizeof(double)) {
     if (n2 > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many lateral slices");
     dim3 grid((unsigned)n2, (unsigned)nb);
     if (dtype == TP_F64)
@@ -202,11 +220,14 @@ int lateral_norms(const void* a, int dtype, int64_t n1, int64_t n2, int64_t n3, 
     else
       hipLaunchKernelGGL(lateral_long_kernel<float>, grid, dim3(LNT), 0, st, (const float*)a, n1, n2, n3, ws);
   } else {
-    dim3 grid((unsigned)((n2 + LT - 1) / LT), (unsigned)nb);
+    const dim3 grid((unsigned)((n2 + lt - 1) / lt), (unsigned)nb);
+    const auto launch = [&](auto kernel, auto* p) {
+      hipLaunchKernelGGL(kernel, grid, dim3(LNT), lds, st, p, n1, n2, n3, lt, ws);
+    };
     if (dtype == TP_F64)
-      hipLaunchKernelGGL(lateral_partial_kernel<double>, grid, dim3(LNT), lds, st, (const double*)a, n1, n2, n3, ws);
+      launch(aligned ? lateral_partial_kernel<double, true> : lateral_partial_kernel<double, false>, (const double*)a);
     else
-      hipLaunchKernelGGL(lateral_partial_kernel<float>, grid, dim3(LNT), lds, st, (const float*)a, n1, n2, n3, ws);
+      launch(aligned ? lateral_partial_kernel<float, true> : lateral_partial_kernel<float, false>, (const float*)a);
   }
   TP_LAUNCH_CHECK();
   hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, ws, nb, n2, out);
