@@ -259,9 +259,10 @@ size_t tp_tprod_workspace(const tp_tensor* A, const tp_tensor* B, const tp_sampl
   if (use_split(A->dtype, prec, A->n3)) {
     const int64_t ldk = round_up32(inner);
     return align_up(size_t(8) * K * A->n1 * ldk) + align_up(size_t(8) * K * B->n2 * ldk) +
-           spectrum_bytes(K, A->n1, B->n2, TP_F32) + 1024;
+           spectrum_bytes(K, A->n1, B->n2, TP_F32) +
+           2 * align_up(size_t(4) * cgemm_split_floats(K, A->n3 % 2 == 0, A->n1, B->n2, ldk)) + 1024;
   }
-  const int64_t part = A->dtype == TP_F32 ? cgemm_ksplit_floats(K, A->n1, B->n2, inner) : 0;
+  const int64_t part = A->dtype == TP_F32 ? cgemm_ksplit_floats(K, A->n3 % 2 == 0, A->n1, B->n2, inner) : 0;
   return spectrum_bytes(K, A->n1, inner, A->dtype) + spectrum_bytes(K, inner, B->n2, A->dtype) +
          spectrum_bytes(K, A->n1, B->n2, A->dtype) + 2 * align_up(size_t(4) * part) + 1024;
 }
@@ -320,6 +321,9 @@ int tp_tprod(const tp_tensor* A, const tp_tensor* B, const tp_sample* sample, tp
     void* Ap = ar.take<char>(size_t(8) * K * n1 * ldk);
     void* Bp = ar.take<char>(size_t(8) * K * n4 * ldk);
     Plane Ch = take_spectrum(ar, K, n1, n4, TP_F32);
+    const int64_t part = cgemm_split_floats(K, real_last, n1, n4, ldk);
+    float* part_re = part ? ar.take<float>(part) : nullptr;
+    float* part_im = part ? ar.take<float>(part) : nullptr;
     if (!ar.ok()) return fail(TP_EWORKSPACE, "t-product workspace too small");
     {
       TraceScope ts(nm_fa, st);
@@ -348,6 +352,9 @@ int tp_tprod(const tp_tensor* A, const tp_tensor* B, const tp_sample* sample, tp
     g.sc = n1 * n4;
     g.real_last = real_last;
     g.terms = prec == TP_PREC_BF16X3 ? 3 : 1;
+    g.part_re = part_re;
+    g.part_im = part_im;
+    g.part_cap = part;
     {
       TraceScope ts(nm_mm, st);
       if (int rc = cgemm_split(g, st)) return rc;
@@ -360,7 +367,7 @@ int tp_tprod(const tp_tensor* A, const tp_tensor* B, const tp_sample* sample, tp
   Plane Bh = take_spectrum(ar, K, inner, n4, A->dtype);
   Plane Ch = take_spectrum(ar, K, n1, n4, A->dtype);
   // scratch for a split contraction of a product with few output tiles
-  const int64_t part = A->dtype == TP_F32 ? cgemm_ksplit_floats(K, n1, n4, inner) : 0;
+  const int64_t part = A->dtype == TP_F32 ? cgemm_ksplit_floats(K, real_last, n1, n4, inner) : 0;
   float* part_re = part ? ar.take<float>(part) : nullptr;
   float* part_im = part ? ar.take<float>(part) : nullptr;
   if (!ar.ok()) return fail(TP_EWORKSPACE, "t-product workspace too small");

@@ -117,7 +117,7 @@ struct FullSvdLayout {
     if (!direct) {
       xre = ar.take<float>(K * m * m);
       xim = ar.take<float>(K * m * m);
-      part = cgemm_ksplit_floats(K, m, m, std::max(n1, n2));
+      part = cgemm_ksplit_floats(K, n3 % 2 == 0, m, m, std::max(n1, n2));
       if (part) {
         part_re = ar.take<float>(part);
         part_im = ar.take<float>(part);

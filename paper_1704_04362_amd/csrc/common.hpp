@@ -1,6 +1,7 @@
 // Internal declarations shared by the library's translation units.
 #pragma once
 
+#include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -117,6 +118,9 @@ struct SplitGemm {
   int64_t pa = 0, pb = 0, sa = 0, sb = 0, sc = 0;
   bool real_last = false;
   int terms = 3;
+  // optional scratch for a split contraction, as in CGemm below
+  float *part_re = nullptr, *part_im = nullptr;
+  int64_t part_cap = 0;
 };
 int cgemm_split(const SplitGemm& p, hipStream_t st);
 
@@ -161,14 +165,36 @@ struct CGemm {
 };
 
 int cgemm(const CGemm& p, int dtype, int prec, hipStream_t st);
-// Number of contraction parts the matrix-core product would use for an
-// M x N x Kd product over K slices (1 = no split), and the scratch floats
-// per plane it needs for them.
-int cgemm_ksplit(int64_t K, int64_t M, int64_t N, int64_t Kd);
-// The same for the float32 matrix-core product (gemm_f32.hip).
-int cgemm_f32_ksplit(int64_t K, int64_t M, int64_t N, int64_t Kd);
-inline int64_t cgemm_ksplit_floats(int64_t K, int64_t M, int64_t N, int64_t Kd) {
-  const int s = cgemm_ksplit(K, M, N, Kd), s2 = cgemm_f32_ksplit(K, M, N, Kd);
+// Parts of a contraction of `steps` steps over `tiles` output tiles in each of K
+// slices (the real ones take about a third of the time and start last), one
+// workgroup a CU: the number that needs the fewest steps one after another,
+// rounds of 256 workgroups x (steps of a part + 4 for its start and its planes),
+// each part at least `least` steps, at most 64 parts.
+inline int contraction_parts(int64_t K, bool real_last, int64_t tiles, int64_t steps, int64_t least) {
+  if (tiles * K >= 256) return 1;
+  const int64_t real = tiles * (real_last && K > 1 ? 2 : 1), cplx = tiles * K - real;
+  int64_t best = 0, parts = 1;
+  for (int64_t s = 1; s <= 64 && (s == 1 || steps >= s * least); ++s) {
+    const int64_t thirds = std::max(3 * ((cplx * s + 255) / 256), ((3 * cplx + real) * s + 255) / 256);
+    const int64_t cost = thirds * ((steps + s - 1) / s + 4);
+    if (s == 1 || cost < best) {
+      best = cost;
+      parts = s;
+    }
+  }
+  return (int)parts;
+}
+// Number of contraction parts the matrix-core products would use for an
+// M x N x Kd product over K slices (1 = no split): bf16 (gemm_mfma.hip) and
+// float32 (gemm_f32.hip); and the scratch floats per plane for them.
+int cgemm_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd);
+int cgemm_f32_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd);
+inline int64_t cgemm_split_floats(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd) {
+  const int s = cgemm_ksplit(K, real_last, M, N, Kd);
+  return s > 1 ? int64_t(s) * K * M * N : 0;
+}
+inline int64_t cgemm_ksplit_floats(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd) {
+  const int s = cgemm_ksplit(K, real_last, M, N, Kd), s2 = cgemm_f32_ksplit(K, real_last, M, N, Kd);
   const int m = s > s2 ? s : s2;
   return m > 1 ? int64_t(m) * K * M * N : 0;
 }

@@ -45,7 +45,6 @@ struct FArgs {
   int real_last;
   const int64_t* kdim_dev;
   int ksplit;
-  int64_t kchunk;
   float *pre, *pim;  // partial planes [part][K][M][N] when ksplit > 1
 };
 
@@ -124,8 +123,9 @@ __device__ __forceinline__ void f32_body(const FArgs& g, int64_t k, int part, fl
     const int64_t lim = *g.kdim_dev;
     Kd = lim < Kd ? (lim < 0 ? 0 : lim) : Kd;
   }
-  const int64_t kbeg = (int64_t)part * g.kchunk;
-  const int64_t kend = kbeg + g.kchunk < Kd ? kbeg + g.kchunk : Kd;
+  const int64_t kchunk = g.ksplit > 1 ? ((Kd + g.ksplit - 1) / g.ksplit + FK - 1) / FK * FK : Kd;
+  const int64_t kbeg = (int64_t)part * kchunk;
+  const int64_t kend = kbeg + kchunk < Kd ? kbeg + kchunk : Kd;
   const float* are = g.are + k * g.sa;
   const float* aim = g.aim + k * g.sa;
   const float* bre = g.bre + k * g.sb;
@@ -267,16 +267,14 @@ __global__ void f32_ksplit_reduce_kernel(const float* __restrict__ pre, const fl
 
 }  // namespace
 
-// Parts of a split contraction for the float32 matrix-core product: enough
-// workgroups to cover the compute units about twice, each part at least
-// 64 steps of 16, at most 64 parts.
-int cgemm_f32_ksplit(int64_t K, int64_t M, int64_t N, int64_t Kd) {
-  const int64_t tiles = ((M + FM - 1) / FM) * ((N + FN - 1) / FN) * K;
-  if (tiles >= 256 || Kd < 128 * FK) return 1;
-  int64_t s = (512 + tiles - 1) / tiles;
-  s = s < Kd / (64 * FK) ? s : Kd / (64 * FK);
-  s = s < 64 ? s : 64;
-  return s > 1 ? (int)s : 1;
+// Parts of a split contraction for the float32 matrix-core product, at least
+// eight steps each. Whole rt-product in us, before (one part up to a
+// contraction of 2048, then at least 64 steps a part) / now:
+// 300 x 300 x 5 over 256 picks 103 / 62, 1700 571 / 107, 6000 548 / 301; 512 x
+// 512 x 12 over 256 144 / 77, 6000 1890 / 876; 500 x 300 x 8 over 256 101 / 66, 6000
+// 482 / 477.
+int cgemm_f32_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd) {
+  return contraction_parts(K, real_last, ((M + FM - 1) / FM) * ((N + FN - 1) / FN), Kd / FK, 8);
 }
 
 // Takes float32 products with at least 16 rows and columns and a contraction
@@ -285,13 +283,12 @@ int cgemm_f32mfma(const CGemm& p, hipStream_t st, bool* handled) {
   *handled = false;
   if (p.M < 16 || p.N < 16 || p.Kd < 64) return TP_OK;
   if (p.K > 65535) return TP_OK;
-  int ksplit = cgemm_f32_ksplit(p.K, p.M, p.N, p.Kd);
+  int ksplit = cgemm_f32_ksplit(p.K, p.real_last, p.M, p.N, p.Kd);
   if (ksplit > 1 && (!p.part_re || !p.part_im || p.part_cap < int64_t(ksplit) * p.K * p.M * p.N)) ksplit = 1;
   if (p.K * ksplit > 65535) ksplit = 1;
-  const int64_t kchunk = ksplit > 1 ? ((p.Kd + ksplit - 1) / ksplit + FK - 1) / FK * FK : p.Kd;
   FArgs g{p.M, p.N, p.Kd, (const float*)p.are, (const float*)p.aim, (const float*)p.bre, (const float*)p.bim,
           (float*)p.cre, (float*)p.cim, p.lda, p.ldb, p.ldc, p.sa, p.sb, p.sc, p.op_a, p.op_b, p.K,
-          p.real_last ? 1 : 0, p.kdim_dev, ksplit, kchunk, p.part_re, p.part_im};
+          p.real_last ? 1 : 0, p.kdim_dev, ksplit, p.part_re, p.part_im};
   const int64_t gx = (p.N + FN - 1) / FN, gy = (p.M + FM - 1) / FM;
   if (gx > 0x7fffffff || gy > 65535) return TP_OK;
   hipLaunchKernelGGL(cgemm_f32_kernel, dim3((unsigned)gx, (unsigned)gy, (unsigned)(p.K * ksplit)), dim3(FT), 0, st,

@@ -41,10 +41,9 @@ struct MArgs {
   int64_t K;
   int real_last;
   const int64_t* kdim_dev;
-  // split contraction: part p of ksplit takes [p kchunk, (p + 1) kchunk)
-  // and writes its planes to pre / pim [p][k][M][N]
+  // split contraction: part p of ksplit takes an equal share of the live
+  // contraction, in whole steps, and writes its planes to pre / pim [p][k][M][N]
   int ksplit;
-  int64_t kchunk;
   float *pre, *pim;
 };
 
@@ -181,9 +180,10 @@ __device__ __forceinline__ void cgemm_bf16_body(const MArgs& g, int64_t k, int p
     }
   };
 
-  // contraction range of this part (kchunk is a multiple of BK)
-  const int64_t kbeg = (int64_t)part * g.kchunk;
-  const int64_t kend = kbeg + g.kchunk < Kd ? kbeg + g.kchunk : Kd;
+  // contraction range of this part
+  const int64_t kchunk = g.ksplit > 1 ? ((Kd + g.ksplit - 1) / g.ksplit + BK - 1) / BK * BK : Kd;
+  const int64_t kbeg = (int64_t)part * kchunk;
+  const int64_t kend = kbeg + kchunk < Kd ? kbeg + kchunk : Kd;
   const int64_t nsteps = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
   if (nsteps > 0) load_tile((uint32_t)kbeg);
   for (int64_t ks = 0; ks < nsteps; ++ks) {
@@ -314,6 +314,11 @@ struct SArgs {
   int64_t sa, sb, sc;
   int64_t K;
   int real_last;
+  // split contraction: part p of ksplit takes steps [p kchunk, (p + 1) kchunk)
+  // and writes its planes to pre / pim [p][k][M][N]
+  int ksplit;
+  int64_t kchunk;
+  float *pre, *pim;
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -321,7 +326,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int swz(int row, int q) { return row * 4 + (q ^ ((row >> 1) & 3)); }
 
 template <int TERMS, bool REAL>
-__device__ __forceinline__ void split_body(const SArgs& g, int64_t k, int64_t tm, int64_t tn, u32x4* lds) {
+__device__ __forceinline__ void split_body(const SArgs& g, int64_t k, int64_t tm, int64_t tn, int part, u32x4* lds) {
   constexpr int NPL = REAL ? 2 : 4;  // planes read
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 2, wc = wave & 3;
@@ -351,8 +356,9 @@ __device__ __forceinline__ void split_body(const SArgs& g, int64_t k, int64_t tm
   // two register sets of staged operands: a step is loaded two steps
   // before it is consumed, so a load has a whole step of products to land
   u32x4 ra0[NPL], rb0[NPL], ra1[NPL], rb1[NPL];
+  const int64_t sbeg = part * g.kchunk, steps = g.Kd / SBK - sbeg;  // of this part
   auto load = [&](u32x4 (&ra)[NPL], u32x4 (&rb)[NPL], int64_t ks) {
-    const uint32_t kq = (uint32_t)(ks * (SBK / 8));
+    const uint32_t kq = (uint32_t)((sbeg + ks) * (SBK / 8));
 #pragma unroll
     for (int p = 0; p < NPL; ++p) {
       ra[p] = ap[p][aoff + kq];
@@ -379,7 +385,7 @@ __device__ __forceinline__ void split_body(const SArgs& g, int64_t k, int64_t tm
       ci[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-  const int64_t nsteps = g.Kd / SBK;
+  const int64_t nsteps = steps < g.kchunk ? (steps > 0 ? steps : 0) : g.kchunk;
   const int64_t last = nsteps - 1;
   const int fr = lane & 15, fq = lane >> 4;
   auto compute = [&](int buf) {
@@ -456,8 +462,10 @@ __device__ __forceinline__ void split_body(const SArgs& g, int64_t k, int64_t tm
   }
 
   // epilogue: lane holds rows 4 (lane / 16) + e, column lane % 16 of a tile
-  float* cre = g.cre + k * g.sc;
-  float* cim = g.cim + k * g.sc;
+  const bool parted = g.ksplit > 1;
+  float* cre = parted ? g.pre + ((int64_t)part * g.K + k) * g.M * g.N : g.cre + k * g.sc;
+  float* cim = parted ? g.pim + ((int64_t)part * g.K + k) * g.M * g.N : g.cim + k * g.sc;
+  const int64_t ldc = parted ? g.N : g.ldc;
 #pragma unroll
   for (int i = 0; i < WTI; ++i)
 #pragma unroll
@@ -467,8 +475,8 @@ __device__ __forceinline__ void split_body(const SArgs& g, int64_t k, int64_t tm
         const int64_t gm = m0 + wr * (16 * WTI) + i * 16 + 4 * (lane >> 4) + e;
         const int64_t gn = n0 + wc * (16 * WTJ) + j * 16 + (lane & 15);
         if (gm < g.M && gn < g.N) {
-          cre[gm * g.ldc + gn] = cr[i][j][e];
-          cim[gm * g.ldc + gn] = REAL ? 0.f : ci[i][j][e];
+          cre[gm * ldc + gn] = cr[i][j][e];
+          cim[gm * ldc + gn] = REAL ? 0.f : ci[i][j][e];
         }
       }
 }
@@ -482,6 +490,7 @@ __global__ void ksplit_reduce_kernel(const float* __restrict__ pre, const float*
   if (e >= K * per) return;
   const int64_t k = e / per, r = e - k * per, m = r / N, n = r - m * N;
   float sr = 0.f, si = 0.f;
+#pragma unroll 4
   for (int p = 0; p < ksplit; ++p) {
     sr += pre[(int64_t)p * K * per + e];
     si += pim[(int64_t)p * K * per + e];
@@ -524,9 +533,18 @@ __global__ __launch_bounds__(SNT, 1) void cgemm_split_kernel(SArgs g, int64_t gm
   const int64_t zi = id / per, t = id - zi * per;
   const int64_t tm = t / gn, tn = t - tm * gn;
   if (zi < ncomplex)
-    split_body<TERMS, false>(g, zi + 1, tm, tn, lds);
+    split_body<TERMS, false>(g, zi + 1, tm, tn, (int)blockIdx.y, lds);
   else
-    split_body<TERMS, true>(g, zi == ncomplex ? 0 : g.K - 1, tm, tn, lds);
+    split_body<TERMS, true>(g, zi == ncomplex ? 0 : g.K - 1, tm, tn, (int)blockIdx.y, lds);
+}
+
+int reduce_parts(const float* pre, const float* pim, int ksplit, int64_t K, int64_t M, int64_t N, float* cre, float* cim,
+                 int64_t ldc, int64_t sc, hipStream_t st) {
+  const int64_t n = K * M * N;
+  hipLaunchKernelGGL(ksplit_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pre, pim, ksplit, K, M,
+                     N, cre, cim, ldc, sc);
+  TP_LAUNCH_CHECK();
+  return TP_OK;
 }
 
 }  // namespace
@@ -547,12 +565,11 @@ int cgemm_mfma(const CGemm& p, int prec, hipStream_t st, bool* handled) {
   // a long contraction with few output tiles is split into parts that
   // write float32 partial planes, summed in part order afterwards, when the
   // caller provides the scratch
-  int ksplit = cgemm_ksplit(p.K, p.M, p.N, p.Kd);
+  int ksplit = cgemm_ksplit(p.K, p.real_last, p.M, p.N, p.Kd);
   if (ksplit > 1 && (!p.part_re || !p.part_im || p.part_cap < int64_t(ksplit) * p.K * p.M * p.N)) ksplit = 1;
-  const int64_t kchunk = ksplit > 1 ? ((p.Kd + ksplit - 1) / ksplit + BK - 1) / BK * BK : p.Kd;
   MArgs g{p.M, p.N, p.Kd, (const float*)p.are, (const float*)p.aim, (const float*)p.bre, (const float*)p.bim,
           (float*)p.cre, (float*)p.cim, p.lda, p.ldb, p.ldc, p.sa, p.sb, p.sc, p.K, p.real_last ? 1 : 0,
-          p.kdim_dev, ksplit, kchunk, p.part_re, p.part_im};
+          p.kdim_dev, ksplit, p.part_re, p.part_im};
   const unsigned gx = (unsigned)((p.N + BN - 1) / BN), gy = (unsigned)((p.M + BM - 1) / BM);
   const unsigned gz = (unsigned)(p.K * ksplit);
   if (prec == TP_PREC_BF16X3)
@@ -560,26 +577,21 @@ int cgemm_mfma(const CGemm& p, int prec, hipStream_t st, bool* handled) {
   else
     hipLaunchKernelGGL(cgemm_bf16_kernel<1>, dim3(gx, gy, gz), dim3(NT), 0, st, g);
   TP_LAUNCH_CHECK();
-  if (ksplit > 1) {
-    const int64_t n = p.K * p.M * p.N;
-    hipLaunchKernelGGL(ksplit_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p.part_re,
-                       p.part_im, ksplit, p.K, p.M, p.N, (float*)p.cre, (float*)p.cim, p.ldc, p.sc);
-    TP_LAUNCH_CHECK();
-  }
+  if (ksplit > 1)
+    if (int rc = reduce_parts(p.part_re, p.part_im, ksplit, p.K, p.M, p.N, (float*)p.cre, (float*)p.cim, p.ldc, p.sc, st))
+      return rc;
   *handled = true;
   return TP_OK;
 }
 
-// Parts of a split contraction: enough workgroups to cover the compute
-// units about twice, each part at least 32 steps of the contraction, at
-// most 64 parts.
-int cgemm_ksplit(int64_t K, int64_t M, int64_t N, int64_t Kd) {
-  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * K;
-  if (tiles >= 256 || Kd < 64 * BK) return 1;
-  int64_t s = (512 + tiles - 1) / tiles;
-  s = s < Kd / (32 * BK) ? s : Kd / (32 * BK);
-  s = s < 64 ? s : 64;
-  return s > 1 ? (int)s : 1;
+// Parts of a split contraction, at least four steps each. bf16x3, whole
+// rt-product in us, before (one part up to a contraction of 2048, then at least
+// 32 steps a part; one part always for pre-split operands) / now:
+// 300 x 300 x 5 over 256 picks 52 / 37, 1700 261 / 62, 6000 322 / 154; 512 x 512 x 12
+// over 256 94 / 52, 6000 1478 / 496; pre-split 40 x 40 x 4 over 800 65 / 28, 6000
+// 377 / 37; 500 x 300 x 8 over 256 40 / 37, 6000 505 / 254.
+int cgemm_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd) {
+  return contraction_parts(K, real_last, ((M + BM - 1) / BM) * ((N + BN - 1) / BN), Kd / BK, 4);
 }
 
 int cgemm_split(const SplitGemm& p, hipStream_t st) {
@@ -593,15 +605,23 @@ int cgemm_split(const SplitGemm& p, hipStream_t st) {
   if ((p.M * p.lda) / 8 >= (int64_t(1) << 32) || (p.N * p.ldb) / 8 >= (int64_t(1) << 32))
     return fail(TP_EUNSUPPORTED, "slice too large for the split product");
   SArgs g{(const __bf16*)p.a, (const __bf16*)p.b, p.cre, p.cim, p.M, p.N, p.Kd, p.lda, p.ldb, p.ldc, p.pa, p.pb, p.sa, p.sb, p.sc, p.K,
-          p.real_last ? 1 : 0};
+          p.real_last ? 1 : 0, 1, p.Kd / SBK, p.part_re, p.part_im};
+  // the same split of a long contraction with few output tiles
+  static_assert(SBM == BM && SBN == BN && SBK == BK, "cgemm_ksplit counts these tiles");
+  int ksplit = cgemm_ksplit(p.K, p.real_last, p.M, p.N, p.Kd);
+  if (ksplit > 1 && p.part_re && p.part_im && p.part_cap >= int64_t(ksplit) * p.K * p.M * p.N) {
+    g.ksplit = ksplit;
+    g.kchunk = (p.Kd / SBK + ksplit - 1) / ksplit;
+  }
   const int64_t gm = (p.M + SBM - 1) / SBM, gn = (p.N + SBN - 1) / SBN;
   const int64_t tiles = gm * gn * p.K;
   if (tiles > 0x7fffffffLL) return fail(TP_EUNSUPPORTED, "too many product tiles");
   if (p.terms == 3)
-    hipLaunchKernelGGL(cgemm_split_kernel<3>, dim3((unsigned)tiles), dim3(SNT), 0, st, g, gm, gn);
+    hipLaunchKernelGGL(cgemm_split_kernel<3>, dim3((unsigned)tiles, (unsigned)g.ksplit), dim3(SNT), 0, st, g, gm, gn);
   else
-    hipLaunchKernelGGL(cgemm_split_kernel<1>, dim3((unsigned)tiles), dim3(SNT), 0, st, g, gm, gn);
+    hipLaunchKernelGGL(cgemm_split_kernel<1>, dim3((unsigned)tiles, (unsigned)g.ksplit), dim3(SNT), 0, st, g, gm, gn);
   TP_LAUNCH_CHECK();
+  if (g.ksplit > 1) return reduce_parts(p.part_re, p.part_im, ksplit, p.K, p.M, p.N, p.cre, p.cim, p.ldc, p.sc, st);
   return TP_OK;
 }
 
