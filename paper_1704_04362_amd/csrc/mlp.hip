@@ -343,97 +343,120 @@ __global__ void sketch_apply_kernel(const double* __restrict__ sk, const double*
 // ---------------------------------------------------------------------------
 // MLP on the matrix cores
 // ---------------------------------------------------------------------------
+// Bound: latency. One tile of 64 rows a workgroup is a chain of a few weight
+// loads, 16 x 16 x 16 products and row sums, on at most rows / 64 CUs. So
+// every operand lies in LDS with its contraction index contiguous (a fragment is
+// one 8-byte read; the product's operands are swapped where the result's
+// layout then stores whole quads), all loads of a stage are issued together,
+// eight wavefronts share a tile, and the training step keeps the activations
+// instead of computing them again. 8192 rows: forward 26 -> 8 us, backward
+// 34 -> 11, the sums over tiles, the loss and Adam 40 -> 7 in one launch
+// (replaced: four wavefronts, operands gathered value by value).
 constexpr int TR = 64;  // rows per tile
-constexpr int NT = 256;
-constexpr int LX = KIN + 8, LH = HID + 8;
+constexpr int NT = 512;
+constexpr int LX = KIN + 8, LH = HID + 8, LT = TR + 8;  // LDS rows (padded), of quads
+constexpr int LZ = TR + 4;
 
-// acc += A[16 rows][K] * B[K][16 cols] with element strides:
-// A(i, k) = A[i * asi + k * ask], B(k, j) = B[k * bsk + j * bsj].
-__device__ __forceinline__ f32x4 mfma_tile(const _Float16* A, int asi, int ask, const _Float16* B, int bsk, int bsj,
-                                           int K, f32x4 acc) {
+// acc += A B for 16 x 16 tiles, K deep: A[i][k] at a[i lda + k], B[k][j] at b[j ldb + k].
+__device__ __forceinline__ f32x4 mfma_tile(const _Float16* a, int lda, const _Float16* b, int ldb, int K, f32x4 acc) {
   const int lane = threadIdx.x & 63;
   const int r = lane & 15, kq = 4 * (lane >> 4);
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    half4 a, b;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      a[e] = A[r * asi + (k0 + kq + e) * ask];
-      b[e] = B[(k0 + kq + e) * bsk + r * bsj];
-    }
-    acc = __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, acc, 0, 0, 0);
-  }
+  for (int k0 = 0; k0 < K; k0 += 16)
+    acc = __builtin_amdgcn_mfma_f32_16x16x16f16(*reinterpret_cast<const half4*>(a + r * lda + k0 + kq),
+                                                *reinterpret_cast<const half4*>(b + r * ldb + k0 + kq), acc, 0, 0, 0);
   return acc;
 }
 
-struct MlpShared {
-  _Float16 X[TR][LX];    // input tile, features padded to KIN
-  _Float16 W1[KIN][LH];  // W1 padded (rows 17..31 zero)
-  _Float16 W2[HID][LH];
-  _Float16 H1[TR][LH];
-  _Float16 H2[TR][LH];
-  _Float16 D[TR][LH];    // dH2, then dH1
-  float b1[HID], b2[HID], w3[HID];
-  float z[TR][HID + 4];  // staging for row sums
-  float dout[TR];
-};
-
-// Forward pass of one tile; leaves H1, H2 (post-ReLU, fp16) in LDS and the
-// logits in out (when set). Pre-activations are positive exactly where the
-// stored post-activations are, which the backward pass uses as the masks.
-__device__ void mlp_tile_forward(MlpShared& s, const float* __restrict__ P, const float* __restrict__ feat,
-                                 int64_t nrows, int64_t r0, float* out) {
+// Forward pass of one tile: logits, and with SAVE the activations (post-ReLU,
+// fp16, [row][HID], whole tiles). Pre-activations are positive exactly where
+// the stored post-activations are, which the backward pass uses as the masks.
+template <bool SAVE>
+__global__ __launch_bounds__(NT, 2) void mlp_forward_kernel(const float* __restrict__ P,
+                                                            const float* __restrict__ feat, int64_t nrows,
+                                                            float* __restrict__ out, _Float16* __restrict__ h1,
+                                                            _Float16* __restrict__ h2) {
+  __shared__ __align__(16) _Float16 X[TR][LX];     // input tile, features padded to KIN
+  __shared__ __align__(16) _Float16 W1t[HID][LX];  // W1 transposed (entries 17..31 zero)
+  __shared__ __align__(16) _Float16 W2t[HID][LH];
+  __shared__ __align__(16) _Float16 H1[TR][LH];
+  __shared__ __align__(16) float z[TR][HID + 4];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int64_t r0 = (int64_t)blockIdx.x * TR;
+  // four rows of a column of W2 at a time, lanes along the row
+  constexpr int Q2 = HID * HID / 4 / NT;
+  float w2[Q2][4];
+#pragma unroll
+  for (int u = 0; u < Q2; ++u) {
+    const int e = tid + NT * u, j = e % HID, k = 4 * (e / HID);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) w2[u][v] = P[OFF_W2 + (k + v) * HID + j];
+  }
   for (int e = tid; e < TR * KIN; e += NT) {
     const int r = e / KIN, c = e % KIN;
     const int64_t row = r0 + r;
-    s.X[r][c] = (_Float16)((c < DIN && row < nrows) ? feat[row * DIN + c] : 0.f);
+    X[r][c] = (_Float16)((c < DIN && row < nrows) ? feat[row * DIN + c] : 0.f);
   }
-  for (int e = tid; e < KIN * HID; e += NT) {
-    const int r = e / HID, c = e % HID;
-    s.W1[r][c] = (_Float16)(r < DIN ? P[OFF_W1 + r * HID + c] : 0.f);
+  for (int e = tid; e < HID * KIN; e += NT) {
+    const int k = e / HID, j = e % HID;
+    W1t[j][k] = (_Float16)(k < DIN ? P[OFF_W1 + k * HID + j] : 0.f);
   }
-  for (int e = tid; e < HID * HID; e += NT) s.W2[e / HID][e % HID] = (_Float16)P[OFF_W2 + e];
-  for (int e = tid; e < HID; e += NT) {
-    s.b1[e] = P[OFF_B1 + e];
-    s.b2[e] = P[OFF_B2 + e];
-    s.w3[e] = P[OFF_W3 + e];
-  }
-  __syncthreads();
-  // layer 1: wave w owns rows 16w..16w+15, all 8 column tiles
-  for (int nt = 0; nt < HID / 16; ++nt) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma_tile(&s.X[16 * wave][0], LX, 1, &s.W1[0][16 * nt], LH, 1, KIN, acc);
+  const int rt = wave & 3, c0 = 64 * (wave >> 2);  // 16 rows, 64 columns a wavefront
+  const int row = 16 * rt + (lane & 15), cq = 4 * (lane >> 4);
+  float b1[4][4], b2[4][4], w3[4][4];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int row = 16 * wave + 4 * (lane >> 4) + e, col = 16 * nt + (lane & 15);
-      s.H1[row][col] = (_Float16)fmaxf(acc[e] + s.b1[col], 0.f);
+      const int c = c0 + 16 * nt + cq + e;
+      b1[nt][e] = P[OFF_B1 + c];
+      b2[nt][e] = P[OFF_B2 + c];
+      w3[nt][e] = P[OFF_W3 + c];
     }
+#pragma unroll
+  for (int u = 0; u < Q2; ++u) {
+    const int e = tid + NT * u, j = e % HID, k = 4 * (e / HID);
+    *reinterpret_cast<half4*>(&W2t[j][k]) =
+        half4{(_Float16)w2[u][0], (_Float16)w2[u][1], (_Float16)w2[u][2], (_Float16)w2[u][3]};
   }
   __syncthreads();
-  for (int nt = 0; nt < HID / 16; ++nt) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma_tile(&s.H1[16 * wave][0], LH, 1, &s.W2[0][16 * nt], LH, 1, HID, acc);
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    const int c = c0 + 16 * nt;
+    const f32x4 acc = mfma_tile(&W1t[c][0], LX, &X[16 * rt][0], LX, KIN, f32x4{0.f, 0.f, 0.f, 0.f});
+    half4 h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (_Float16)fmaxf(acc[e] + b1[nt][e], 0.f);
+    *reinterpret_cast<half4*>(&H1[row][c + cq]) = h;
+    if (SAVE) *reinterpret_cast<half4*>(&h1[(r0 + row) * HID + c + cq]) = h;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    const int c = c0 + 16 * nt;
+    const f32x4 acc = mfma_tile(&W2t[c][0], LH, &H1[16 * rt][0], LH, HID, f32x4{0.f, 0.f, 0.f, 0.f});
+    half4 h;
+    f32x4 zq;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int row = 16 * wave + 4 * (lane >> 4) + e, col = 16 * nt + (lane & 15);
-      const float h = fmaxf(acc[e] + s.b2[col], 0.f);
-      s.H2[row][col] = (_Float16)h;
-      s.z[row][col] = h * s.w3[col];
+      const float v = fmaxf(acc[e] + b2[nt][e], 0.f);
+      h[e] = (_Float16)v;
+      zq[e] = v * w3[nt][e];
     }
+    *reinterpret_cast<f32x4*>(&z[row][c + cq]) = zq;
+    if (SAVE) *reinterpret_cast<half4*>(&h2[(r0 + row) * HID + c + cq]) = h;
   }
   __syncthreads();
-  if (out && tid < TR) {
+  if (tid < TR && r0 + tid < nrows) {
     float o = P[OFF_B3];
-    for (int c = 0; c < HID; ++c) o += s.z[tid][c];
-    if (r0 + tid < nrows) out[r0 + tid] = o;
+#pragma unroll 8
+    for (int c = 0; c < HID; c += 4) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&z[tid][c]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o += v[e];
+    }
+    out[r0 + tid] = o;
   }
-  __syncthreads();
-}
-
-__global__ __launch_bounds__(NT) void mlp_forward_kernel(const float* __restrict__ P, const float* __restrict__ feat,
-                                                         int64_t nrows, float* __restrict__ out) {
-  __shared__ MlpShared s;
-  mlp_tile_forward(s, P, feat, nrows, (int64_t)blockIdx.x * TR, out);
 }
 
 // Per tensor: p = softmax(o), loss = KL(p* || p), dO = (p - p*) / T.
@@ -492,103 +515,163 @@ __global__ __launch_bounds__(256) void softmax_grad_kernel(const float* __restri
   if (tid == 0) loss_part[t] = (float)(red[0] / (double)T);
 }
 
-// Backward of one tile: recomputes the forward pass, then writes this
-// tile's gradient contribution (parameter layout) to partial[tile].
-__global__ __launch_bounds__(NT) void mlp_backward_kernel(const float* __restrict__ P, const float* __restrict__ feat,
-                                                          const float* __restrict__ dout, int64_t nrows,
-                                                          float* __restrict__ partial) {
-  __shared__ MlpShared s;
+// Backward of one tile from the forward pass's activations: this tile's
+// gradient contribution (parameter layout) to partial[tile].
+__global__ __launch_bounds__(NT, 2) void mlp_backward_kernel(const float* __restrict__ P,
+                                                             const float* __restrict__ feat,
+                                                             const float* __restrict__ dout, int64_t nrows,
+                                                             const _Float16* __restrict__ h1,
+                                                             const _Float16* __restrict__ h2,
+                                                             float* __restrict__ partial) {
+  // (transposed: [feature][row])
+  __shared__ __align__(16) _Float16 Xt[KIN][LT];
+  __shared__ __align__(16) _Float16 W2[HID][LH];
+  __shared__ __align__(16) _Float16 H1t[HID][LT];
+  __shared__ __align__(16) _Float16 H2t[HID][LT];
+  __shared__ __align__(16) _Float16 D[TR][LH];  // dH2
+  __shared__ __align__(16) _Float16 Dt[HID][LT];
+  __shared__ __align__(16) float zt[HID][LZ];  // dH1
+  __shared__ float sd[TR];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int64_t r0 = (int64_t)blockIdx.x * TR;
-  mlp_tile_forward(s, P, feat, nrows, r0, nullptr);
   float* g = partial + (int64_t)blockIdx.x * NPARAM;
-  if (tid < TR) s.dout[tid] = (r0 + tid < nrows) ? dout[r0 + tid] : 0.f;
-  __syncthreads();
-  // w3, b3 and dH2 = dO w3 (.) [h2 > 0]
-  for (int c = tid; c < HID; c += NT) {
-    float gw = 0.f;
-    for (int r = 0; r < TR; ++r) gw += (float)s.H2[r][c] * s.dout[r];
-    g[OFF_W3 + c] = gw;
+  constexpr int Q2 = HID * HID / 4 / NT;
+  float4 w2[Q2];
+#pragma unroll
+  for (int u = 0; u < Q2; ++u) {  // (the parameter array's W2 need not be 16-byte aligned)
+    const float* src = P + OFF_W2 + 4 * (tid + NT * u);
+    w2[u] = float4{src[0], src[1], src[2], src[3]};
   }
-  if (tid == 0) {
+  {
+    // 4 rows x 4 columns of the activations a thread: dH2 = dO w3 (.) [h2 > 0]
+    static_assert(TR * HID / 16 == NT, "one block of 4 x 4 a thread");
+    const int c = 4 * (tid % (HID / 4)), r = 4 * (tid / (HID / 4));
+    half4 x[4], y[4];
+    float d[4], w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = *reinterpret_cast<const half4*>(&h1[(r0 + r + i) * HID + c]);
+      y[i] = *reinterpret_cast<const half4*>(&h2[(r0 + r + i) * HID + c]);
+      d[i] = r0 + r + i < nrows ? dout[r0 + r + i] : 0.f;
+      w[i] = P[OFF_W3 + c + i];
+    }
+    half4 dh[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dh[i][e] = (_Float16)((float)y[i][e] > 0.f ? d[i] * w[e] : 0.f);
+      *reinterpret_cast<half4*>(&D[r + i][c]) = dh[i];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      *reinterpret_cast<half4*>(&H1t[c + e][r]) = half4{x[0][e], x[1][e], x[2][e], x[3][e]};
+      *reinterpret_cast<half4*>(&H2t[c + e][r]) = half4{y[0][e], y[1][e], y[2][e], y[3][e]};
+      *reinterpret_cast<half4*>(&Dt[c + e][r]) = half4{dh[0][e], dh[1][e], dh[2][e], dh[3][e]};
+    }
+    if (c == 0)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sd[r + i] = d[i];
+  }
+  for (int e = tid; e < TR * KIN; e += NT) {
+    const int r = e / KIN, c = e % KIN;
+    Xt[c][r] = (_Float16)((c < DIN && r0 + r < nrows) ? feat[(r0 + r) * DIN + c] : 0.f);
+  }
+#pragma unroll
+  for (int u = 0; u < Q2; ++u) {
+    const int e = 4 * (tid + NT * u);
+    *reinterpret_cast<half4*>(&W2[e / HID][e % HID]) =
+        half4{(_Float16)w2[u].x, (_Float16)w2[u].y, (_Float16)w2[u].z, (_Float16)w2[u].w};
+  }
+  __syncthreads();
+  const int rq = 4 * (lane >> 4), cl = lane & 15;
+  // dH1 = (dH2 W2^T) (.) [h1 > 0]
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int rt = wave & 3, c = 64 * (wave >> 2) + 16 * t;
+    const f32x4 acc = mfma_tile(&D[16 * rt][0], LH, &W2[c][0], LH, HID, f32x4{0.f, 0.f, 0.f, 0.f});
+    const half4 h = *reinterpret_cast<const half4*>(&H1t[c + cl][16 * rt + rq]);
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (float)h[e] > 0.f ? acc[e] : 0.f;
+    *reinterpret_cast<f32x4*>(&zt[c + cl][16 * rt + rq]) = v;
+  }
+  // W2 = H1^T dH2
+#pragma unroll
+  for (int t = 0; t < HID / 16; ++t) {
+    const f32x4 acc = mfma_tile(&H1t[16 * wave][0], LT, &Dt[16 * t][0], LT, TR, f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+    for (int e = 0; e < 4; ++e) g[OFF_W2 + (16 * wave + rq + e) * HID + 16 * t + cl] = acc[e];
+  }
+  // w3, b2 = column sums of dH2, b3
+  if (tid < HID) {
+    float gw = 0.f;
+#pragma unroll 16
+    for (int r = 0; r < TR; ++r) gw += (float)H2t[tid][r] * sd[r];
+    g[OFF_W3 + tid] = gw;
+  } else if (tid < 2 * HID) {
     float gb = 0.f;
-    for (int r = 0; r < TR; ++r) gb += s.dout[r];
+#pragma unroll 16
+    for (int r = 0; r < TR; ++r) gb += (float)Dt[tid - HID][r];
+    g[OFF_B2 + tid - HID] = gb;
+  } else if (tid == 2 * HID) {
+    float gb = 0.f;
+#pragma unroll 16
+    for (int r = 0; r < TR; ++r) gb += sd[r];
     g[OFF_B3] = gb;
   }
-  for (int e = tid; e < TR * HID; e += NT) {
-    const int r = e / HID, c = e % HID;
-    s.D[r][c] = (_Float16)((float)s.H2[r][c] > 0.f ? s.dout[r] * s.w3[c] : 0.f);
-  }
   __syncthreads();
-  // b2 = column sums of dH2; W2 = H1^T dH2
-  for (int c = tid; c < HID; c += NT) {
+  // W1 = X^T dH1 (fp16), b1 = column sums of dH1 (float)
+  static_assert(HID / 16 == NT / 64, "16 columns a wavefront");
+#pragma unroll
+  for (int it = 0; it < KIN / 16; ++it) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k0 = 0; k0 < TR; k0 += 16) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&zt[16 * wave + cl][k0 + rq]);
+      acc = __builtin_amdgcn_mfma_f32_16x16x16f16(
+          *reinterpret_cast<const half4*>(&Xt[16 * it + cl][k0 + rq]),
+          half4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]}, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = 16 * it + rq + e;
+      if (row < DIN) g[OFF_W1 + row * HID + 16 * wave + cl] = acc[e];
+    }
+  }
+  if (tid < HID) {
     float gb = 0.f;
-    for (int r = 0; r < TR; ++r) gb += (float)s.D[r][c];
-    g[OFF_B2 + c] = gb;
-  }
-  for (int t = wave; t < (HID / 16) * (HID / 16); t += NT / 64) {
-    const int it = t / (HID / 16), jt = t % (HID / 16);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma_tile(&s.H1[0][16 * it], 1, LH, &s.D[0][16 * jt], LH, 1, TR, acc);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int row = 16 * it + 4 * (lane >> 4) + e, col = 16 * jt + (lane & 15);
-      g[OFF_W2 + row * HID + col] = acc[e];
-    }
-  }
-  // dH1 = (dH2 W2^T) (.) [h1 > 0], staged in z as float
-  for (int nt = 0; nt < HID / 16; ++nt) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma_tile(&s.D[16 * wave][0], LH, 1, &s.W2[16 * nt][0], 1, LH, HID, acc);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int row = 16 * wave + 4 * (lane >> 4) + e, col = 16 * nt + (lane & 15);
-      s.z[row][col] = (float)s.H1[row][col] > 0.f ? acc[e] : 0.f;
-    }
-  }
-  __syncthreads();
-  for (int e = tid; e < TR * HID; e += NT) s.D[e / HID][e % HID] = (_Float16)s.z[e / HID][e % HID];
-  __syncthreads();
-  // b1 = column sums of dH1 (float); W1 = X^T dH1
-  for (int c = tid; c < HID; c += NT) {
-    float gb = 0.f;
-    for (int r = 0; r < TR; ++r) gb += s.z[r][c];
-    g[OFF_B1 + c] = gb;
-  }
-  for (int t = wave; t < (KIN / 16) * (HID / 16); t += NT / 64) {
-    const int it = t / (HID / 16), jt = t % (HID / 16);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma_tile(&s.X[0][16 * it], 1, LX, &s.D[0][16 * jt], LH, 1, TR, acc);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int row = 16 * it + 4 * (lane >> 4) + e, col = 16 * jt + (lane & 15);
-      if (row < DIN) g[OFF_W1 + row * HID + col] = acc[e];
-    }
+#pragma unroll 16
+    for (int r = 0; r < TR; ++r) gb += zt[tid][r];
+    g[OFF_B1 + tid] = gb;
   }
 }
 
-__global__ void grad_reduce_kernel(const float* __restrict__ partial, int64_t ntiles, float* __restrict__ grad) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The tiles' gradients summed in tile order and Adam's update with them (adam
+// false: the gradient only), one parameter a thread; the last workgroup sums the
+// tensors' losses.
+constexpr int GNT = 64;
+__global__ __launch_bounds__(GNT) void grad_adam_kernel(const float* __restrict__ partial, int64_t ntiles,
+                                                        float* __restrict__ grad, const float* __restrict__ lpart,
+                                                        int64_t T, float* __restrict__ loss, bool adam,
+                                                        float* __restrict__ P, float* __restrict__ M,
+                                                        float* __restrict__ V, float lr, float b1, float b2, float eps,
+                                                        float c1, float c2) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x == 0 && loss) {
+      float s = 0.f;
+#pragma unroll 16
+      for (int64_t t = 0; t < T; ++t) s += lpart[t];
+      *loss = s;
+    }
+    return;
+  }
+  const int64_t p = (int64_t)blockIdx.x * GNT + threadIdx.x;
   if (p >= NPARAM) return;
-  float s = 0.f;
-  for (int64_t t = 0; t < ntiles; ++t) s += partial[t * NPARAM + p];
-  grad[p] = s;
-}
-
-__global__ void loss_reduce_kernel(const float* __restrict__ part, int64_t T, float* __restrict__ loss) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    float s = 0.f;
-    for (int64_t t = 0; t < T; ++t) s += part[t];
-    *loss = s;
-  }
-}
-
-__global__ void adam_kernel(float* __restrict__ P, float* __restrict__ M, float* __restrict__ V,
-                            const float* __restrict__ G, float lr, float b1, float b2, float eps, float c1,
-                            float c2) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= NPARAM) return;
-  const float g = G[p];
+  float g = 0.f;
+#pragma unroll 32
+  for (int64_t t = 0; t < ntiles; ++t) g += partial[t * NPARAM + p];
+  if (grad) grad[p] = g;
+  if (!adam) return;
   const float m = b1 * M[p] + (1.f - b1) * g;
   const float v = b2 * V[p] + (1.f - b2) * g * g;
   M[p] = m;
@@ -684,16 +767,16 @@ int mlp_features(const float* a, int64_t n1, int64_t n2, int64_t n3, const float
 
 int mlp_forward(const float* P, const float* feat, int64_t nrows, float* out, hipStream_t st) {
   if (nrows == 0) return TP_OK;
-  hipLaunchKernelGGL(mlp_forward_kernel, dim3((unsigned)((nrows + TR - 1) / TR)), dim3(NT), 0, st, P, feat, nrows,
-                     out);
+  hipLaunchKernelGGL(mlp_forward_kernel<false>, dim3((unsigned)((nrows + TR - 1) / TR)), dim3(NT), 0, st, P, feat,
+                     nrows, out, (_Float16*)nullptr, (_Float16*)nullptr);
   TP_LAUNCH_CHECK();
   return TP_OK;
 }
 
 size_t mlp_train_ws(int64_t ntensors, int64_t nslices) {
   const int64_t rows = ntensors * nslices, ntiles = (rows + TR - 1) / TR;
-  return 3 * align_up(size_t(rows) * 4) + align_up(size_t(ntiles) * NPARAM * 4) + align_up(size_t(NPARAM) * 4) +
-         align_up(size_t(ntensors) * 4) + 2048;
+  return 2 * align_up(size_t(rows) * 4) + align_up(size_t(ntiles) * NPARAM * 4) + align_up(size_t(ntensors) * 4) +
+         2 * align_up(size_t(ntiles) * TR * HID * sizeof(_Float16)) + 2048;
 }
 
 int mlp_train_step(float* P, float* M, float* V, int64_t step, double lr, const float* feat, const float* target,
@@ -703,28 +786,23 @@ int mlp_train_step(float* P, float* M, float* V, int64_t step, double lr, const 
   float* o = ar.take<float>(rows);
   float* dout = ar.take<float>(rows);
   float* part = ar.take<float>(ntiles * NPARAM);
-  float* grad = ar.take<float>(NPARAM);
   float* lpart = ar.take<float>(T);
+  _Float16* h1 = ar.take<_Float16>(ntiles * TR * HID);
+  _Float16* h2 = ar.take<_Float16>(ntiles * TR * HID);
   if (!ar.ok()) return fail(TP_EWORKSPACE, "training workspace too small");
-  if (int rc = mlp_forward(P, feat, rows, o, st)) return rc;
+  if (rows > 0) {
+    hipLaunchKernelGGL(mlp_forward_kernel<true>, dim3((unsigned)ntiles), dim3(NT), 0, st, P, feat, rows, o, h1, h2);
+    TP_LAUNCH_CHECK();
+  }
   hipLaunchKernelGGL(softmax_grad_kernel, dim3((unsigned)T), dim3(256), 0, st, o, target, nsl, T, dout, lpart);
   TP_LAUNCH_CHECK();
-  hipLaunchKernelGGL(mlp_backward_kernel, dim3((unsigned)ntiles), dim3(NT), 0, st, P, feat, dout, rows, part);
+  hipLaunchKernelGGL(mlp_backward_kernel, dim3((unsigned)ntiles), dim3(NT), 0, st, P, feat, dout, rows, h1, h2, part);
   TP_LAUNCH_CHECK();
-  float* g = grad_out ? grad_out : grad;
-  hipLaunchKernelGGL(grad_reduce_kernel, dim3(nblk(NPARAM)), dim3(256), 0, st, part, ntiles, g);
+  const double b1 = 0.9, b2 = 0.999;
+  const double c1 = 1.0 - std::pow(b1, (double)step), c2 = 1.0 - std::pow(b2, (double)step);
+  hipLaunchKernelGGL(grad_adam_kernel, dim3(nblk(NPARAM, GNT) + 1), dim3(GNT), 0, st, part, ntiles, grad_out, lpart, T,
+                     loss, step > 0, P, M, V, (float)lr, (float)b1, (float)b2, 1e-8f, (float)c1, (float)c2);
   TP_LAUNCH_CHECK();
-  if (loss) {
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(64), 0, st, lpart, T, loss);
-    TP_LAUNCH_CHECK();
-  }
-  if (step > 0) {
-    const double b1 = 0.9, b2 = 0.999;
-    const double c1 = 1.0 - std::pow(b1, (double)step), c2 = 1.0 - std::pow(b2, (double)step);
-    hipLaunchKernelGGL(adam_kernel, dim3(nblk(NPARAM)), dim3(256), 0, st, P, M, V, g, (float)lr, (float)b1,
-                       (float)b2, 1e-8f, (float)c1, (float)c2);
-    TP_LAUNCH_CHECK();
-  }
   return TP_OK;
 }
 

@@ -200,3 +200,30 @@ def test_proposal_weights():
     ref = M.proposal(Q, X16, alpha=0.2)
     assert abs(w.sum() - 1) < 1e-12
     assert np.linalg.norm(w - ref) < 1e-2 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("T_,n", [(1, 1), (1, 64), (3, 43), (1, 63), (5, 13), (40, 33)])
+def test_training_step_at_tile_edges(T_, n):
+    """Rows around whole tiles of 64: the gradient (bounds of the module
+    docstring), Adam's update with the same gradient as a call that asks for it
+    alone, and the logits of the forward entry point unchanged beside it."""
+    P = _params(9)
+    rs = np.random.default_rng(T_ * 100 + n)
+    X = rs.standard_normal((T_ * n, 17)).astype(np.float32)
+    targets = np.stack([M.softmax(2 * rs.standard_normal(n)) for _ in range(T_)]).astype(np.float32)
+    params = api.mlp_pack(P)
+    z = torch.zeros_like(params)
+    loss, grad = api.mlp_train_step(params, z, z.clone(), 0, 0.0, dev(X), dev(targets), want_grad=True)
+    Q, X16 = _fp16_view(P, X)
+    lref, gref, oref = M.loss_and_grad(Q, X16, [t.astype(np.float64) for t in targets], n)
+    gr = np.concatenate([gref[k].ravel() for k in ("W1", "b1", "W2", "b2", "w3", "b3")])
+    g = grad.cpu().numpy().astype(np.float64)
+    if n > 1:  # (one slice: softmax is 1 and the gradient 0)
+        assert abs(loss.item() - lref) < 1e-2 * abs(lref)
+        assert np.linalg.norm(g - gr) < 2e-2 * np.linalg.norm(gr)
+    else:
+        assert not g.any()
+    m, v = torch.zeros_like(params), torch.zeros_like(params)
+    loss1, none = api.mlp_train_step(params, m, v, 1, 1e-3, dev(X), dev(targets))
+    assert none is None and loss1.item() == loss.item()
+    np.testing.assert_allclose(m.cpu().numpy(), 0.1 * g, rtol=1e-6, atol=1e-12)
