@@ -10,7 +10,7 @@
 //
 // Tiling: a 256-thread workgroup owns 64 rows x NB (32 or 64) columns of
 // one Fourier slice and walks the contraction in 32-deep steps; wavefront w
-// owns rows 16 w .. 16 w + 15 and all NB columns. A step's A and B tiles are
+// owns rows 16 w .. 16 w + 15 and all NB columns. In float32 a step's A and B tiles are
 // staged in LDS (two buffers) and the next step's values are loaded into
 // registers while the current step is on the matrix cores.
 #include "common.hpp"
@@ -180,89 +180,192 @@ __global__ __launch_bounds__(TT) void cgemm_tall_kernel(TArgs g) {
   tall_store<NB>(g, k, m0, wave, gq, c, cr, ci, real);
 }
 
-// Split bf16 matrix cores. LDS holds the four planes (hi re, lo re, hi im,
-// lo im) of A as [m][k] and of B^T as [n][k], k contiguous, so that a lane
-// reads its 8 consecutive k values of a 32-deep step with one 16-byte read.
-template <int OPA, int NB>
-__global__ __launch_bounds__(TT) void cgemm_tall_split_kernel(TArgs g) {
-  // 96-byte rows (32 mod 64): the 16-byte fragment reads are free of bank conflicts
-  constexpr int LK = KB + 16, NTL = NB / 16;
-  __shared__ __align__(16) __bf16 as[2][4][TM][LK];
-  __shared__ __align__(16) __bf16 bs[2][4][NB][LK];
+// Split bf16 matrix cores. A wavefront owns its 16 rows of op(A) alone, so a
+// lane loads its 8 values of a 32-deep step (row c, k = 8 gq ..) straight from
+// HBM, two steps ahead, and splits them in registers; only B, shared by the
+// wavefronts, goes through LDS: four planes (hi re, lo re, hi im, lo im) of B^T as
+// [n][k], 64 deep at a time, quads of k written at once (NB = 32: two buffers;
+// 64: one, for two workgroups a CU). Bound: reading A. 1024 x 30 x 1024 over
+// 65 slices (545 MB): op = N 216 -> 131 us, op = C 315 -> 135 (replaced: both
+// operands split value by value into LDS by predicated loads).
+template <int NB>
+struct TallLds {
+  // 160-byte rows (32 mod 64): the 16-byte fragment reads are free of bank conflicts
+  static constexpr int KC = 64, LK = KC + 16, bufs = NB == 32 ? 2 : 1;
+  __bf16 b[bufs][4][NB][LK];
+};
+
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& lo) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const __bf16 h = (__bf16)x[e];
+    hi[e] = h;
+    lo[e] = (__bf16)(x[e] - (float)h);
+  }
+}
+
+template <int OPA, int NB, bool REAL>
+__device__ __forceinline__ void tall_split_body(const TArgs& g, int64_t k, int64_t m0, int64_t kd, TallLds<NB>& lds) {
+  using L = TallLds<NB>;
+  constexpr int NTL = NB / 16, NP = REAL ? 1 : 2, KC = L::KC, RB = KC * NB / 4 / TT;
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int gq = lane >> 4, c = lane & 15;
-  const int64_t k = blockIdx.z, m0 = (int64_t)blockIdx.y * TM;
-  const bool real = (k == 0) || (g.real_last && k == g.K - 1);
-  const int64_t kd = tall_kd(g);
-  const float* are = g.are + k * g.sa;
-  const float* aim = g.aim + k * g.sa;
-  const float* bre = g.bre + k * g.sb;
-  const float* bim = g.bim + k * g.sb;
-  using L = StepLoad<OPA, NB>;
-  L ld;
-  auto split_put = [](__bf16* hi, __bf16* lo, float x) {
-    const __bf16 h = (__bf16)x;
-    *hi = h;
-    *lo = (__bf16)(x - (float)h);
-  };
-  auto put = [&](int b) {
+  // rows beyond M and columns beyond N read the last one; they are never stored
+  const int64_t m = m0 + 16 * wave + c < g.M ? m0 + 16 * wave + c : g.M - 1;
+  const float* ap[2] = {g.are + k * g.sa, g.aim + k * g.sa};
+  const float* bp[2] = {g.bre + k * g.sb, g.bim + k * g.sb};
+  const int64_t a0 = OPA == 0 ? m * g.lda + 8 * gq : 8 * gq * g.lda + m, astep = OPA == 0 ? KB : KB * g.lda;
+  const int64_t nfull = kd / KB, last = nfull - 1, nch = (nfull + 1) / 2;
+
+  float a[2][NP][8], rb[RB][NP][4];
+  auto load_a = [&](float (&x)[NP][8], int64_t st) {
+    const int64_t o = a0 + (st < last ? st : last) * astep;
 #pragma unroll
-    for (int u = 0; u < L::RA; ++u) {
-      int m, kk;
-      L::a_index(tid + TT * u, m, kk);
-      split_put(&as[b][0][m][kk], &as[b][1][m][kk], ld.ar[u]);
-      split_put(&as[b][2][m][kk], &as[b][3][m][kk], ld.ai[u]);
+    for (int p = 0; p < NP; ++p) {
+      if constexpr (OPA == 0) {
+        __builtin_memcpy(x[p], ap[p] + o, 16);
+        __builtin_memcpy(x[p] + 4, ap[p] + o + 4, 16);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[p][e] = ap[p][o + e * g.lda];
+      }
     }
+  };
+  auto load_b = [&](int64_t ch) {
 #pragma unroll
-    for (int u = 0; u < L::RB; ++u) {
-      const int e = tid + TT * u, kk = e / NB, n = e % NB;
-      split_put(&bs[b][0][n][kk], &bs[b][1][n][kk], ld.br[u]);
-      split_put(&bs[b][2][n][kk], &bs[b][3][n][kk], ld.bi[u]);
+    for (int u = 0; u < RB; ++u) {
+      const int e = tid + TT * u, n = e % NB < g.N ? e % NB : (int)g.N - 1;
+      const int64_t k0 = ch * KC + 4 * (e / NB);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t kk = k0 + v < kd ? k0 + v : kd - 1;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) rb[u][p][v] = bp[p][kk * g.ldb + n];
+      }
+    }
+  };
+  auto put_b = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+      const int e = tid + TT * u, n = e % NB, kq = 4 * (e / NB);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        bf16x4 hi, lo;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          hi[v] = (__bf16)rb[u][p][v];
+          lo[v] = (__bf16)(rb[u][p][v] - (float)hi[v]);
+        }
+        *reinterpret_cast<bf16x4*>(&lds.b[buf][2 * p][n][kq]) = hi;
+        *reinterpret_cast<bf16x4*>(&lds.b[buf][2 * p + 1][n][kq]) = lo;
+      }
     }
   };
   f32x4 cr[NTL], ci[NTL];
 #pragma unroll
   for (int nt = 0; nt < NTL; ++nt) cr[nt] = ci[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int64_t nsteps = (kd + KB - 1) / KB;
-  if (nsteps > 0) {
-    ld.load(g, are, aim, bre, bim, m0, 0, kd, real, tid);
-    put(0);
-    __syncthreads();
-  }
-  for (int64_t st = 0; st < nsteps; ++st) {
-    const int b = (int)(st & 1);
-    if (st + 1 < nsteps) ld.load(g, are, aim, bre, bim, m0, (st + 1) * KB, kd, real, tid);
-    const int row = 16 * wave + c, col = 8 * gq;
-    const bf16x8 arh = *reinterpret_cast<const bf16x8*>(&as[b][0][row][col]);
-    const bf16x8 arl = *reinterpret_cast<const bf16x8*>(&as[b][1][row][col]);
-    const bf16x8 aih = *reinterpret_cast<const bf16x8*>(&as[b][2][row][col]);
-    const bf16x8 ail = *reinterpret_cast<const bf16x8*>(&as[b][3][row][col]);
-    const bf16x8 nih = bneg(aih), nil = bneg(ail);
+  struct Split {
+    bf16x8 h[NP], l[NP];
+  };
+  auto products = [&](const Split& x, int buf, int k0) {
+    const int col = k0 + 8 * gq;
+    bf16x8 aih, ail, nih, nil;
+    if constexpr (!REAL) {  // conjugate for op = C
+      const bf16x8 th = bneg(x.h[1]), tl = bneg(x.l[1]);
+      aih = OPA == 0 ? x.h[1] : th;
+      ail = OPA == 0 ? x.l[1] : tl;
+      nih = OPA == 0 ? th : x.h[1];
+      nil = OPA == 0 ? tl : x.l[1];
+    }
 #pragma unroll
     for (int nt = 0; nt < NTL; ++nt) {
       const int n = 16 * nt + c;
-      const bf16x8 brh = *reinterpret_cast<const bf16x8*>(&bs[b][0][n][col]);
-      const bf16x8 brl = *reinterpret_cast<const bf16x8*>(&bs[b][1][n][col]);
-      const bf16x8 bih = *reinterpret_cast<const bf16x8*>(&bs[b][2][n][col]);
-      const bf16x8 bil = *reinterpret_cast<const bf16x8*>(&bs[b][3][n][col]);
+      const bf16x8 brh = *reinterpret_cast<const bf16x8*>(&lds.b[buf][0][n][col]);
+      const bf16x8 brl = *reinterpret_cast<const bf16x8*>(&lds.b[buf][1][n][col]);
       // Re += Ar Br - Ai Bi, Im += Ar Bi + Ai Br (three split terms each)
-      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arh, brh, cr[nt], 0, 0, 0);
-      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arh, brl, cr[nt], 0, 0, 0);
-      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arl, brh, cr[nt], 0, 0, 0);
-      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nih, bih, cr[nt], 0, 0, 0);
-      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nih, bil, cr[nt], 0, 0, 0);
-      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nil, bih, cr[nt], 0, 0, 0);
-      ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arh, bih, ci[nt], 0, 0, 0);
-      ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arh, bil, ci[nt], 0, 0, 0);
-      ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arl, bih, ci[nt], 0, 0, 0);
-      ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aih, brh, ci[nt], 0, 0, 0);
-      ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aih, brl, ci[nt], 0, 0, 0);
-      ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ail, brh, ci[nt], 0, 0, 0);
+      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.h[0], brh, cr[nt], 0, 0, 0);
+      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.h[0], brl, cr[nt], 0, 0, 0);
+      cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.l[0], brh, cr[nt], 0, 0, 0);
+      if constexpr (!REAL) {
+        const bf16x8 bih = *reinterpret_cast<const bf16x8*>(&lds.b[buf][2][n][col]);
+        const bf16x8 bil = *reinterpret_cast<const bf16x8*>(&lds.b[buf][3][n][col]);
+        cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nih, bih, cr[nt], 0, 0, 0);
+        cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nih, bil, cr[nt], 0, 0, 0);
+        cr[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nil, bih, cr[nt], 0, 0, 0);
+        ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.h[0], bih, ci[nt], 0, 0, 0);
+        ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.h[0], bil, ci[nt], 0, 0, 0);
+        ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.l[0], bih, ci[nt], 0, 0, 0);
+        ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aih, brh, ci[nt], 0, 0, 0);
+        ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aih, brl, ci[nt], 0, 0, 0);
+        ci[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ail, brh, ci[nt], 0, 0, 0);
+      }
     }
-    if (st + 1 < nsteps) put(b ^ 1);
+  };
+  auto split_a = [&](const float (&x)[NP][8]) {
+    Split s;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) split8(x[p], s.h[p], s.l[p]);
+    return s;
+  };
+  if (nfull > 0) {
+    load_b(0);
+    load_a(a[0], 0);
+    load_a(a[1], 1);
+    put_b(0);
     __syncthreads();
+    for (int64_t ch = 0; ch < nch; ++ch) {
+      const int buf = L::bufs == 2 ? (int)(ch & 1) : 0;
+      load_b(ch + 1 < nch ? ch + 1 : ch);  // (past the end: the same again, never used)
+      {
+        const Split x = split_a(a[0]);
+        load_a(a[0], 2 * ch + 2);
+        products(x, buf, 0);
+      }
+      if (2 * ch + 1 < nfull) {
+        const Split x = split_a(a[1]);
+        load_a(a[1], 2 * ch + 3);
+        products(x, buf, KB);
+      }
+      if (L::bufs == 1) __syncthreads();
+      put_b(L::bufs == 2 ? buf ^ 1 : 0);
+      __syncthreads();
+    }
   }
-  tall_store<NB>(g, k, m0, wave, gq, c, cr, ci, real);
+  // the last k < 32, zero beyond the contraction
+  if (const int64_t kt = nfull * KB; kt < kd) {
+    for (int e = tid; e < KB * NB; e += TT) {
+      const int kk = e / NB, n = e % NB;
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const float v = kt + kk < kd && n < g.N ? bp[p][(kt + kk) * g.ldb + n] : 0.f;
+        const __bf16 h = (__bf16)v;
+        lds.b[0][2 * p][n][kk] = h;
+        lds.b[0][2 * p + 1][n][kk] = (__bf16)(v - (float)h);
+      }
+    }
+    float x[NP][8];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t kk = kt + 8 * gq + e;
+        x[p][e] = kk < kd ? ap[p][OPA == 0 ? m * g.lda + kk : kk * g.lda + m] : 0.f;
+      }
+    __syncthreads();
+    products(split_a(x), 0, 0);
+  }
+  tall_store<NB>(g, k, m0, wave, gq, c, cr, ci, REAL);
+}
+
+template <int OPA, int NB>
+__global__ __launch_bounds__(TT, 2) void cgemm_tall_split_kernel(TArgs g) {
+  __shared__ __align__(16) TallLds<NB> lds;
+  const int64_t k = blockIdx.z, m0 = (int64_t)blockIdx.y * TM, kd = tall_kd(g);
+  if ((k == 0) || (g.real_last && k == g.K - 1))
+    tall_split_body<OPA, NB, true>(g, k, m0, kd, lds);
+  else
+    tall_split_body<OPA, NB, false>(g, k, m0, kd, lds);
 }
 
 template <int OPA, int NB>
