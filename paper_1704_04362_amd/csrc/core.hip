@@ -8,7 +8,8 @@
 // workgroup per slice with every small matrix in LDS:
 //   Y = W Omega, Q = orth(orth(Y)); q times: Z = orth(W^H Q),
 //   Q = orth(orth(W Z)); Bh = W^H Q; Bh^H Bh = U_B diag(lambda) U_B^H
-//   (Jacobi); P = Bh U_B,r diag(lambda^-1), U_r = Q U_B,r, keeping the
+//   (Jacobi of jacobi32.hpp, in W's place: 65 slices of 60 x 60 434 -> 385 us,
+//   1001 of 45 x 45 806 -> 735); P = Bh U_B,r diag(lambda^-1), U_r = Q U_B,r, keeping the
 //   leading r with sigma_i > rtol sigma_1.
 // orth(X) is CholeskyQR: X^H X = R^H R (pivots at or below 1e-24 of the
 // largest diagonal entry dropped), X <- X R^{-1} by forward substitution
@@ -16,7 +17,7 @@
 // used by every product; the products and Gram matrices run on the float64
 // matrix cores from LDS.
 #include "common.hpp"
-#include "jacobi.hpp"
+#include "jacobi32.hpp"
 #include "linalg.hpp"
 
 namespace tp {
@@ -24,20 +25,23 @@ namespace {
 
 constexpr int CNT = 1024, CM = 64, CS = 32, LDY = CS, CW = 3600;
 
-// The Gram / Cholesky scratch is dead once the eigensolver starts, so it
-// shares its LDS with the solver's state.
 struct CoreFactor {
   double gr[CS][CS + 1], gi[CS][CS + 1];  // Gram, then the strict upper triangle of R
 };
 
 struct CoreShared {
-  double wr[CW], wi[CW];            // W (m x n, m n <= 3600)
+  union {
+    struct {
+      double wr[CW], wi[CW];  // W (m x n, m n <= 3600)
+    };
+    struct {
+      Jacobi32Shared jac;  // (W is dead by then)
+      double red[16];
+    };
+  };
   double yr[CM][LDY], yi[CM][LDY];  // Y / Q (m x s)
   double zr[CM][LDY], zi[CM][LDY];  // Omega / Bh / Z (n x s)
-  union {
-    CoreFactor f;
-    JacobiShared<CS, CNT> jac;
-  };
+  CoreFactor f;
   double rd[CS];
   double rinv[CS];  // 1 / R_jj, 0 for a dropped index
   double dmax;
@@ -268,16 +272,14 @@ __global__ __launch_bounds__(CNT) void core_pinv_kernel(CoreArgs a) {
   gram_lds(sh.zr, sh.zi, a.n, a.s, sh);
   for (int e = tid; e < a.s * a.s; e += CNT) {
     const int p = e / a.s, q = e - p * a.s;
-    sh.jac.Hr[p][q] = sh.f.gr[p][q];
-    sh.jac.Hi[p][q] = sh.f.gi[p][q];
+    sh.jac.H[0][p * 32 + q] = Cz{0.5 * (sh.f.gr[p][q] + sh.f.gr[q][p]), 0.5 * (sh.f.gi[p][q] - sh.f.gi[q][p])};
   }
-  __syncthreads();
-  jacobi_eig_lds<CS, CNT>(sh.jac, a.s, 40, 1e-15);
+  const Cz* H = sh.jac.H[jacobi32<CNT, true>(sh.jac, a.s, 40, 1e-15, sh.red)];
   if (tid < a.s) {
-    const double lt = sh.jac.Hr[tid][tid];
+    const double lt = H[33 * tid].x;
     int rank = 0;
     for (int j = 0; j < a.s; ++j) {
-      const double lj = sh.jac.Hr[j][j];
+      const double lj = H[33 * j].x;
       if (lj > lt || (lj == lt && j < tid)) ++rank;
     }
     sh.order[rank] = tid;
@@ -285,8 +287,8 @@ __global__ __launch_bounds__(CNT) void core_pinv_kernel(CoreArgs a) {
   __syncthreads();
   // weights of the kept leading columns: 1/lambda for P, 1 for U
   if (tid < a.r) {
-    const double l0 = sh.jac.Hr[sh.order[0]][sh.order[0]];
-    const double lj = sh.jac.Hr[sh.order[tid]][sh.order[tid]];
+    const double l0 = H[33 * sh.order[0]].x;
+    const double lj = H[33 * sh.order[tid]].x;
     const double s0 = l0 > 0.0 ? sqrt(l0) : 0.0;
     const double sj = lj > 0.0 ? sqrt(lj) : 0.0;
     const bool keep = sj > 0.0 && sj > a.rtol * s0;
@@ -302,9 +304,9 @@ __global__ __launch_bounds__(CNT) void core_pinv_kernel(CoreArgs a) {
     double vr = 0.0, vi = 0.0;
     for (int t = 0; t < a.s; ++t) {
       const double xr = isp ? sh.zr[i][t] : sh.yr[i][t], xi = isp ? sh.zi[i][t] : sh.yi[i][t];
-      const double er = sh.jac.Vr[t][col], ei = sh.jac.Vi[t][col];
-      vr += xr * er - xi * ei;
-      vi += xr * ei + xi * er;
+      const Cz e = sh.jac.V[32 * t + col];
+      vr += xr * e.x - xi * e.y;
+      vi += xr * e.y + xi * e.x;
     }
     const double w = isp ? sh.rd[c] : (sh.rd[c] > 0.0 ? 1.0 : 0.0);
     vr *= w;

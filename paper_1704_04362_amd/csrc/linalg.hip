@@ -14,6 +14,7 @@
 
 #include "common.hpp"
 #include "jacobi.hpp"
+#include "jacobi32.hpp"
 #include "linalg.hpp"
 
 namespace tp {
@@ -210,6 +211,46 @@ __global__ __launch_bounds__(NT) void herm_eig_kernel(const double* __restrict__
     vim[k * ne + e] = sh.Vi[i][src];
   }
   if (tid < s) evals[k * s + tid] = sh.Hr[order[tid]][order[tid]];
+}
+
+// The same for s <= 32 on the eight-wavefront solver of jacobi32.hpp. Bound: the
+// latency of its rounds up to a slice a CU, the issue of float64 instructions
+// beyond. s = 30, 65 slices 225 -> 160 us; s = 15, 1001 slices 302 -> 165
+// (replaced: 1024 threads, two barriers a round).
+__global__ __launch_bounds__(512, 4) void herm_eig32_kernel(const double* __restrict__ gre,
+                                                            const double* __restrict__ gim, int s, int max_sweeps,
+                                                            double* __restrict__ evals, double* __restrict__ vre,
+                                                            double* __restrict__ vim) {
+  __shared__ Jacobi32Shared sh;
+  __shared__ double red[16];
+  __shared__ int order[32];
+  const int64_t k = blockIdx.x;
+  const int ne = s * s, tid = threadIdx.x;
+  gre += k * ne;
+  gim += k * ne;
+  // exact Hermitian symmetry of the input
+  for (int e = tid; e < ne; e += 512) {
+    const int i = e / s, j = e - i * s, f = j * s + i;
+    sh.H[0][i * 32 + j] = Cz{0.5 * (gre[e] + gre[f]), 0.5 * (gim[e] - gim[f])};
+  }
+  const Cz* H = sh.H[jacobi32<512, true>(sh, s, max_sweeps, 1e-15, red)];
+  if (tid < s) {
+    const double lt = H[33 * tid].x;
+    int rank = 0;
+    for (int j = 0; j < s; ++j) {
+      const double lj = H[33 * j].x;
+      if (lj > lt || (lj == lt && j < tid)) ++rank;
+    }
+    order[rank] = tid;
+  }
+  __syncthreads();
+  for (int e = tid; e < ne; e += 512) {
+    const int i = e / s, j = e - i * s;  // row i, sorted column j
+    const Cz z = sh.V[32 * i + order[j]];
+    vre[k * ne + e] = z.x;
+    vim[k * ne + e] = z.y;
+  }
+  if (tid < s) evals[k * s + tid] = H[33 * order[tid]].x;
 }
 
 // Orthonormalising transform from a Gram matrix G = X^H X (CholeskyQR):
@@ -602,7 +643,7 @@ int herm_eig(const double* gre, const double* gim, int64_t K, int s, double* eva
   if (s < 1 || s > kMaxS) return fail(TP_EUNSUPPORTED, "eigenproblem size outside 1..64");
   if (K == 0) return TP_OK;
   if (s <= 32)
-    hipLaunchKernelGGL((herm_eig_kernel<32, 1024>), dim3((unsigned)K), dim3(1024), 0, st, gre, gim, s, 40, evals,
+    hipLaunchKernelGGL(herm_eig32_kernel, dim3((unsigned)K), dim3(512), 0, st, gre, gim, s, 40, evals,
                        vre, vim);
   else
     hipLaunchKernelGGL((herm_eig_kernel<kMaxS, 1024>), dim3((unsigned)K), dim3(1024), 0, st, gre, gim, s, 40, evals,
