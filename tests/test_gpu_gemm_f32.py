@@ -1,0 +1,37 @@
+"""GPU parity of the float32 per-slice products on the float32 matrix cores at
+the edges of their two tile sizes (64 and 128 rows and columns, 16-deep steps of
+the contraction), every pair of operations, real and complex last slices.
+
+Tolerance: every one of Kd additions rounds by at most 2^-24 of its partial
+sum, at random; the three-product form doubles the error: 2^-24 sqrt(Kd) x 4 of
+the result's norm.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+api = pytest.importorskip("paper_1704_04362_amd.api")
+
+SHAPES = [(1, 65, 65, 64), (3, 64, 128, 79), (2, 127, 129, 65), (5, 192, 193, 80), (9, 257, 66, 96),
+          (40, 130, 129, 64), (33, 256, 256, 65), (2, 700, 640, 100)]
+
+
+@pytest.mark.parametrize("K,M,N,Kd", SHAPES)
+@pytest.mark.parametrize("op_a,op_b", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("real_last", [False, True])
+def test_f32_products_at_tile_edges(K, M, N, Kd, op_a, op_b, real_last):
+    g = np.random.default_rng([K, M, N, Kd])
+    A = g.standard_normal((2, K, Kd, M) if op_a else (2, K, M, Kd)).astype(np.float32)
+    B = g.standard_normal((2, K, N, Kd) if op_b else (2, K, Kd, N)).astype(np.float32)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    re, im = api.spectrum_matmul((dev(A[0]), dev(A[1])), (dev(B[0]), dev(B[1])), op_a, op_b, real_last=real_last,
+                                 prec="f32")
+    for k in range(K):
+        real = k == 0 or (real_last and k == K - 1)
+        a = A[0, k].astype(np.float64) + (0 if real else 1j * A[1, k])
+        b = B[0, k].astype(np.float64) + (0 if real else 1j * B[1, k])
+        ref = (a.conj().T if op_a else a) @ (b.conj().T if op_b else b)
+        got = re[k].cpu().numpy() + 1j * im[k].cpu().numpy()
+        assert np.linalg.norm(got - ref) <= 2.0 ** -24 * np.sqrt(Kd) * 4 * np.linalg.norm(ref)
