@@ -185,17 +185,22 @@ inline int contraction_parts(int64_t K, bool real_last, int64_t tiles, int64_t s
   return (int)parts;
 }
 // Number of contraction parts the matrix-core products would use for an
-// M x N x Kd product over K slices (1 = no split): bf16 (gemm_mfma.hip) and
-// float32 (gemm_f32.hip); and the scratch floats per plane for them.
+// M x N x Kd product over K slices (1 = no split): bf16 (gemm_mfma.hip),
+// float32 (gemm_f32.hip) and narrow results (gemm_tall.hip); and the scratch
+// floats per plane for them.
 int cgemm_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd);
 int cgemm_f32_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd);
+int cgemm_tall_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd);
+// C[k] = sum over the parts' planes [p][k][M][N], in part order
+int reduce_parts(const float* pre, const float* pim, int ksplit, int64_t K, int64_t M, int64_t N, float* cre, float* cim,
+                 int64_t ldc, int64_t sc, hipStream_t st);
 inline int64_t cgemm_split_floats(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd) {
   const int s = cgemm_ksplit(K, real_last, M, N, Kd);
   return s > 1 ? int64_t(s) * K * M * N : 0;
 }
 inline int64_t cgemm_ksplit_floats(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd) {
-  const int s = cgemm_ksplit(K, real_last, M, N, Kd), s2 = cgemm_f32_ksplit(K, real_last, M, N, Kd);
-  const int m = s > s2 ? s : s2;
+  const int m = std::max(cgemm_tall_ksplit(K, real_last, M, N, Kd),
+                         std::max(cgemm_ksplit(K, real_last, M, N, Kd), cgemm_f32_ksplit(K, real_last, M, N, Kd)));
   return m > 1 ? int64_t(m) * K * M * N : 0;
 }
 

@@ -265,22 +265,6 @@ __global__ __launch_bounds__(FT, W == 4 ? 1 : 3) void cgemm_f32_kernel(FArgs g) 
 }
 
 // C[k] = sum over the parts, in part order
-__global__ void f32_ksplit_reduce_kernel(const float* __restrict__ pre, const float* __restrict__ pim, int ksplit,
-                                         int64_t K, int64_t M, int64_t N, float* __restrict__ cre,
-                                         float* __restrict__ cim, int64_t ldc, int64_t sc) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t per = M * N;
-  if (e >= K * per) return;
-  const int64_t k = e / per, r = e - k * per, m = r / N, n = r - m * N;
-  float sr = 0.f, si = 0.f;
-  for (int p = 0; p < ksplit; ++p) {
-    sr += pre[(int64_t)p * K * per + e];
-    si += pim[(int64_t)p * K * per + e];
-  }
-  cre[k * sc + m * ldc + n] = sr;
-  cim[k * sc + m * ldc + n] = si;
-}
-
 }  // namespace
 
 // Parts of a split contraction for the float32 matrix-core product, at least
@@ -337,12 +321,9 @@ int cgemm_f32mfma(const CGemm& p, hipStream_t st, bool* handled) {
   else
     launch(std::integral_constant<int, 2>{});
   TP_LAUNCH_CHECK();
-  if (ksplit > 1) {
-    const int64_t n = p.K * p.M * p.N;
-    hipLaunchKernelGGL(f32_ksplit_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p.part_re,
-                       p.part_im, ksplit, p.K, p.M, p.N, (float*)p.cre, (float*)p.cim, p.ldc, p.sc);
-    TP_LAUNCH_CHECK();
-  }
+  if (ksplit > 1)
+    if (int rc = reduce_parts(p.part_re, p.part_im, ksplit, p.K, p.M, p.N, (float*)p.cre, (float*)p.cim, p.ldc, p.sc, st))
+      return rc;
   *handled = true;
   return TP_OK;
 }

@@ -538,6 +538,8 @@ __global__ __launch_bounds__(SNT, 1) void cgemm_split_kernel(SArgs g, int64_t gm
     split_body<TERMS, true>(g, zi == ncomplex ? 0 : g.K - 1, tm, tn, (int)blockIdx.y, lds);
 }
 
+}  // namespace
+
 int reduce_parts(const float* pre, const float* pim, int ksplit, int64_t K, int64_t M, int64_t N, float* cre, float* cim,
                  int64_t ldc, int64_t sc, hipStream_t st) {
   const int64_t n = K * M * N;
@@ -546,8 +548,6 @@ int reduce_parts(const float* pre, const float* pim, int ksplit, int64_t K, int6
   TP_LAUNCH_CHECK();
   return TP_OK;
 }
-
-}  // namespace
 
 // Takes the product when it is an as-stored (NN) product of float32 spectra
 // with 16-byte aligned rows; reports handled = false otherwise.

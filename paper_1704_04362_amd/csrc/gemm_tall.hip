@@ -32,6 +32,10 @@ struct TArgs {
   int64_t K;
   int real_last;
   const int64_t* kdim_dev;
+  // split contraction: part p of ksplit takes an equal share of the live
+  // contraction, in whole steps, and writes its planes to pre / pim [p][k][M][N]
+  int ksplit;
+  float *pre, *pim;
 };
 
 __device__ __forceinline__ bf16x8 bneg(bf16x8 x) {
@@ -83,11 +87,19 @@ struct StepLoad {
   }
 };
 
-__device__ __forceinline__ int64_t tall_kd(const TArgs& g) {
+// The contraction range of this workgroup's part: its first k and length
+__device__ __forceinline__ int64_t tall_kd(const TArgs& g, int64_t& kbeg) {
   int64_t kd = g.Kd;
   if (g.kdim_dev) {
     const int64_t lim = *g.kdim_dev;
     kd = lim < kd ? (lim < 0 ? 0 : lim) : kd;
+  }
+  kbeg = 0;
+  if (g.ksplit > 1) {
+    const int64_t chunk = ((kd + g.ksplit - 1) / g.ksplit + KB - 1) / KB * KB;
+    kbeg = (int64_t)blockIdx.x * chunk;
+    kd = kbeg < kd ? (kd - kbeg < chunk ? kd - kbeg : chunk) : 0;
+    if (kd == 0) kbeg = 0;
   }
   return kd;
 }
@@ -96,8 +108,10 @@ __device__ __forceinline__ int64_t tall_kd(const TArgs& g) {
 template <int NB>
 __device__ __forceinline__ void tall_store(const TArgs& g, int64_t k, int64_t m0, int wave, int gq, int c,
                                            const f32x4 (&cr)[NB / 16], const f32x4 (&ci)[NB / 16], bool real) {
-  float* cre = g.cre + k * g.sc;
-  float* cim = g.cim + k * g.sc;
+  const bool parted = g.ksplit > 1;
+  const int64_t plane = ((int64_t)blockIdx.x * g.K + k) * g.M * g.N, ldc = parted ? g.N : g.ldc;
+  float* cre = parted ? g.pre + plane : g.cre + k * g.sc;
+  float* cim = parted ? g.pim + plane : g.cim + k * g.sc;
 #pragma unroll
   for (int nt = 0; nt < NB / 16; ++nt) {
     const int64_t n = 16 * nt + c;
@@ -106,8 +120,8 @@ __device__ __forceinline__ void tall_store(const TArgs& g, int64_t k, int64_t m0
     for (int v = 0; v < 4; ++v) {
       const int64_t m = m0 + 16 * wave + 4 * gq + v;
       if (m < g.M) {
-        cre[m * g.ldc + n] = cr[nt][v];
-        cim[m * g.ldc + n] = real ? 0.f : ci[nt][v];
+        cre[m * ldc + n] = cr[nt][v];
+        cim[m * ldc + n] = real ? 0.f : ci[nt][v];
       }
     }
   }
@@ -124,11 +138,9 @@ __global__ __launch_bounds__(TT) void cgemm_tall_kernel(TArgs g) {
   const int gq = lane >> 4, c = lane & 15;
   const int64_t k = blockIdx.z, m0 = (int64_t)blockIdx.y * TM;
   const bool real = (k == 0) || (g.real_last && k == g.K - 1);
-  const int64_t kd = tall_kd(g);
-  const float* are = g.are + k * g.sa;
-  const float* aim = g.aim + k * g.sa;
-  const float* bre = g.bre + k * g.sb;
-  const float* bim = g.bim + k * g.sb;
+  int64_t kbeg;
+  const int64_t kd = tall_kd(g, kbeg), oa = k * g.sa + (OPA == 0 ? kbeg : kbeg * g.lda), ob = k * g.sb + kbeg * g.ldb;
+  const float *are = g.are + oa, *aim = g.aim + oa, *bre = g.bre + ob, *bim = g.bim + ob;
   using L = StepLoad<OPA, NB>;
   L ld;
   auto put = [&](int b) {
@@ -205,7 +217,8 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& 
 }
 
 template <int OPA, int NB, bool REAL>
-__device__ __forceinline__ void tall_split_body(const TArgs& g, int64_t k, int64_t m0, int64_t kd, TallLds<NB>& lds) {
+__device__ __forceinline__ void tall_split_body(const TArgs& g, int64_t k, int64_t m0, int64_t kbeg, int64_t kd,
+                                                TallLds<NB>& lds) {
   using L = TallLds<NB>;
   constexpr int NTL = NB / 16, NP = REAL ? 1 : 2, KC = L::KC, RB = KC * NB / 4 / TT;
   typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -213,8 +226,9 @@ __device__ __forceinline__ void tall_split_body(const TArgs& g, int64_t k, int64
   const int gq = lane >> 4, c = lane & 15;
   // rows beyond M and columns beyond N read the last one; they are never stored
   const int64_t m = m0 + 16 * wave + c < g.M ? m0 + 16 * wave + c : g.M - 1;
-  const float* ap[2] = {g.are + k * g.sa, g.aim + k * g.sa};
-  const float* bp[2] = {g.bre + k * g.sb, g.bim + k * g.sb};
+  const int64_t oa = k * g.sa + (OPA == 0 ? kbeg : kbeg * g.lda), ob = k * g.sb + kbeg * g.ldb;
+  const float* ap[2] = {g.are + oa, g.aim + oa};
+  const float* bp[2] = {g.bre + ob, g.bim + ob};
   const int64_t a0 = OPA == 0 ? m * g.lda + 8 * gq : 8 * gq * g.lda + m, astep = OPA == 0 ? KB : KB * g.lda;
   const int64_t nfull = kd / KB, last = nfull - 1, nch = (nfull + 1) / 2;
 
@@ -361,11 +375,12 @@ __device__ __forceinline__ void tall_split_body(const TArgs& g, int64_t k, int64
 template <int OPA, int NB>
 __global__ __launch_bounds__(TT, 2) void cgemm_tall_split_kernel(TArgs g) {
   __shared__ __align__(16) TallLds<NB> lds;
-  const int64_t k = blockIdx.z, m0 = (int64_t)blockIdx.y * TM, kd = tall_kd(g);
+  int64_t kbeg;
+  const int64_t k = blockIdx.z, m0 = (int64_t)blockIdx.y * TM, kd = tall_kd(g, kbeg);
   if ((k == 0) || (g.real_last && k == g.K - 1))
-    tall_split_body<OPA, NB, true>(g, k, m0, kd, lds);
+    tall_split_body<OPA, NB, true>(g, k, m0, kbeg, kd, lds);
   else
-    tall_split_body<OPA, NB, false>(g, k, m0, kd, lds);
+    tall_split_body<OPA, NB, false>(g, k, m0, kbeg, kd, lds);
 }
 
 template <int OPA, int NB>
@@ -378,6 +393,14 @@ void launch_tall(const TArgs& g, int split, dim3 grid, hipStream_t st) {
 
 }  // namespace
 
+// Parts of a split contraction, at least four steps each; whole rt-product in
+// us, one part / parts: 1000 x 20 x 12 over 256 picks 71 / 31 in float32, 69 / 29
+// in bf16x3, over 6000 2147 / 306 and 2117 / 250; 40 x 40 x 5 over 1700 190 / 34
+// and 153 / 28.
+int cgemm_tall_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd) {
+  return N > 64 ? 1 : contraction_parts(K, real_last, (M + TM - 1) / TM, Kd / KB, 4);
+}
+
 // Takes float32 products C_k = op(A_k) B_k (op_b = N) with at most 64
 // result columns (any contraction length), in float32 (split = 0)
 // or split bf16 (split = 1); *handled says whether it did.
@@ -387,8 +410,10 @@ int cgemm_tall(const CGemm& p, int split, hipStream_t st, bool* handled) {
   if (p.K > 65535 || (p.M + TM - 1) / TM > 65535) return TP_OK;
   TArgs g{p.M, p.N, p.Kd, (const float*)p.are, (const float*)p.aim, (const float*)p.bre, (const float*)p.bim,
           (float*)p.cre, (float*)p.cim, p.lda, p.ldb, p.ldc, p.sa, p.sb, p.sc, p.K, p.real_last ? 1 : 0,
-          p.kdim_dev};
-  const dim3 grid(1u, (unsigned)((p.M + TM - 1) / TM), (unsigned)p.K);
+          p.kdim_dev, 1, p.part_re, p.part_im};
+  const int parts = cgemm_tall_ksplit(p.K, p.real_last, p.M, p.N, p.Kd);
+  if (p.part_re && p.part_im && p.part_cap >= int64_t(parts) * p.K * p.M * p.N) g.ksplit = parts;
+  const dim3 grid((unsigned)g.ksplit, (unsigned)((p.M + TM - 1) / TM), (unsigned)p.K);
   if (p.op_a == 0) {
     if (p.N <= 32)
       launch_tall<0, 32>(g, split, grid, st);
@@ -401,6 +426,10 @@ int cgemm_tall(const CGemm& p, int split, hipStream_t st, bool* handled) {
       launch_tall<1, 64>(g, split, grid, st);
   }
   TP_LAUNCH_CHECK();
+  if (g.ksplit > 1)
+    if (int rc = reduce_parts(p.part_re, p.part_im, g.ksplit, p.K, p.M, p.N, (float*)p.cre, (float*)p.cim, p.ldc, p.sc,
+                              st))
+      return rc;
   *handled = true;
   return TP_OK;
 }

@@ -1,7 +1,7 @@
 """GPU parity of products with few output tiles, whose contraction is cut into
 parts: lengths around the shortest that is cut (256), parts of unequal length,
 picks whose count (read on the device) leaves parts empty; tube lengths with
-pre-split operands (8) and without (5).
+pre-split operands (8) and without (5); narrow results (at most 64 columns).
 
 Tolerances: float32 1e-5, the bound stated for the t-product; bf16x3 1.3e-5
 and bf16 1e-2 (2^-16 and 2^-8 dropped per product).
@@ -27,7 +27,8 @@ def dev(x):
 
 @pytest.mark.parametrize("prec", sorted(TOL))
 @pytest.mark.parametrize("n3", [5, 8])
-@pytest.mark.parametrize("n1,n2,n4", [(65, 255, 66), (65, 256, 66), (129, 545, 127), (70, 2049, 300)])
+@pytest.mark.parametrize("n1,n2,n4", [(65, 255, 66), (65, 256, 66), (129, 545, 127), (70, 2049, 300),
+                                      (70, 300, 33), (129, 1030, 64), (33, 257, 1)])
 def test_products_in_parts(n1, n2, n4, n3, prec):
     A = W.gaussian((n1, n2, n3), seed=n2).astype(np.float32)
     B = W.gaussian((n2, n4, n3), seed=n2 + 1).astype(np.float32)
