@@ -373,8 +373,7 @@ int tp_tprod(const tp_tensor* A, const tp_tensor* B, const tp_sample* sample, tp
   if (!ar.ok()) return fail(TP_EWORKSPACE, "t-product workspace too small");
   if (inner > 0) {
     TraceScope ts(sample ? "rtprod.fft_ab" : "tprod.fft_ab", st);
-    if (int rc = fft_forward(A->data, A->dtype, n3, ga, Ah.re, Ah.im, st)) return rc;
-    if (int rc = fft_forward(B->data, B->dtype, n3, gb, Bh.re, Bh.im, st)) return rc;
+    if (int rc = fft_forward_pair(A->data, ga, Ah.re, Ah.im, B->data, gb, Bh.re, Bh.im, A->dtype, n3, st)) return rc;
   }
   CGemm p;
   p.K = K;

@@ -94,6 +94,9 @@ struct TubeGather {
 // sums, whose last bits the sweep-capped ADMM needs unchanged (api_svt.cpp).
 int fft_forward(const void* x, int dtype, int64_t n3, const TubeGather& g, void* re, void* im, hipStream_t st,
                 bool sums = false);
+// Two operands of the same tube length, in one launch where that saves one.
+int fft_forward_pair(const void* x, const TubeGather& g, void* re, void* im, const void* y, const TubeGather& h,
+                     void* yre, void* yim, int dtype, int64_t n3, hipStream_t st);
 int fft_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t rows, int64_t cols, void* x,
                 hipStream_t st, bool sums = false);
 bool fft_supported(int64_t n3);

@@ -84,3 +84,21 @@ def test_four_step_tiles(n3, shape, dtype):
     assert not im[0].any() and not im[-1].any()
     Y = api.tifft(re, im, n3).cpu().numpy().astype(np.float64)
     assert np.linalg.norm(Y - X) < 2 * tol * np.linalg.norm(X)
+
+
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-12), ("f32", 1e-5)])
+@pytest.mark.parametrize("n3", [1, 2, 3, 5, 16, 23, 64, 168, 24])
+def test_products_with_both_operands_in_one_launch(n3, prec, tol):
+    """Both operands of a product transformed by one launch (lengths with a
+    tube a thread): operands of one tube, of less and more than a workgroup, a
+    sampled one. Tolerances: those of the t-product."""
+    dtype = np.float64 if prec == "f64" else np.float32
+    for n1, n2, n4 in ((1, 1, 1), (1, 70, 3), (9, 13, 31)):
+        A = W.gaussian((n1, n2, n3), seed=n3).astype(dtype)
+        B = W.gaussian((n2, n4, n3), seed=n3 + 1).astype(dtype)
+        C = api.tprod(dev(A), dev(B), prec=prec).cpu().numpy()
+        assert T.rel_fro(C, T.tprod_fft(A.astype(np.float64), B.astype(np.float64))) < tol
+    picks = api.tsample("uniform", 7, mode="iid", seed=1, n=13)
+    Z = api.tprod(dev(A), dev(B), picks=picks, prec=prec).cpu().numpy()
+    idx, sc = picks.host()
+    assert T.rel_fro(Z, D.rtprod(A, B, idx.numpy(), sc.numpy())) < tol
