@@ -804,12 +804,13 @@ int svt_jacobi(float* xre, float* xim, float* ure, float* uim, int64_t K, int64_
     return TP_OK;
   };
   // The slices are independent: when one launch would leave compute units
-  // with a free pair-step slot (two fit per compute unit by LDS) but has more
-  // workgroups than compute units, the second half of the slices runs on
+  // with a free pair-step slot (two fit per compute unit by registers) but has
+  // more workgroups than compute units, the second half of the slices runs on
   // the side stream, so that one half's pair steps fill the units that the
-  // other half's launch leaves idle. Measured on 51 slices of 256 x 256 (408
-  // pair steps per launch on 256 units): 7% faster than one stream; on 85
-  // slices of 192 x 1140 (510 pair steps, every slot taken): 7% slower.
+  // other half's launch leaves idle. Six completion iterations on one / two
+  // streams: 26 slices of 256 x 256 (208 pair steps per launch on 256 units)
+  // 19.6 / 24.0 ms, 33 (264) 32.0 / 27.2, 51 (408) 35.6 / 32.3; 85 of 192 x 1140
+  // (510, every slot taken) 60.1 / 62.2.
   int dev = 0, cus = 0;
   TP_HIP_CHECK(hipGetDevice(&dev));
   TP_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
