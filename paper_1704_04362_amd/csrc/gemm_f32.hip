@@ -86,13 +86,13 @@ __device__ __forceinline__ void stage_coords(const bool along_k, int p, int& row
   }
 }
 
-template <bool REAL, int W>
+template <bool REAL, int W, typename Off>
 __device__ __forceinline__ void load_stage(Stage<W>& s, const float* xr, const float* xi, int64_t ld, bool along_k,
                                            int64_t r0, int64_t rows, int64_t k0, int64_t kend) {
   s.keep = 0;
-  // a uniform origin and 32-bit offsets in the tile (ld < 2^23, checked on the
-  // host), of which only the test for the end of the contraction is not the
-  // same in every step
+  // a uniform origin and the values' offsets in the tile (Off: 32 bits below
+  // ld = 2^23), of which only the test for the end of the contraction is not
+  // the same in every step
   const int rlim = (int)(rows - r0 < 32 * W ? rows - r0 : 32 * W), klim = (int)(kend - k0 < FK ? kend - k0 : FK);
   const int64_t o = along_k ? r0 * ld + k0 : k0 * ld + r0;
   xr += o;
@@ -101,9 +101,9 @@ __device__ __forceinline__ void load_stage(Stage<W>& s, const float* xr, const f
   for (int p = 0; p < 2 * W; ++p) {
     int row, kk;
     stage_coords<W>(along_k, p, row, kk);
-    const uint32_t r = row < rlim ? row : 0, l = (uint32_t)ld;
-    const uint32_t tr = along_k ? r * l : r, tk = along_k ? (uint32_t)kk : kk * l;
-    const uint32_t t = tr + (kk < klim ? tk : 0u);
+    const Off r = row < rlim ? row : 0, l = (Off)ld;
+    const Off tr = along_k ? r * l : r, tk = along_k ? (Off)kk : kk * l;
+    const Off t = tr + (kk < klim ? tk : 0u);
     s.re[p] = xr[t];
     if (!REAL) s.im[p] = xi[t];
     s.keep |= row < rlim && kk < klim ? (1u << p) : 0u;
@@ -129,7 +129,7 @@ __device__ __forceinline__ void store_stage(const Stage<W>& s, bool along_k, boo
   }
 }
 
-template <bool REAL, int W, int OPA, int OPB>
+template <bool REAL, int W, int OPA, int OPB, typename Off>
 __device__ __forceinline__ void f32_body(const FArgs& g, int64_t k, int part, float* lds) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;
@@ -166,8 +166,8 @@ __device__ __forceinline__ void f32_body(const FArgs& g, int64_t k, int part, fl
   Stage<W> sa, sb;
   const int64_t nsteps = kend > kbeg ? (kend - kbeg + FK - 1) / FK : 0;
   if (nsteps > 0) {
-    load_stage<REAL, W>(sa, are, aim, g.lda, a_along_k, m0, g.M, kbeg, kend);
-    load_stage<REAL, W>(sb, bre, bim, g.ldb, b_along_k, n0, g.N, kbeg, kend);
+    load_stage<REAL, W, Off>(sa, are, aim, g.lda, a_along_k, m0, g.M, kbeg, kend);
+    load_stage<REAL, W, Off>(sb, bre, bim, g.ldb, b_along_k, n0, g.N, kbeg, kend);
   }
   const int fr = lane & 15, fq = lane >> 4;
   for (int64_t st = 0; st < nsteps; ++st) {
@@ -177,8 +177,8 @@ __device__ __forceinline__ void f32_body(const FArgs& g, int64_t k, int part, fl
     __syncthreads();
     if (st + 1 < nsteps) {
       const int64_t k0 = kbeg + (st + 1) * FK;
-      load_stage<REAL, W>(sa, are, aim, g.lda, a_along_k, m0, g.M, k0, kend);
-      load_stage<REAL, W>(sb, bre, bim, g.ldb, b_along_k, n0, g.N, k0, kend);
+      load_stage<REAL, W, Off>(sa, are, aim, g.lda, a_along_k, m0, g.M, k0, kend);
+      load_stage<REAL, W, Off>(sb, bre, bim, g.ldb, b_along_k, n0, g.N, k0, kend);
     }
     // fragments: lane (fq, fr) reads row fr of a 16-row tile, chunk fq:
     // the values for k = fq + 4 s, s = 0..3 (sub-step s of the 16-deep step)
@@ -252,16 +252,16 @@ __device__ __forceinline__ void f32_body(const FArgs& g, int64_t k, int part, fl
       }
 }
 
-template <int W, int OPA, int OPB>
+template <int W, int OPA, int OPB, typename Off>
 __global__ __launch_bounds__(FT, W == 4 ? 1 : 3) void cgemm_f32_kernel(FArgs g) {
   __shared__ __attribute__((aligned(16))) float lds[2 * 6 * 32 * W * FK];  // 96 or 48 KB
   const int part = (int)(blockIdx.z % (unsigned)g.ksplit);
   const int64_t k = blockIdx.z / (unsigned)g.ksplit;
   const bool real = k == 0 || (g.real_last && k == g.K - 1);
   if (real)
-    f32_body<true, W, OPA, OPB>(g, k, part, lds);
+    f32_body<true, W, OPA, OPB, Off>(g, k, part, lds);
   else
-    f32_body<false, W, OPA, OPB>(g, k, part, lds);
+    f32_body<false, W, OPA, OPB, Off>(g, k, part, lds);
 }
 
 // C[k] = sum over the parts, in part order
@@ -299,27 +299,30 @@ static bool f32_wide(const CGemm& p, int ksplit) {
 int cgemm_f32mfma(const CGemm& p, hipStream_t st, bool* handled) {
   *handled = false;
   if (p.M < 16 || p.N < 16 || p.Kd < 64) return TP_OK;
-  if (p.K > 65535 || p.lda >= (1 << 23) || p.ldb >= (1 << 23)) return TP_OK;
+  if (p.K > 65535) return TP_OK;
   int ksplit = cgemm_f32_ksplit(p.K, p.real_last, p.M, p.N, p.Kd);
   if (ksplit > 1 && (!p.part_re || !p.part_im || p.part_cap < int64_t(ksplit) * p.K * p.M * p.N)) ksplit = 1;
   if (p.K * ksplit > 65535) ksplit = 1;
   FArgs g{p.M, p.N, p.Kd, (const float*)p.are, (const float*)p.aim, (const float*)p.bre, (const float*)p.bim,
           (float*)p.cre, (float*)p.cim, p.lda, p.ldb, p.ldc, p.sa, p.sb, p.sc, p.op_a, p.op_b, p.K,
           p.real_last ? 1 : 0, p.kdim_dev, ksplit, p.part_re, p.part_im};
-  const bool wide = f32_wide(p, ksplit);
+  const bool near = p.lda < (1 << 23) && p.ldb < (1 << 23), wide = !near || f32_wide(p, ksplit);
   const int64_t side = wide ? 128 : 64, gx = (p.N + side - 1) / side, gy = (p.M + side - 1) / side;
   if (gx > 0x7fffffff || gy > 65535) return TP_OK;
   const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)(p.K * ksplit));
-  const auto launch = [&](auto w) {
+  const auto launch = [&](auto w, auto off) {
     constexpr int W = decltype(w)::value;
-    const auto kernel = p.op_a ? (p.op_b ? cgemm_f32_kernel<W, 1, 1> : cgemm_f32_kernel<W, 1, 0>)
-                               : (p.op_b ? cgemm_f32_kernel<W, 0, 1> : cgemm_f32_kernel<W, 0, 0>);
+    using Off = decltype(off);
+    const auto kernel = p.op_a ? (p.op_b ? cgemm_f32_kernel<W, 1, 1, Off> : cgemm_f32_kernel<W, 1, 0, Off>)
+                               : (p.op_b ? cgemm_f32_kernel<W, 0, 1, Off> : cgemm_f32_kernel<W, 0, 0, Off>);
     hipLaunchKernelGGL(kernel, grid, dim3(FT), 0, st, g);
   };
-  if (wide)
-    launch(std::integral_constant<int, 4>{});
+  if (!near)
+    launch(std::integral_constant<int, 4>{}, uint64_t{});
+  else if (wide)
+    launch(std::integral_constant<int, 4>{}, uint32_t{});
   else
-    launch(std::integral_constant<int, 2>{});
+    launch(std::integral_constant<int, 2>{}, uint32_t{});
   TP_LAUNCH_CHECK();
   if (ksplit > 1)
     if (int rc = reduce_parts(p.part_re, p.part_im, ksplit, p.K, p.M, p.N, (float*)p.cre, (float*)p.cim, p.ldc, p.sc, st))

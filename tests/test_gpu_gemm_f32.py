@@ -35,3 +35,26 @@ def test_f32_products_at_tile_edges(K, M, N, Kd, op_a, op_b, real_last):
         ref = (a.conj().T if op_a else a) @ (b.conj().T if op_b else b)
         got = re[k].cpu().numpy() + 1j * im[k].cpu().numpy()
         assert np.linalg.norm(got - ref) <= 2.0 ** -24 * np.sqrt(Kd) * 4 * np.linalg.norm(ref)
+
+
+def test_f32_products_of_rows_beyond_32_bit_tile_offsets():
+    """Rows of 2^23 + 3 values (offsets in a tile of 64 bits), both operands read
+    along the contraction; the reference in float64 on the same device, a block of the
+    contraction at a time. Tolerance as above, over 2^23 additions."""
+    Kd, M, N = 2 ** 23 + 3, 17, 66
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda n: torch.randn((2, n, Kd), device="cuda", generator=g)  # noqa: E731
+    a, b = (rnd(M), rnd(M)), (rnd(N), rnd(N))
+    re, im = api.spectrum_matmul(a, b, 0, 1, real_last=False, prec="f32")
+    ref = torch.zeros((2, 2, M, N), dtype=torch.float64, device="cuda")  # (re, im) per slice
+    for k0 in range(0, Kd, 2 ** 20):
+        ar, ai = (t[..., k0:k0 + 2 ** 20].double() for t in a)
+        br, bi = (t[..., k0:k0 + 2 ** 20].double() for t in b)
+        for k in range(2):  # A B^H; slice 0 is real
+            ref[k, 0] += ar[k] @ br[k].T.contiguous()
+            if k:
+                ref[k, 0] += ai[k] @ bi[k].T.contiguous()
+                ref[k, 1] += ai[k] @ br[k].T.contiguous() - ar[k] @ bi[k].T.contiguous()
+    err = torch.stack((re.double(), im.double()), 1) - ref
+    for k in range(2):
+        assert err[k].norm() <= 2.0 ** -24 * Kd ** 0.5 * 4 * ref[k].norm()
