@@ -515,6 +515,14 @@ __global__ __launch_bounds__(256) void softmax_grad_kernel(const float* __restri
   if (tid == 0) loss_part[t] = (float)(red[0] / (double)T);
 }
 
+// a b rounded once, to fp16 (left to itself the compiler fuses the conversion
+// into some of these products and rounds others twice)
+__device__ __forceinline__ _Float16 mul_f16(float a, float b) {
+  uint32_t r;
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b));
+  return __builtin_bit_cast(_Float16, (uint16_t)r);
+}
+
 // Backward of one tile from the forward pass's activations: this tile's
 // gradient contribution (parameter layout) to partial[tile].
 __global__ __launch_bounds__(NT, 2) void mlp_backward_kernel(const float* __restrict__ P,
@@ -559,7 +567,7 @@ __global__ __launch_bounds__(NT, 2) void mlp_backward_kernel(const float* __rest
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) dh[i][e] = (_Float16)((float)y[i][e] > 0.f ? d[i] * w[e] : 0.f);
+      for (int e = 0; e < 4; ++e) dh[i][e] = (float)y[i][e] > 0.f ? mul_f16(d[i], w[e]) : (_Float16)0.f;
       *reinterpret_cast<half4*>(&D[r + i][c]) = dh[i];
     }
 #pragma unroll
@@ -672,8 +680,10 @@ __global__ __launch_bounds__(GNT) void grad_adam_kernel(const float* __restrict_
   for (int64_t t = 0; t < ntiles; ++t) g += partial[t * NPARAM + p];
   if (grad) grad[p] = g;
   if (!adam) return;
-  const float m = b1 * M[p] + (1.f - b1) * g;
-  const float v = b2 * V[p] + (1.f - b2) * g * g;
+  // (the fused operations are written out: a parameter whose gradient is near
+  // zero moves by up to lr on the moments' last bits)
+  const float m = fmaf(1.f - b1, g, b1 * M[p]);
+  const float v = fmaf(g, (1.f - b2) * g, b2 * V[p]);
   M[p] = m;
   V[p] = v;
   P[p] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
