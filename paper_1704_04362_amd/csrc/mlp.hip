@@ -459,46 +459,46 @@ __global__ __launch_bounds__(NT, 2) void mlp_forward_kernel(const float* __restr
   }
 }
 
-// Per tensor: p = softmax(o), loss = KL(p* || p), dO = (p - p*) / T.
+// The tree over 256 threads' values that halves them seven times more (thread
+// t takes t + 128, t + 64, ..., t + 1), for every thread: the first two levels
+// from LDS and the others by shuffles in the first wavefront, two barriers in
+// place of nine.
+template <typename F>
+__device__ __forceinline__ double tree256(double v, double* red, F op) {
+  const int tid = threadIdx.x;
+  red[tid] = v;
+  __syncthreads();
+  if (tid < 64) {
+    v = op(op(red[tid], red[tid + 128]), op(red[tid + 64], red[tid + 192]));
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) v = op(v, __shfl_down(v, w));
+    if (tid == 0) red[256] = v;
+  }
+  __syncthreads();
+  return red[256];
+}
+
+// Per tensor: p = softmax(o), loss = KL(p* || p), dO = (p - p*) / T. Bound: the
+// latency of four reductions in a row (16 x 512: 6.7 -> 5.7 us with tree256).
 __global__ __launch_bounds__(256) void softmax_grad_kernel(const float* __restrict__ o,
                                                            const float* __restrict__ target, int64_t nsl, int64_t T,
                                                            float* __restrict__ dout, float* __restrict__ loss_part) {
-  __shared__ double red[256];
+  __shared__ double red[4][257];
   const int64_t t = blockIdx.x;
   const int tid = threadIdx.x;
   const float* ot = o + t * nsl;
   const float* pt = target + t * nsl;
+  const auto add = [](double a, double b) { return a + b; };
   double m = -INFINITY;
   for (int64_t j = tid; j < nsl; j += 256) m = fmax(m, (double)ot[j]);
-  red[tid] = m;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) red[tid] = fmax(red[tid], red[tid + w]);
-    __syncthreads();
-  }
-  const double mx = red[0];
-  __syncthreads();
+  const double mx = tree256(m, red[0], [](double a, double b) { return fmax(a, b); });
   double se = 0.0;
   for (int64_t j = tid; j < nsl; j += 256) se += exp((double)ot[j] - mx);
-  red[tid] = se;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
-  }
-  const double lse = mx + log(red[0]);
-  __syncthreads();
+  const double lse = mx + log(tree256(se, red[1], add));
   // the target row is normalised here (any positive scale is accepted)
   double qs = 0.0;
   for (int64_t j = tid; j < nsl; j += 256) qs += (double)pt[j];
-  red[tid] = qs;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
-  }
-  const double qinv = red[0] > 0.0 ? 1.0 / red[0] : 0.0;
-  __syncthreads();
+  const double qsum = tree256(qs, red[2], add), qinv = qsum > 0.0 ? 1.0 / qsum : 0.0;
   double kl = 0.0;
   for (int64_t j = tid; j < nsl; j += 256) {
     const double lp = (double)ot[j] - lse;
@@ -506,13 +506,8 @@ __global__ __launch_bounds__(256) void softmax_grad_kernel(const float* __restri
     if (q > 0) kl += q * (log(q) - lp);
     dout[t * nsl + j] = (float)((exp(lp) - q) / (double)T);
   }
-  red[tid] = kl;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
-  }
-  if (tid == 0) loss_part[t] = (float)(red[0] / (double)T);
+  kl = tree256(kl, red[3], add);
+  if (tid == 0) loss_part[t] = (float)(kl / (double)T);
 }
 
 // a b rounded once, to fp16 (left to itself the compiler fuses the conversion
