@@ -37,6 +37,12 @@ constexpr int PT = 512;      // threads of a pair step
 // one more outer sweep in total against a full inner solve, at a fraction of
 // the price per step.
 constexpr int kInnerSweeps = 1;
+// A pair whose off-diagonal mass is within this of its Gram matrix's (Frobenius
+// norms) is not rotated: below, its entries are rounding of the large rows'
+// products, and the loop of api_svt.cpp needs the pair steps' bits unchanged.
+// (The sums are taken only where no single entry decides: 32 entries of at most
+// the largest a side, so the norm is at most 32 times that one.)
+constexpr double kPairTol = 1e-14;
 
 struct PairArgs {
   int64_t K, n1, n2;
@@ -301,6 +307,34 @@ __device__ __forceinline__ void rotate_rows(const RotArgs& a, const Cz* V, const
   }
 }
 
+// Whether the off-diagonal mass of h is within kPairTol of the total
+__device__ __forceinline__ bool negligible(const Cz* h, double (*red)[PT / 64]) {
+  const int tid = threadIdx.x, w = tid >> 6;
+  double off = 0.0, tot = 0.0;
+  for (int e = tid; e < PR * PR; e += PT) {
+    const double m = fma(h[e].x, h[e].x, h[e].y * h[e].y);
+    tot += m;
+    off += e % (PR + 1) ? m : 0.0;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    off += __shfl_xor(off, o);
+    tot += __shfl_xor(tot, o);
+  }
+  __syncthreads();
+  if ((tid & 63) == 0) {
+    red[0][w] = off;
+    red[1][w] = tot;
+  }
+  __syncthreads();
+  off = tot = 0.0;
+  for (int q = 0; q < PT / 64; ++q) {
+    off += red[0][q];
+    tot += red[1][q];
+  }
+  return off <= kPairTol * kPairTol * tot;
+}
+
 // One pair step of one slice, eight wavefronts. On one CU for 256 columns
 // (cycles of a 2.2 GHz CU): Gram matrix 31,000, test and symmetrisation 3,000,
 // inner sweep 46,000 (31 rounds bound by float64 issue, see jacobi32.hpp),
@@ -319,7 +353,8 @@ __global__ __launch_bounds__(PT, 4) void svt_pair_kernel(PairArgs a, int round) 
     } raw;
   } sh;
   __shared__ int rows[PR];
-  __shared__ double ratio_red[PT / 64];
+  __shared__ double ratio_red[PT / 64], mass_red[2][PT / 64];
+  __shared__ int top;  // upper half of the largest diagonal entry
   const int64_t k = a.k0 + blockIdx.y;
   const int pair = blockIdx.x;
   const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -331,6 +366,7 @@ __global__ __launch_bounds__(PT, 4) void svt_pair_kernel(PairArgs a, int round) 
     const int64_t r = (int64_t)blk * RB + (tid % RB);
     rows[tid] = r < a.n1 ? (int)r : -1;
   }
+  if (tid == 0) top = 0;
   const RotArgs rot{a.xre + k * a.n1 * a.n2, a.xim + k * a.n1 * a.n2, a.ure + k * a.n1 * a.n1,
                     a.uim + k * a.n1 * a.n1, a.n1,                    a.n2,
                     (a.n2 + 31) / 32,        real,                    (int64_t)(max(ba, bb) + 1) * RB <= a.n1};
@@ -345,6 +381,7 @@ __global__ __launch_bounds__(PT, 4) void svt_pair_kernel(PairArgs a, int round) 
         } else {
           sh.raw.re[s][t] = acc[v];
           if (s0 != t0) sh.raw.re[t][s] = acc[v];
+          if (s == t) atomicMax(&top, __double2hiint(acc[v]));
         }
       }
     };
@@ -370,27 +407,39 @@ __global__ __launch_bounds__(PT, 4) void svt_pair_kernel(PairArgs a, int round) 
   // angle is below tol relative to the pair's spectral gap, which bounds
   // the error of the thresholded result by ~tol ||M||.
   double mr = 0.0;
+  // (from above the largest diagonal entry)
+  const double bound = __hiloint2double(top + 0x100000, 0) * (PR * kPairTol);
+  bool large = false;  // one entry of more than kPairTol of the Frobenius norm
 #pragma unroll
   for (int q = 0; q < PR * PR / PT; ++q) {
     const int e = tid + PT * q, s = e / PR, t = e - s * PR;
     const double gr = sh.raw.re[s][t], gi = sh.raw.im[s][t];
     const double hr = sh.raw.re[t][s], hi = sh.raw.im[t][s];
+    // exactly Hermitian
+    const double re = s == t ? gr : 0.5 * (gr + hr);
+    const double im = s < t ? 0.5 * (gi - hi) : (s > t ? -(0.5 * (hi - gi)) : 0.0);
     if (s != t) {
       const double d = fmax(sh.raw.re[s][s], sh.raw.re[t][t]);
       if (d > 0.0) mr = fmax(mr, sqrt(fma(gr, gr, gi * gi)) / d);
+      large |= fmax(fabs(re), fabs(im)) > bound;
     }
-    // exactly Hermitian
-    const double im = s < t ? 0.5 * (gi - hi) : (s > t ? -(0.5 * (hi - gi)) : 0.0);
-    sh.raw.h0[e] = Cz{s == t ? gr : 0.5 * (gr + hr), im};
+    sh.raw.h0[e] = Cz{re, im};
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mr = fmax(mr, __shfl_xor(mr, o));
-  if (l == 0) ratio_red[w] = mr;
+  large = __any(large);
+  if (l == 0) {
+    ratio_red[w] = mr;
+    mass_red[0][w] = large ? 1.0 : 0.0;
+  }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < PT / 64; ++q) mr = fmax(mr, ratio_red[q]);
+  for (int q = 0; q < PT / 64; ++q) {
+    mr = fmax(mr, ratio_red[q]);
+    large |= mass_red[0][q] != 0.0;
+  }
   if (tid == 0) a.ratio[((int64_t)round * a.K + k) * (a.nb / 2) + pair] = (float)mr;
-  if (mr < a.tol) return;
+  if (mr < a.tol || (!large && negligible(sh.raw.h0, mass_red))) return;
   int row[8];
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) row[kk] = rows[4 * kk + (l >> 4)];
