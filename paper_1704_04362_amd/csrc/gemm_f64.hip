@@ -179,8 +179,9 @@ template <int W, bool HA, bool HB>
 __global__ __launch_bounds__(NT, 2) void cgemm_f64_kernel(DArgs g) {
   __shared__ Stage<W> st;
   const int64_t per = (int64_t)g.tm * g.tn, total = per * g.K, q = (total + 7) / 8;
-  const int64_t L = g.runs ? (blockIdx.x % 8) * q + blockIdx.x / 8 : blockIdx.x;
-  if (L >= total) return;
+  // (rows of the grid are a multiple of 8 long: B mod 8 = blockIdx.x mod 8)
+  const int64_t B = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, L = g.runs ? (B % 8) * q + B / 8 : B;
+  if (B >= 8 * q || L >= total) return;
   const int64_t k = L / per, t = L - k * per;
   const int64_t m0 = (t / g.tn) * Stage<W>::T, n0 = (t % g.tn) * Stage<W>::T;
   if (k == 0 || (g.real_last && k == g.K - 1))
@@ -204,14 +205,15 @@ int cgemm_f64mfma(const CGemm& p, hipStream_t st) {
   const int64_t t64 = ((p.M + 63) / 64) * ((p.N + 63) / 64) * p.K, t32 = ((p.M + 31) / 32) * ((p.N + 31) / 32) * p.K;
   const bool wide = 40 * ((t64 + 255) / 256) <= 11 * ((t32 + 255) / 256);
   const int64_t T = wide ? 64 : 32, blocks = wide ? t64 : t32;
-  if (blocks > 0x7ffffff0LL) return fail(TP_EUNSUPPORTED, "product too large for one launch");
+  // a launch's x extent holds 2^32 work-items: at most 2^23 workgroups a row of the grid
+  const int64_t gx = std::min<int64_t>((blocks + 7) / 8 * 8, 1 << 23), gy = (blocks + gx - 1) / gx;
+  if (gy > 65535) return fail(TP_EUNSUPPORTED, "product too large for one launch");
   DArgs g{p.M, p.N, p.Kd, (const double*)p.are, (const double*)p.aim, (const double*)p.bre, (const double*)p.bim,
           (double*)p.cre, (double*)p.cim, p.lda, p.ldb, p.ldc, p.sa, p.sb, p.sc, p.K,
           p.real_last ? 1 : 0, p.kdim_dev, (int)((p.M + T - 1) / T), (int)((p.N + T - 1) / T),
           !wide && p.K >= 24 ? 1 : 0};
-  const unsigned grid = (unsigned)((blocks + 7) / 8 * 8);
   auto kernel = wide ? pick<2>(p.op_a != 0, p.op_b != 0) : pick<1>(p.op_a != 0, p.op_b != 0);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), 0, st, g);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)gx, (unsigned)gy), dim3(NT), 0, st, g);
   TP_LAUNCH_CHECK();
   return TP_OK;
 }

@@ -37,3 +37,15 @@ def test_f64_products_at_tile_edges(K, M, N, Kd, op_a, op_b, real_last):
         ref = (a.conj().T if op_a else a) @ (b.conj().T if op_b else b)
         got = re[k].cpu().numpy() + 1j * im[k].cpu().numpy()
         assert np.linalg.norm(got - ref) <= 1e-14 * np.sqrt(Kd) * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("K,N", [(1, 2 ** 29 + 70), (30, 2 ** 24 * 32 // 30 + 5)])
+def test_f64_products_of_more_tiles_than_a_grid_row_holds(K, N):
+    """2^24 tiles and a few more (a launch's x extent holds 2^32 work-items), in
+    the round-robin order and in runs per XCD. Products of one term: exact."""
+    a = torch.full((K, 1, 1), 3.0, dtype=torch.float64, device="cuda")
+    b = torch.arange(K * N, dtype=torch.float64, device="cuda").view(K, 1, N)
+    re, im = api.spectrum_matmul((a, a), (b, b), real_last=False, prec="f64")
+    assert torch.equal(re[0], 3.0 * b[0]) and not im[0].any()
+    if K > 1:  # (3 + 3i)(b + bi) = 6bi
+        assert not re[1:].any() and torch.equal(im[1:], 6.0 * b[1:])
