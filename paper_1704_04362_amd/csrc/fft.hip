@@ -691,7 +691,8 @@ int pair_impl(const T* x, const TubeGather& g, T* re, T* im, const T* y, const T
   const bool packed = pick_pair<T>(n3) != nullptr;
   const auto k = packed ? pick_pair<T>(n3) : pick_small_pair<T>(n3);
   const int64_t nt = packed ? kTile : kSmallNT, np = (p.a.ntubes + nt - 1) / nt, nq = (q.a.ntubes + nt - 1) / nt;
-  *handled = k && np + nq <= 0x7fffffffLL && np + nq > 0;
+  // (a launch holds 2^32 work-items: beyond, each operand has its own)
+  *handled = k && np + nq > 0 && (np + nq) * nt < int64_t(1) << 32;
   if (!*handled) return TP_OK;
   hipLaunchKernelGGL(k, dim3((unsigned)(np + nq)), dim3((unsigned)nt), 0, st, p, np, q);
   TP_LAUNCH_CHECK();

@@ -102,3 +102,18 @@ def test_products_with_both_operands_in_one_launch(n3, prec, tol):
     Z = api.tprod(dev(A), dev(B), picks=picks, prec=prec).cpu().numpy()
     idx, sc = picks.host()
     assert T.rel_fro(Z, D.rtprod(A, B, idx.numpy(), sc.numpy())) < tol
+
+
+def test_product_of_operands_of_more_tubes_together_than_a_launch_holds():
+    """2^32 tubes in both operands (20 GB; a launch holds 2^32 work-items): two
+    launches. Whole numbers small enough for exact float32 products and sums."""
+    n2 = 40_000_000
+    A = torch.zeros((64, n2, 1), dtype=torch.float32, device="cuda")
+    B = torch.zeros((n2, 64, 1), dtype=torch.float32, device="cuda")
+    at = torch.randint(n2, (1000,), generator=torch.Generator().manual_seed(1)).unique().cuda()
+    A[:, at] = torch.arange(64 * len(at), device="cuda").remainder(7).float().view(64, -1, 1)
+    B[at] = torch.arange(len(at) * 64, device="cuda").remainder(5).float().view(-1, 64, 1)
+    C = api.tprod(A, B, prec="f32")
+    ref = A[:, at, 0].cpu().double() @ B[at, :, 0].cpu().double()
+    api._WS_CACHE.clear()  # (41 GB)
+    assert torch.equal(C[..., 0].cpu().double(), ref)
