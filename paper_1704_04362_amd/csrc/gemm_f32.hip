@@ -306,7 +306,8 @@ int cgemm_f32mfma(const CGemm& p, hipStream_t st, bool* handled) {
   FArgs g{p.M, p.N, p.Kd, (const float*)p.are, (const float*)p.aim, (const float*)p.bre, (const float*)p.bim,
           (float*)p.cre, (float*)p.cim, p.lda, p.ldb, p.ldc, p.sa, p.sb, p.sc, p.op_a, p.op_b, p.K,
           p.real_last ? 1 : 0, p.kdim_dev, ksplit, p.part_re, p.part_im};
-  const bool near = p.lda < (1 << 23) && p.ldb < (1 << 23), wide = !near || f32_wide(p, ksplit);
+  // (64-row tiles of more than 4,194,240 rows pass the 65,535 rows of the grid)
+  const bool near = p.lda < (1 << 23) && p.ldb < (1 << 23), wide = !near || p.M > 64 * 65535 || f32_wide(p, ksplit);
   const int64_t side = wide ? 128 : 64, gx = (p.N + side - 1) / side, gy = (p.M + side - 1) / side;
   if (gx > 0x7fffffff || gy > 65535) return TP_OK;
   const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)(p.K * ksplit));

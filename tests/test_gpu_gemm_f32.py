@@ -58,3 +58,19 @@ def test_f32_products_of_rows_beyond_32_bit_tile_offsets():
     err = torch.stack((re.double(), im.double()), 1) - ref
     for k in range(2):
         assert err[k].norm() <= 2.0 ** -24 * Kd ** 0.5 * 4 * ref[k].norm()
+
+
+@pytest.mark.parametrize("M", [64 * 65535, 64 * 65535 + 1])
+@pytest.mark.parametrize("N", [20, 150])
+def test_f32_products_of_very_many_rows(M, N):
+    """As many rows as the grid holds in tiles of 64, and one more (tiles of 128).
+    Either tile, and a product of the last rows alone, adds an output's products
+    in the same order: the same bits; the vector kernel, whose complex products take
+    four real ones, gives others."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=g)  # noqa: E731
+    a, b = (rnd(2, M, 64), rnd(2, M, 64)), (rnd(2, N, 64), rnd(2, N, 64))
+    re, im = api.spectrum_matmul(a, b, 0, 1, real_last=False, prec="f32")
+    for rows in (slice(0, 200), slice(M - 200, M)):
+        few = api.spectrum_matmul(tuple(t[:, rows].contiguous() for t in a), b, 0, 1, real_last=False, prec="f32")
+        assert torch.equal(re[:, rows], few[0]) and torch.equal(im[:, rows], few[1])
