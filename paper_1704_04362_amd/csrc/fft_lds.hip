@@ -260,14 +260,18 @@ __device__ void load_tubes(const T* x, const int64_t* src, const double* scl, co
       if (f >= pc.total || piece >= pc.nv) continue;
       const bool live = src[u] >= 0;
       const double s = scl[u];
-      T w[E];
+      // a scaled value is rounded to its type, except before Bluestein's chirp
+      double w[E];
 #pragma unroll
-      for (int e = 0; e < E; ++e) w[e] = !live ? T(0) : (s == 1.0) ? v[q].v[e] : (T)((double)v[q].v[e] * s);
+      for (int e = 0; e < E; ++e) {
+        const double t = (double)v[q].v[e], ts = t * s;
+        w[e] = !live ? 0.0 : (s == 1.0) ? t : BLUE ? ts : (double)(T)ts;
+      }
       constexpr int C = E > 1 ? E / 2 : 1;
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         const int m = piece * C + c;
-        double zr = (double)w[E > 1 ? 2 * c : 0], zi = E > 1 ? (double)w[E > 1 ? 2 * c + 1 : 0] : 0.0;
+        double zr = w[E > 1 ? 2 * c : 0], zi = E > 1 ? w[E > 1 ? 2 * c + 1 : 0] : 0.0;
         if constexpr (BLUE) {
           const Cx<double> h = l.chirp[m];
           const double t = zr;

@@ -117,3 +117,24 @@ def test_product_of_operands_of_more_tubes_together_than_a_launch_holds():
     ref = A[:, at, 0].cpu().double() @ B[at, :, 0].cpu().double()
     api._WS_CACHE.clear()  # (41 GB)
     assert torch.equal(C[..., 0].cpu().double(), ref)
+
+
+@pytest.mark.parametrize("n3", [499, 998])
+def test_scaled_slices_enter_bluesteins_transform_unrounded(n3):
+    """Impulses of 1 to 1.02 times a scale just below 1 + 2^-24: rounded to float32
+    before the chirp, every scaled value falls back to the impulse, 2^-24 of it,
+    and a product of two twice that (at position 7, whose chirp is no power of two
+    times 1: the rounding after it is another for every value). The roundings of the transforms and products
+    differ from slice to slice and from output to output: their mean over 64 x 64
+    outputs of 250 slices or more is a hundredth of 2^-24."""
+    s = 1.0 + 0.98 * 2.0 ** -24
+    g = np.random.default_rng(n3)
+    A, B = np.zeros((64, 1, n3), np.float32), np.zeros((1, 64, n3), np.float32)
+    A[:, 0, 7], B[0, :, 7] = 1 + 0.02 * g.random(64), 1 + 0.02 * g.random(64)
+    picks = api.Picks(1, "cuda")
+    picks.idx.zero_()
+    picks.scale.fill_(s)
+    picks.count.fill_(1)
+    Z = api.tprod(dev(A), dev(B), picks=picks, prec="f32").cpu().numpy().astype(np.float64)
+    ref = np.outer(A[:, 0, 7].astype(np.float64), B[0, :, 7].astype(np.float64)) * s * s
+    assert abs(np.mean(Z[:, :, 14] / ref - 1)) < 2.0 ** -24
