@@ -20,9 +20,9 @@
 //      and each slice k is written with one coalesced store per wavefront.
 // The inverse kernel runs these steps backwards. Short lengths without a
 // packed kernel run one tube per thread (rfft_small_kernel); other lengths
-// that LDS holds take the transforms of fft_lds.hip; even ones beyond it (up
-// to 2^19) a four-step transform through HBM; the rest a direct O(n3^2)
-// transform.
+// that LDS holds take the transforms of fft_lds.hip, or of fft_dense.hip where
+// there is a prime factor above 13; even ones beyond it (up to 2^19) a
+// four-step transform through HBM; the rest a direct O(n3^2) transform.
 #include <cmath>
 #include <mutex>
 #include <vector>
@@ -671,7 +671,7 @@ struct TypeOf<double> {
   static constexpr int dtype = TP_F64;
 };
 
-// longest tube of the LDS transforms (fft_lds.hip)
+// longest tube of fft_lds.hip and fft_dense.hip
 template <typename T>
 constexpr int64_t lds_max() {
   return 32768 / (int64_t)sizeof(T);
@@ -712,9 +712,10 @@ int fwd_impl(const T* x, int64_t n3, const TubeGather& g, T* re, T* im, hipStrea
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kSmallNT), 0, st, x, a, re, im);
   } else {
     bool handled = false;
-    if (n3 <= lds_max<T>() && !sums)
+    if (n3 <= lds_max<T>() && !sums) {
       if (int rc = lds_forward(x, TypeOf<T>::dtype, n3, a, re, im, st, &handled)) return rc;
-    if (handled) return TP_OK;
+      return handled ? TP_OK : dense_forward(x, TypeOf<T>::dtype, n3, a, re, im, st);
+    }
     if (n3 >= kLongMin)
       if (int rc = four_forward(x, TypeOf<T>::dtype, n3, a, re, im, st, &handled)) return rc;
     if (handled) return TP_OK;
@@ -742,9 +743,10 @@ int inv_impl(const T* re, const T* im, int64_t n3, int64_t ntubes, T* y, hipStre
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kSmallNT), 0, st, re, im, ntubes, y);
   } else {
     bool handled = false;
-    if (n3 <= lds_max<T>() && !sums)
+    if (n3 <= lds_max<T>() && !sums) {
       if (int rc = lds_inverse(re, im, TypeOf<T>::dtype, n3, ntubes, y, st, &handled)) return rc;
-    if (handled) return TP_OK;
+      return handled ? TP_OK : dense_inverse(re, im, TypeOf<T>::dtype, n3, ntubes, y, st);
+    }
     if (n3 >= kLongMin)
       if (int rc = four_inverse(re, im, TypeOf<T>::dtype, n3, ntubes, y, st, &handled)) return rc;
     if (handled) return TP_OK;

@@ -1,29 +1,23 @@
-// Tube transforms of any length that LDS holds and that has no register
-// kernel: 2^lg tubes per workgroup.
+// Tube transforms of the lengths without prime factors above 13 that LDS holds
+// and that have no register kernel: 2^lg tubes per workgroup.
 //
 // A real tube of even length n is packed as N = n/2 complex values
 // z[m] = x[2m] + i x[2m+1]; an odd one takes N = n complex values with zero
 // imaginary part. The N-point transforms run in place through LDS in the
 // mixed-radix stages of fft_stages.hpp. Lengths whose N has a prime factor
-// above 13 take Bluestein's chirp-z transform: with w[m] = exp(-i pi m^2 / N),
-// Z[k] = w[k] sum_m (z[m] w[m]) conj(w[k - m]) (from 2 m k = m^2 + k^2 -
-// (k - m)^2), a circular convolution of length L >= 2N - 1: a forward
-// transform (decimation in frequency, which leaves its result digit-reversed),
-// the product with the transformed filter (kept in the same order), and the
-// inverse through the conjugate (decimation in time, digit-reversed in).
+// above 13 take the dense products of fft_dense.hip.
 //
 // What bounds it: HBM, then the LDS round trips of the stages. Several tubes
 // per workgroup make the spectrum side of the transform, slice-major, runs of
-// 2^lg neighbouring values instead of single ones, and spread the roots, the
-// index table and the Bluestein filter over that many tubes; XCD-contiguous
+// 2^lg neighbouring values instead of single ones, and spread the roots and
+// the index table over that many tubes; XCD-contiguous
 // launch order lets neighbouring workgroups complete each other's cache lines
 // in one L2. Stages of radix up to 16 in registers (three for n = 2000), with
 // float64 butterflies (see fft_stages.hpp).
 // Measured (3e7 values, us forward / inverse, against the transforms these
 // replaced: one workgroup per tube with a run-time radix for n > 256, a direct
 // sum per tube below): float32 n = 80 1374 / 1901 -> 112 / 80, n = 256
-// 2677 / 11831 -> 112 / 80, n = 2000 1656 / 1641 -> 118 / 98, n = 1021
-// (Bluestein) 3232 / 3193 -> 620 / 625; float64 n = 60 1779 / 2197 -> 132 / 117,
+// 2677 / 11831 -> 112 / 80, n = 2000 1656 / 1641 -> 118 / 98; float64 n = 60 1779 / 2197 -> 132 / 117,
 // n = 2000 1626 / 1697 -> 194 / 188. A copy of the same bytes takes 46 (92) us:
 // the rest is the vector work of the stages, whose LDS round trips and
 // twiddles take about as long as the bytes.
@@ -96,49 +90,31 @@ constexpr int64_t kLdsMax = 160 * 1024;  // per workgroup (and per CU)
 
 struct LdsPlan {
   int n, N, lg;  // tube length, complex length, log2 of the tubes per workgroup
-  lfft::Plan pl; // length N, or the convolution length
+  lfft::Plan pl; // length N
 };
 
-// dynamic LDS, in order: roots of the stages; Bluestein: roots of the
-// separation (even n), chirp, transformed filter; data; tube sources and
-// scales; plain: positions
-template <typename S, bool BLUE>
+// dynamic LDS, in order: roots of the stages; data; tube sources and scales;
+// positions
+template <typename S>
 struct Layout {
-  Cx<double>*tab, *post, *chirp;
-  Cx<S>*filt, *buf;
+  Cx<double>* tab;
+  Cx<S>* buf;
   int64_t* src;  // [2][tubes]: of this block and the next
   double* scl;
   uint16_t* pos;
   size_t bytes;
   __host__ __device__ Layout(const LdsPlan& p, unsigned char* base) {
-    const int L = p.pl.n, even = p.n % 2 == 0;
     size_t o = 0;
     tab = (Cx<double>*)(base + o);
-    o += sizeof(Cx<double>) * (L / 2 + 1);
-    post = tab;
-    chirp = nullptr;
-    filt = nullptr;
-    pos = nullptr;
-    if (BLUE) {
-      if (even) {
-        post = (Cx<double>*)(base + o);
-        o += sizeof(Cx<double>) * (p.N / 2 + 1);
-      }
-      chirp = (Cx<double>*)(base + o);
-      o += sizeof(Cx<double>) * p.N;
-      filt = (Cx<S>*)(base + o);
-      o += sizeof(Cx<S>) * L;
-    }
+    o += sizeof(Cx<double>) * (p.N / 2 + 1);
     buf = (Cx<S>*)(base + o);
-    o += (sizeof(Cx<S>) * L) << p.lg;
+    o += (sizeof(Cx<S>) * p.N) << p.lg;
     src = (int64_t*)(base + o);
     o += size_t(16) << p.lg;
     scl = (double*)(base + o);
     o += size_t(16) << p.lg;
-    if (!BLUE) {
-      pos = (uint16_t*)(base + o);
-      o += 2 * size_t(p.N);
-    }
+    pos = (uint16_t*)(base + o);
+    o += 2 * size_t(p.N);
     bytes = o;
   }
 };
@@ -159,62 +135,12 @@ __device__ __forceinline__ void store_run(T* p, const Run<T, E>& r) {
   __builtin_memcpy(p, &r, sizeof(r));
 }
 
-// roots, positions, Bluestein's chirp and its transformed filter
-template <typename S, bool BLUE, bool EXACT>
-__device__ void setup(const LdsPlan& p, const Layout<S, BLUE>& l) {
-  lfft::fill_roots(p.pl.n, l.tab);
-  if constexpr (!BLUE) {
-    lfft::fill_positions(p.pl, l.pos);
-  } else {
-    const int N = p.N, L = p.pl.n;
-    if (p.n % 2 == 0) lfft::fill_roots(N, l.post);
-    for (int m = threadIdx.x; m < N; m += blockDim.x) {
-      double s, c;
-      const int64_t e = ((int64_t)m * m) % (2 * (int64_t)N);
-      sincospi(-(double)e / (double)N, &s, &c);
-      l.chirp[m] = Cx<double>{c, s};
-    }
-    __syncthreads();
-    for (int m = threadIdx.x; m < L; m += blockDim.x) {
-      Cx<S> v{S(0), S(0)};
-      const int d = m < N ? m : (m > L - N ? L - m : -1);
-      if (d >= 0) v = Cx<S>{(S)l.chirp[d].x, (S)-l.chirp[d].y};
-      l.filt[m] = v;
-    }
-    __syncthreads();
-    lfft::stages<S, true, EXACT>(p.pl, l.filt, 0, l.tab);
-  }
-}
-
-// Bluestein: buf holds z[m] w[m] (zeros from N on); leaves conj(L (z w * conj w))
-template <typename S, bool EXACT>
-__device__ void convolve(const LdsPlan& p, const Layout<S, true>& l) {
-  lfft::stages<S, true, EXACT>(p.pl, l.buf, p.lg, l.tab);
-  for (int e = threadIdx.x; e < (p.pl.n << p.lg); e += blockDim.x) {
-    const Cx<S> a = l.buf[e], f = l.filt[e >> p.lg];
-    const double ar = (double)a.x, ai = (double)a.y, fr = (double)f.x, fi = (double)f.y;
-    l.buf[e] = Cx<S>{(S)(ar * fr - ai * fi), (S)(-(ar * fi + ai * fr))};
-  }
-  __syncthreads();
-  lfft::stages<S, false, EXACT>(p.pl, l.buf, p.lg, l.tab);
-}
-
-// element k of the transform of the sequence `u` (plain: DIF stages done;
-// Bluestein: convolve done)
-template <typename S, bool BLUE>
-__device__ __forceinline__ void result(const LdsPlan& p, const Layout<S, BLUE>& l, int k, int u, double& r, double& i) {
-  if constexpr (BLUE) {
-    const Cx<S> v = l.buf[(k << p.lg) + u];
-    const Cx<double> w = l.chirp[k];
-    const double inv = 1.0 / (double)p.pl.n;
-    const double yr = (double)v.x * inv, yi = -(double)v.y * inv;
-    r = yr * w.x - yi * w.y;
-    i = yr * w.y + yi * w.x;
-  } else {
-    const Cx<S> v = l.buf[((int)l.pos[k] << p.lg) + u];
-    r = (double)v.x;
-    i = (double)v.y;
-  }
+// element k of the transform of the sequence `u` (after the stages)
+template <typename S>
+__device__ __forceinline__ void result(const LdsPlan& p, const Layout<S>& l, int k, int u, double& r, double& i) {
+  const Cx<S> v = l.buf[((int)l.pos[k] << p.lg) + u];
+  r = (double)v.x;
+  i = (double)v.y;
 }
 
 // Tube-major side: pieces of E values, 2^plog consecutive pieces of a tube
@@ -237,9 +163,9 @@ constexpr int kBatch = 8;  // pieces whose loads a thread keeps in flight
 
 // Reads the tubes into buf in natural order. E values make E/2 complex
 // elements (even n), or one with zero imaginary part (E = 1, odd n).
-template <typename T, typename S, bool BLUE, int E>
+template <typename T, typename S, int E>
 __device__ void load_tubes(const T* x, const int64_t* src, const double* scl, const LdsPlan& p,
-                           const Layout<S, BLUE>& l) {
+                           const Layout<S>& l) {
   const Pieces pc(p.n / E, p.lg);
   for (int f0 = threadIdx.x; f0 < pc.total; f0 += kBatch * blockDim.x) {
     Run<T, E> v[kBatch];
@@ -260,24 +186,18 @@ __device__ void load_tubes(const T* x, const int64_t* src, const double* scl, co
       if (f >= pc.total || piece >= pc.nv) continue;
       const bool live = src[u] >= 0;
       const double s = scl[u];
-      // a scaled value is rounded to its type, except before Bluestein's chirp
+      // a scaled value is rounded to its type
       double w[E];
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const double t = (double)v[q].v[e], ts = t * s;
-        w[e] = !live ? 0.0 : (s == 1.0) ? t : BLUE ? ts : (double)(T)ts;
+        w[e] = !live ? 0.0 : (s == 1.0) ? t : (double)(T)ts;
       }
       constexpr int C = E > 1 ? E / 2 : 1;
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         const int m = piece * C + c;
-        double zr = w[E > 1 ? 2 * c : 0], zi = E > 1 ? w[E > 1 ? 2 * c + 1 : 0] : 0.0;
-        if constexpr (BLUE) {
-          const Cx<double> h = l.chirp[m];
-          const double t = zr;
-          zr = t * h.x - zi * h.y;
-          zi = t * h.y + zi * h.x;
-        }
+        const double zr = w[E > 1 ? 2 * c : 0], zi = E > 1 ? w[E > 1 ? 2 * c + 1 : 0] : 0.0;
         l.buf[(m << p.lg) + u] = Cx<S>{(S)zr, (S)zi};
       }
     }
@@ -286,8 +206,8 @@ __device__ void load_tubes(const T* x, const int64_t* src, const double* scl, co
 
 // Writes the tubes: element m of the transformed conjugate, conjugated and
 // times `inv`, is the tube's values 2m and 2m+1 (odd n: value m)
-template <typename T, typename S, bool BLUE, int E>
-__device__ void store_tubes(T* y, int64_t t0, int64_t ntubes, const LdsPlan& p, const Layout<S, BLUE>& l) {
+template <typename T, typename S, int E>
+__device__ void store_tubes(T* y, int64_t t0, int64_t ntubes, const LdsPlan& p, const Layout<S>& l) {
   const Pieces pc(p.n / E, p.lg);
   const double inv = 1.0 / (double)p.N;
   for (int f = threadIdx.x; f < pc.total; f += blockDim.x) {
@@ -300,27 +220,20 @@ __device__ void store_tubes(T* y, int64_t t0, int64_t ntubes, const LdsPlan& p, 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       const int m = piece * C + c;
-      double r, i;
-      if constexpr (BLUE) {
-        result<S, true>(p, l, m, u, r, i);
-      } else {
-        const Cx<S> w = l.buf[(m << p.lg) + u];
-        r = (double)w.x;
-        i = (double)w.y;
-      }
-      v.v[E > 1 ? 2 * c : 0] = (T)(r * inv);
-      if constexpr (E > 1) v.v[2 * c + 1] = (T)(-i * inv);
+      const Cx<S> w = l.buf[(m << p.lg) + u];
+      v.v[E > 1 ? 2 * c : 0] = (T)((double)w.x * inv);
+      if constexpr (E > 1) v.v[2 * c + 1] = (T)(-(double)w.y * inv);
     }
     store_run<T, E>(y + t * p.n + (int64_t)piece * E, v);
   }
 }
 
-template <typename T, typename S, bool BLUE>
+template <typename T, typename S>
 __global__ __launch_bounds__(kMaxNT, 4) void rfft_lds_kernel(const T* __restrict__ x, FwdArgs a, LdsPlan p,
                                                           T* __restrict__ ore, T* __restrict__ oim) {
   constexpr bool EXACT = sizeof(T) == 8;
   extern __shared__ __align__(16) unsigned char lfft_lds[];
-  const Layout<S, BLUE> l(p, lfft_lds);
+  const Layout<S> l(p, lfft_lds);
   const int TB = 1 << p.lg, N = p.N;
   const int64_t ks = a.ntubes;
   auto sources = [&](int64_t G, int half) {
@@ -338,35 +251,30 @@ __global__ __launch_bounds__(kMaxNT, 4) void rfft_lds_kernel(const T* __restrict
   bool more = walk.next(G);
   if (!more) return;
   sources(G, 0);
-  setup<S, BLUE, EXACT>(p, l);
+  lfft::fill_roots(N, l.tab);
+  lfft::fill_positions(p.pl, l.pos);
   __syncthreads();
   for (int half = 0; more; half ^= 1, G = next) {
     const int64_t t0 = G << p.lg;
     const int64_t* src = l.src + half * TB;
     const double* scl = l.scl + half * TB;
     if (p.n % 2)
-      load_tubes<T, S, BLUE, 1>(x, src, scl, p, l);
+      load_tubes<T, S, 1>(x, src, scl, p, l);
     else if (sizeof(T) == 4 && p.n % 4 == 0)
-      load_tubes<T, S, BLUE, sizeof(T) == 4 ? 4 : 2>(x, src, scl, p, l);
+      load_tubes<T, S, sizeof(T) == 4 ? 4 : 2>(x, src, scl, p, l);
     else
-      load_tubes<T, S, BLUE, 2>(x, src, scl, p, l);
+      load_tubes<T, S, 2>(x, src, scl, p, l);
     more = walk.next(next);
     if (more) sources(next, half ^ 1);
-    if constexpr (BLUE) {
-      for (int e = (p.N << p.lg) + threadIdx.x; e < (p.pl.n << p.lg); e += blockDim.x) l.buf[e] = Cx<S>{S(0), S(0)};
-      __syncthreads();
-      convolve<S, EXACT>(p, l);
-    } else {
-      __syncthreads();
-      lfft::stages<S, true, EXACT>(p.pl, l.buf, p.lg, l.tab);
-    }
+    __syncthreads();
+    lfft::stages<S, true, EXACT>(p.pl, l.buf, p.lg, l.tab);
     if (p.n % 2) {
       for (int e = threadIdx.x; e < ((p.n / 2 + 1) << p.lg); e += blockDim.x) {
         const int k = e >> p.lg, u = e & (TB - 1);
         const int64_t t = t0 + u;
         if (t >= ks) continue;
         double r, i;
-        result<S, BLUE>(p, l, k, u, r, i);
+        result<S>(p, l, k, u, r, i);
         ore[(int64_t)k * ks + t] = (T)r;
         oim[(int64_t)k * ks + t] = k == 0 ? T(0) : (T)i;
       }
@@ -380,7 +288,7 @@ __global__ __launch_bounds__(kMaxNT, 4) void rfft_lds_kernel(const T* __restrict
       const int64_t t = t0 + u;
       if (t >= ks) continue;
       double zr, zi, wr, wi;
-      result<S, BLUE>(p, l, k, u, zr, zi);
+      result<S>(p, l, k, u, zr, zi);
       if (k == 0) {
         ore[t] = (T)(zr + zi);
         oim[t] = T(0);
@@ -388,10 +296,10 @@ __global__ __launch_bounds__(kMaxNT, 4) void rfft_lds_kernel(const T* __restrict
         oim[(int64_t)N * ks + t] = T(0);
         continue;
       }
-      result<S, BLUE>(p, l, N - k, u, wr, wi);
+      result<S>(p, l, N - k, u, wr, wi);
       const double er = 0.5 * (zr + wr), ei = 0.5 * (zi - wi);
       const double dr = 0.5 * (zi + wi), di = 0.5 * (wr - zr);
-      const Cx<double> w = l.post[k];
+      const Cx<double> w = l.tab[k];
       const double pr = dr * w.x - di * w.y, pi = dr * w.y + di * w.x;
       ore[(int64_t)k * ks + t] = (T)(er + pr);
       oim[(int64_t)k * ks + t] = (T)(ei + pi);
@@ -406,14 +314,15 @@ __global__ __launch_bounds__(kMaxNT, 4) void rfft_lds_kernel(const T* __restrict
 
 constexpr int kInvBatch = 4;  // (k, N - k) pairs whose loads a thread keeps in flight
 
-template <typename T, typename S, bool BLUE>
+template <typename T, typename S>
 __global__ __launch_bounds__(kMaxNT, 4) void irfft_lds_kernel(const T* __restrict__ xre, const T* __restrict__ xim,
                                                            int64_t ks, LdsPlan p, T* __restrict__ y) {
   constexpr bool EXACT = sizeof(T) == 8;
   extern __shared__ __align__(16) unsigned char lfft_lds[];
-  const Layout<S, BLUE> l(p, lfft_lds);
+  const Layout<S> l(p, lfft_lds);
   const int TB = 1 << p.lg, N = p.N;
-  setup<S, BLUE, EXACT>(p, l);
+  lfft::fill_roots(N, l.tab);
+  lfft::fill_positions(p.pl, l.pos);
   __syncthreads();
   XcdWalk walk((ks + TB - 1) >> p.lg);
   for (int64_t G; walk.next(G);) {
@@ -421,12 +330,7 @@ __global__ __launch_bounds__(kMaxNT, 4) void irfft_lds_kernel(const T* __restric
     // conj Z into buf: the forward transform of the conjugate is the conjugate
     // of the inverse
     auto put = [&](int k, int u, double zr, double zi) {
-      if constexpr (BLUE) {
-        const Cx<double> h = l.chirp[k];
-        l.buf[(k << p.lg) + u] = Cx<S>{(S)(zr * h.x - zi * h.y), (S)(zr * h.y + zi * h.x)};
-      } else {
-        l.buf[((int)l.pos[k] << p.lg) + u] = Cx<S>{(S)zr, (S)zi};
-      }
+      l.buf[((int)l.pos[k] << p.lg) + u] = Cx<S>{(S)zr, (S)zi};
     };
     const bool odd = p.n % 2;
     const int total = (N / 2 + 1) << p.lg;
@@ -460,26 +364,20 @@ __global__ __launch_bounds__(kMaxNT, 4) void irfft_lds_kernel(const T* __restric
         const double yr = (double)br[q], yi = k == 0 ? 0.0 : (double)bi[q];
         const double er = 0.5 * (xr + yr), ei = 0.5 * (xi - yi);
         const double dr = 0.5 * (xr - yr), di = 0.5 * (xi + yi);
-        const Cx<double> w = l.post[k];
+        const Cx<double> w = l.tab[k];
         const double qr = dr * w.x + di * w.y, qi = di * w.x - dr * w.y;
         put(k, u, er - qi, -(ei + qr));
         if (k > 0 && 2 * k < N) put(N - k, u, er + qi, ei - qr);
       }
     }
-    if constexpr (BLUE) {
-      for (int e = (N << p.lg) + threadIdx.x; e < (p.pl.n << p.lg); e += blockDim.x) l.buf[e] = Cx<S>{S(0), S(0)};
-      __syncthreads();
-      convolve<S, EXACT>(p, l);
-    } else {
-      __syncthreads();
-      lfft::stages<S, false, EXACT>(p.pl, l.buf, p.lg, l.tab);
-    }
+    __syncthreads();
+    lfft::stages<S, false, EXACT>(p.pl, l.buf, p.lg, l.tab);
     if (odd)
-      store_tubes<T, S, BLUE, 1>(y, t0, ks, p, l);
+      store_tubes<T, S, 1>(y, t0, ks, p, l);
     else if (sizeof(T) == 4 && p.n % 4 == 0)
-      store_tubes<T, S, BLUE, sizeof(T) == 4 ? 4 : 2>(y, t0, ks, p, l);
+      store_tubes<T, S, sizeof(T) == 4 ? 4 : 2>(y, t0, ks, p, l);
     else
-      store_tubes<T, S, BLUE, 2>(y, t0, ks, p, l);
+      store_tubes<T, S, 2>(y, t0, ks, p, l);
     __syncthreads();
   }
 }
@@ -488,12 +386,12 @@ __global__ __launch_bounds__(kMaxNT, 4) void irfft_lds_kernel(const T* __restric
 // 112 us against 137 with 512; 512 otherwise: n = 2048 117 against 133). As many tubes (a power of two) as leave
 // two workgroups per CU (half of the LDS each), or eight if one fills it;
 // fewer when there are too few tubes for two workgroups per CU.
-template <typename S, bool BLUE>
+template <typename S>
 bool lds_fit(LdsPlan& p, int64_t ntubes, size_t& bytes, int& nt) {
   auto need = [&](int lg) {
     LdsPlan q = p;
     q.lg = lg;
-    return (int64_t)Layout<S, BLUE>(q, nullptr).bytes;
+    return (int64_t)Layout<S>(q, nullptr).bytes;
   };
   if (need(0) > kLdsMax) return false;
   p.lg = 0;
@@ -519,39 +417,32 @@ int64_t lds_grid(int64_t blocks, size_t bytes, int nt) {
   return xcd_grid(std::min<int64_t>(blocks, 256 * std::max<int64_t>(per_cu, 1)));
 }
 
-// plan of a tube length: the complex length itself, or Bluestein's
-// convolution length
-bool lds_plan(int64_t n, LdsPlan& p, bool& blue) {
+bool lds_plan(int64_t n, LdsPlan& p) {
   p.n = (int)n;
   p.N = n % 2 ? (int)n : (int)(n / 2);
-  blue = false;
-  if (lfft::radix_plan(p.N, p.pl)) return true;
-  blue = true;
-  for (int64_t L = 2 * (int64_t)p.N - 1; L < 2 * (2 * (int64_t)p.N); ++L)
-    if (lfft::radix_plan(L, p.pl)) return true;
-  return false;
+  return lfft::radix_plan(p.N, p.pl);
 }
 
-template <typename T, typename S, bool BLUE>
+template <typename T, typename S>
 int launch_fwd(LdsPlan p, const T* x, const FwdArgs& a, T* re, T* im, hipStream_t st, bool* handled) {
   size_t bytes;
   int nt;
-  if (!lds_fit<S, BLUE>(p, a.ntubes, bytes, nt)) return TP_OK;
+  if (!lds_fit<S>(p, a.ntubes, bytes, nt)) return TP_OK;
   *handled = true;
   const int64_t grid = lds_grid((a.ntubes + (1 << p.lg) - 1) >> p.lg, bytes, nt);
-  hipLaunchKernelGGL((rfft_lds_kernel<T, S, BLUE>), dim3((unsigned)grid), dim3(nt), bytes, st, x, a, p, re, im);
+  hipLaunchKernelGGL((rfft_lds_kernel<T, S>), dim3((unsigned)grid), dim3(nt), bytes, st, x, a, p, re, im);
   TP_LAUNCH_CHECK();
   return TP_OK;
 }
 
-template <typename T, typename S, bool BLUE>
+template <typename T, typename S>
 int launch_inv(LdsPlan p, const T* re, const T* im, int64_t ntubes, T* y, hipStream_t st, bool* handled) {
   size_t bytes;
   int nt;
-  if (!lds_fit<S, BLUE>(p, ntubes, bytes, nt)) return TP_OK;
+  if (!lds_fit<S>(p, ntubes, bytes, nt)) return TP_OK;
   *handled = true;
   const int64_t grid = lds_grid((ntubes + (1 << p.lg) - 1) >> p.lg, bytes, nt);
-  hipLaunchKernelGGL((irfft_lds_kernel<T, S, BLUE>), dim3((unsigned)grid), dim3(nt), bytes, st, re, im, ntubes, p, y);
+  hipLaunchKernelGGL((irfft_lds_kernel<T, S>), dim3((unsigned)grid), dim3(nt), bytes, st, re, im, ntubes, p, y);
   TP_LAUNCH_CHECK();
   return TP_OK;
 }
@@ -567,40 +458,26 @@ int lds_forward(const void* x, int dtype, int64_t n3, const FwdArgs& a, void* re
                 bool* handled) {
   *handled = false;
   LdsPlan p;
-  bool blue;
-  if (n3 < 2 || n3 > kLdsLenMax || !lds_plan(n3, p, blue)) return TP_OK;
-  if (dtype == TP_F64) {
-    const double* xd = (const double*)x;
-    return blue ? launch_fwd<double, double, true>(p, xd, a, (double*)re, (double*)im, st, handled)
-                : launch_fwd<double, double, false>(p, xd, a, (double*)re, (double*)im, st, handled);
-  }
+  if (n3 < 2 || n3 > kLdsLenMax || !lds_plan(n3, p)) return TP_OK;
+  if (dtype == TP_F64)
+    return launch_fwd<double, double>(p, (const double*)x, a, (double*)re, (double*)im, st, handled);
   const float* xf = (const float*)x;
   float *fr = (float*)re, *fi = (float*)im;
-  if (n3 <= kWideMax)
-    return blue ? launch_fwd<float, double, true>(p, xf, a, fr, fi, st, handled)
-                : launch_fwd<float, double, false>(p, xf, a, fr, fi, st, handled);
-  return blue ? launch_fwd<float, float, true>(p, xf, a, fr, fi, st, handled)
-              : launch_fwd<float, float, false>(p, xf, a, fr, fi, st, handled);
+  return n3 <= kWideMax ? launch_fwd<float, double>(p, xf, a, fr, fi, st, handled)
+                        : launch_fwd<float, float>(p, xf, a, fr, fi, st, handled);
 }
 
 int lds_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t ntubes, void* y, hipStream_t st,
                 bool* handled) {
   *handled = false;
   LdsPlan p;
-  bool blue;
-  if (n3 < 2 || n3 > kLdsLenMax || !lds_plan(n3, p, blue)) return TP_OK;
-  if (dtype == TP_F64) {
-    const double *dr = (const double*)re, *di = (const double*)im;
-    return blue ? launch_inv<double, double, true>(p, dr, di, ntubes, (double*)y, st, handled)
-                : launch_inv<double, double, false>(p, dr, di, ntubes, (double*)y, st, handled);
-  }
+  if (n3 < 2 || n3 > kLdsLenMax || !lds_plan(n3, p)) return TP_OK;
+  if (dtype == TP_F64)
+    return launch_inv<double, double>(p, (const double*)re, (const double*)im, ntubes, (double*)y, st, handled);
   const float *fr = (const float*)re, *fi = (const float*)im;
   float* yf = (float*)y;
-  if (n3 <= kWideMax)
-    return blue ? launch_inv<float, double, true>(p, fr, fi, ntubes, yf, st, handled)
-                : launch_inv<float, double, false>(p, fr, fi, ntubes, yf, st, handled);
-  return blue ? launch_inv<float, float, true>(p, fr, fi, ntubes, yf, st, handled)
-              : launch_inv<float, float, false>(p, fr, fi, ntubes, yf, st, handled);
+  return n3 <= kWideMax ? launch_inv<float, double>(p, fr, fi, ntubes, yf, st, handled)
+                        : launch_inv<float, float>(p, fr, fi, ntubes, yf, st, handled);
 }
 
 }  // namespace tp

@@ -1,5 +1,5 @@
 // What the tube-transform kernels share: which input tube feeds an output
-// slot, and the LDS transforms of fft_lds.hip.
+// slot, and the transforms of the other files.
 #pragma once
 
 #include "common.hpp"
@@ -56,13 +56,18 @@ struct XcdWalk {
 };
 inline int64_t xcd_grid(int64_t total) { return (total + 7) / 8 * 8; }
 
-// Transforms of many tubes per workgroup in LDS (fft_lds.hip): lengths
-// without prime factors above 13, and Bluestein's transform for other
-// lengths, as far as LDS reaches. *handled is false for other lengths.
+// Transforms of many tubes per workgroup in LDS (fft_lds.hip) of lengths
+// without prime factors above 13 (in n3 / 2 of an even n3), as far as LDS
+// reaches. *handled is false for other lengths.
 int lds_forward(const void* x, int dtype, int64_t n3, const FwdArgs& a, void* re, void* im, hipStream_t st,
                 bool* handled);
 int lds_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t ntubes, void* y, hipStream_t st,
                 bool* handled);
+
+// Dense products with the roots on the matrix cores (fft_dense.hip), for the
+// other lengths (3 to 8192).
+int dense_forward(const void* x, int dtype, int64_t n3, const FwdArgs& a, void* re, void* im, hipStream_t st);
+int dense_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t ntubes, void* y, hipStream_t st);
 
 // Four-step transforms through HBM (fft_four.hip): even lengths up to 2^19 whose
 // half has no prime factor above 13. *handled is false for other lengths.
