@@ -36,7 +36,8 @@ struct Radix {
   int p;
   float cost;  // of a stage, per element: its LDS round trip and its butterfly
 };
-constexpr Radix kRadices[] = {{16, 25}, {15, 26}, {13, 35}, {12, 23}, {11, 33}, {10, 23}, {9, 24},
+// (14 only where a 7 and a 2 would be left)
+constexpr Radix kRadices[] = {{16, 25}, {15, 26}, {14, 35}, {13, 35}, {12, 23}, {11, 33}, {10, 23}, {9, 24},
                               {8, 21},  {7, 27},  {6, 21},  {5, 21},  {4, 18},  {3, 19},  {2, 16}};
 
 void search(int n, int first, float cost, int depth, int* cur, float& best, int* out, int& nout) {
@@ -204,12 +205,11 @@ __device__ void load_tubes(const T* x, const int64_t* src, const double* scl, co
   }
 }
 
-// Writes the tubes: element m of the transformed conjugate, conjugated and
-// times `inv`, is the tube's values 2m and 2m+1 (odd n: value m)
+// Writes the tubes: element m of the transformed conjugate, conjugated, is the
+// tube's values 2m and 2m+1 (odd n: value m)
 template <typename T, typename S, int E>
 __device__ void store_tubes(T* y, int64_t t0, int64_t ntubes, const LdsPlan& p, const Layout<S>& l) {
   const Pieces pc(p.n / E, p.lg);
-  const double inv = 1.0 / (double)p.N;
   for (int f = threadIdx.x; f < pc.total; f += blockDim.x) {
     int piece, u;
     pc.at(f, p.lg, piece, u);
@@ -221,8 +221,8 @@ __device__ void store_tubes(T* y, int64_t t0, int64_t ntubes, const LdsPlan& p, 
     for (int c = 0; c < C; ++c) {
       const int m = piece * C + c;
       const Cx<S> w = l.buf[(m << p.lg) + u];
-      v.v[E > 1 ? 2 * c : 0] = (T)((double)w.x * inv);
-      if constexpr (E > 1) v.v[2 * c + 1] = (T)(-(double)w.y * inv);
+      v.v[E > 1 ? 2 * c : 0] = (T)w.x;
+      if constexpr (E > 1) v.v[2 * c + 1] = (T)-w.y;
     }
     store_run<T, E>(y + t * p.n + (int64_t)piece * E, v);
   }
@@ -324,13 +324,14 @@ __global__ __launch_bounds__(kMaxNT, 4) void irfft_lds_kernel(const T* __restric
   lfft::fill_roots(N, l.tab);
   lfft::fill_positions(p.pl, l.pos);
   __syncthreads();
+  const double inv = 1.0 / (double)N;
   XcdWalk walk((ks + TB - 1) >> p.lg);
   for (int64_t G; walk.next(G);) {
     const int64_t t0 = G << p.lg;
-    // conj Z into buf: the forward transform of the conjugate is the conjugate
-    // of the inverse
+    // conj Z / N into buf: the forward transform of the conjugate is the conjugate
+    // of the inverse (divided here, in float64, and not once more rounded at the end)
     auto put = [&](int k, int u, double zr, double zi) {
-      l.buf[((int)l.pos[k] << p.lg) + u] = Cx<S>{(S)zr, (S)zi};
+      l.buf[((int)l.pos[k] << p.lg) + u] = Cx<S>{(S)(zr * inv), (S)(zi * inv)};
     };
     const bool odd = p.n % 2;
     const int total = (N / 2 + 1) << p.lg;
@@ -447,8 +448,18 @@ int launch_inv(LdsPlan p, const T* re, const T* im, int64_t ntubes, T* y, hipStr
   return TP_OK;
 }
 
-// float32 tubes up to this length are kept in float64 between the stages
+// float32 tubes up to this length are kept in float64 between the stages, and so
+// are those of 4 11^a 13^b, whose stages (of 11, of 13, and of the 2 left over)
+// would round once more often than the sums of 4, 11 and 13 that a transform of
+// the unpacked tube takes (n = 484, float32 between: error 5.2e-8 / 5.6e-8, so
+// 2.5e-8 / 1.7e-8; 1.5e6 values 18 / 15 us, so 19 / 16)
 constexpr int64_t kWideMax = 256;
+bool wide(const LdsPlan& p) {
+  int r = p.N % 2 ? 0 : p.N / 2;
+  for (int q : {11, 13})
+    while (r && r % q == 0) r /= q;
+  return p.n <= kWideMax || (r == 1 && p.n % 2 == 0);
+}
 // lengths that LDS could hold at all
 constexpr int64_t kLdsLenMax = 8192;
 
@@ -463,8 +474,8 @@ int lds_forward(const void* x, int dtype, int64_t n3, const FwdArgs& a, void* re
     return launch_fwd<double, double>(p, (const double*)x, a, (double*)re, (double*)im, st, handled);
   const float* xf = (const float*)x;
   float *fr = (float*)re, *fi = (float*)im;
-  return n3 <= kWideMax ? launch_fwd<float, double>(p, xf, a, fr, fi, st, handled)
-                        : launch_fwd<float, float>(p, xf, a, fr, fi, st, handled);
+  return wide(p) ? launch_fwd<float, double>(p, xf, a, fr, fi, st, handled)
+                 : launch_fwd<float, float>(p, xf, a, fr, fi, st, handled);
 }
 
 int lds_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t ntubes, void* y, hipStream_t st,
@@ -476,8 +487,8 @@ int lds_inverse(const void* re, const void* im, int dtype, int64_t n3, int64_t n
     return launch_inv<double, double>(p, (const double*)re, (const double*)im, ntubes, (double*)y, st, handled);
   const float *fr = (const float*)re, *fi = (const float*)im;
   float* yf = (float*)y;
-  return n3 <= kWideMax ? launch_inv<float, double>(p, fr, fi, ntubes, yf, st, handled)
-                        : launch_inv<float, float>(p, fr, fi, ntubes, yf, st, handled);
+  return wide(p) ? launch_inv<float, double>(p, fr, fi, ntubes, yf, st, handled)
+                 : launch_inv<float, float>(p, fr, fi, ntubes, yf, st, handled);
 }
 
 }  // namespace tp

@@ -424,6 +424,7 @@ __device__ void stages(const Plan& pl, Cx<S>* buf, int lg, int ld, Tab tab) {
       case 11: stage<S, 11, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
       case 12: stage<S, 12, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
       case 13: stage<S, 13, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
+      case 14: stage<S, 14, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
       case 15: stage<S, 15, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
       default: stage<S, 16, DIF, EXACT>(buf, lg, ld, pl.n, m, mag, tab); break;
     }
