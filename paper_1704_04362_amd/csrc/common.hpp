@@ -168,6 +168,12 @@ struct CGemm {
 };
 
 int cgemm(const CGemm& p, int dtype, int prec, hipStream_t st);
+// Rounds of 256 workgroups, in thirds of a complex tile's time, that `s` parts of
+// `tiles` output tiles in each of K slices take (a real tile takes a third)
+inline int64_t contraction_thirds(int64_t K, bool real_last, int64_t tiles, int64_t s) {
+  const int64_t real = tiles * (real_last && K > 1 ? 2 : 1), cplx = tiles * K - real;
+  return std::max(3 * ((cplx * s + 255) / 256), ((3 * cplx + real) * s + 255) / 256);
+}
 // Parts of a contraction of `steps` steps over `tiles` output tiles in each of K
 // slices (the real ones take about a third of the time and start last), one
 // workgroup a CU: the number that needs the fewest steps one after another,
@@ -175,11 +181,9 @@ int cgemm(const CGemm& p, int dtype, int prec, hipStream_t st);
 // each part at least `least` steps, at most 64 parts.
 inline int contraction_parts(int64_t K, bool real_last, int64_t tiles, int64_t steps, int64_t least) {
   if (tiles * K >= 256) return 1;
-  const int64_t real = tiles * (real_last && K > 1 ? 2 : 1), cplx = tiles * K - real;
   int64_t best = 0, parts = 1;
   for (int64_t s = 1; s <= 64 && (s == 1 || steps >= s * least); ++s) {
-    const int64_t thirds = std::max(3 * ((cplx * s + 255) / 256), ((3 * cplx + real) * s + 255) / 256);
-    const int64_t cost = thirds * ((steps + s - 1) / s + 4);
+    const int64_t cost = contraction_thirds(K, real_last, tiles, s) * ((steps + s - 1) / s + 4);
     if (s == 1 || cost < best) {
       best = cost;
       parts = s;

@@ -594,6 +594,21 @@ int cgemm_ksplit(int64_t K, bool real_last, int64_t M, int64_t N, int64_t Kd) {
   return contraction_parts(K, real_last, ((M + BM - 1) / BM) * ((N + BN - 1) / BN), Kd / BK, 4);
 }
 
+// Whether parts of a contraction of pre-split operands pay for the launch that
+// sums their planes (3 us and the planes' bytes both ways), for a product that is
+// long enough not to hide behind the other launches (13 us), at a step's time of
+// 1.9 us (bf16x3) or 1.3 us (bf16). t-product in us, parts / one part, bf16x3 and
+// bf16: 512 x 512 x 16 over 256 53 / 45 and 49 / 39, 512 69 / 66 and 60 / 54, 1024
+// 100 / 111 and 82 / 85; 40 x 40 x 1 over 256 29 / 25 and 29 / 25; 64 x 257 x 16 over
+// 400 36 / 47 and 32 / 37.
+static bool split_parts_pay(const SplitGemm& p, int parts) {
+  const int64_t tiles = ((p.M + SBM - 1) / SBM) * ((p.N + SBN - 1) / SBN), steps = p.Kd / SBK;
+  const auto us = [&](int64_t s) {
+    return (p.terms == 3 ? 1.9 : 1.3) / 3 * (double)(contraction_thirds(p.K, p.real_last, tiles, s) * ((steps + s - 1) / s));
+  };
+  return us(1) >= 13.0 && us(parts) + 3.0 + (double)(16 * parts * p.K * p.M * p.N) / 6e6 < us(1);
+}
+
 int cgemm_split(const SplitGemm& p, hipStream_t st) {
   if (p.K == 0 || p.M == 0 || p.N == 0) return TP_OK;
   if (p.Kd % SBK || p.lda % SBK || p.ldb % SBK || p.lda < p.Kd || p.ldb < p.Kd)
@@ -609,6 +624,7 @@ int cgemm_split(const SplitGemm& p, hipStream_t st) {
   // the same split of a long contraction with few output tiles
   static_assert(SBM == BM && SBN == BN && SBK == BK, "cgemm_ksplit counts these tiles");
   int ksplit = cgemm_ksplit(p.K, p.real_last, p.M, p.N, p.Kd);
+  if (ksplit > 1 && !split_parts_pay(p, ksplit)) ksplit = 1;
   if (ksplit > 1 && p.part_re && p.part_im && p.part_cap >= int64_t(ksplit) * p.K * p.M * p.N) {
     g.ksplit = ksplit;
     g.kchunk = (p.Kd / SBK + ksplit - 1) / ksplit;
