@@ -520,20 +520,25 @@ __global__ __launch_bounds__(kNT, 4) void four_inv_tube_kernel(int64_t ks, FourP
 }
 
 // Four-step plan of an even n: N = n/2 = N1 N2 with N2 the largest divisor
-// <= kMaxN2 that leaves N1 <= kMaxN1, both without prime factors above 13.
+// <= kMaxN2 that leaves N1 <= kMaxN1, both without prime factors above 13; where
+// there is none, the smallest divisor above kMaxN2 and up to kMaxN1 that does
+// (375 x 625), else the same with N1 <= 2 kMaxN1 (1331 x 121): so every n up to
+// 2 kMaxN1 kMaxN2 whose half has no prime factor above 13.
 bool four_plan(int64_t n, FourPlan& fs) {
   if (n % 2 || n < 4) return false;
   const int64_t N = n / 2;
   if (N > (int64_t)kMaxN1 * kMaxN2) return false;
-  for (int64_t n2 = kMaxN2 < N ? kMaxN2 : N; n2 >= 1; --n2) {
-    if (N % n2) continue;
-    const int64_t n1 = N / n2;
-    if (n1 > kMaxN1) break;
-    if (lfft::radix_plan(n1, fs.p1) && lfft::radix_plan(n2, fs.p2)) {
-      fs.N1 = (int)n1;
-      fs.N2 = (int)n2;
-      return true;
-    }
+  const auto take = [&](int64_t n2, int64_t most) {
+    if (N % n2 || N / n2 > most) return false;
+    fs.N1 = (int)(N / n2);
+    fs.N2 = (int)n2;
+    return lfft::radix_plan(fs.N1, fs.p1) && lfft::radix_plan(fs.N2, fs.p2);
+  };
+  for (const int64_t most : {kMaxN1, 2 * kMaxN1}) {
+    for (int64_t n2 = kMaxN2 < N ? kMaxN2 : N; n2 >= 1 && N / n2 <= most; --n2)
+      if (take(n2, most)) return true;
+    for (int64_t n2 = kMaxN2 + 1; n2 <= kMaxN1 && n2 <= N; ++n2)
+      if (take(n2, most)) return true;
   }
   return false;
 }
