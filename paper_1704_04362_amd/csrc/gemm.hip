@@ -27,8 +27,8 @@ constexpr int BK = 16, NT = 256;
 
 struct GemmArgs {
   int64_t M, N, Kd;
-  const void *are, *aim, *bre, *bim;
-  void *cre, *cim;
+  const float *are, *aim, *bre, *bim;
+  float *cre, *cim;
   int64_t lda, ldb, ldc, sa, sb, sc;
   int op_a, op_b;
   int64_t K;
@@ -40,12 +40,12 @@ struct GemmArgs {
 // columns tx + TX j with TY = BM / 4, TX = BN / 4): 64 x 64 in general,
 // 128 x 32 for products with at most 32 columns (the range-finder sketches)
 // so that no thread computes columns past the end.
-template <typename T, int BM, int BN>
+template <int BM, int BN>
 __global__ __launch_bounds__(NT) void cgemm_simt_kernel(GemmArgs g) {
   constexpr int TY = BM / 4, TX = BN / 4;
   static_assert(TY * TX == NT, "4 x 4 outputs per thread");
-  __shared__ T As_re[BK][BM + 1], As_im[BK][BM + 1];
-  __shared__ T Bs_re[BK][BN + 1], Bs_im[BK][BN + 1];
+  __shared__ float As_re[BK][BM + 1], As_im[BK][BM + 1];
+  __shared__ float Bs_re[BK][BN + 1], Bs_im[BK][BN + 1];
   const int tid = threadIdx.x;
   const int tx = tid % TX, ty = tid / TX;
   const int64_t k = blockIdx.z;
@@ -56,21 +56,21 @@ __global__ __launch_bounds__(NT) void cgemm_simt_kernel(GemmArgs g) {
     const int64_t lim = *g.kdim_dev;
     Kd = lim < Kd ? (lim < 0 ? 0 : lim) : Kd;
   }
-  const T* are = (const T*)g.are + k * g.sa;
-  const T* aim = (const T*)g.aim + k * g.sa;
-  const T* bre = (const T*)g.bre + k * g.sb;
-  const T* bim = (const T*)g.bim + k * g.sb;
+  const float* are = g.are + k * g.sa;
+  const float* aim = g.aim + k * g.sa;
+  const float* bre = g.bre + k * g.sb;
+  const float* bim = g.bim + k * g.sb;
 
-  T cr[4][4], ci[4][4];
+  float cr[4][4], ci[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) cr[i][j] = ci[i][j] = T(0);
+    for (int j = 0; j < 4; ++j) cr[i][j] = ci[i][j] = 0.f;
 
   // the next k step's tile values are loaded into registers while the
   // current one is consumed from LDS
   constexpr int RA = (BM * BK) / NT, RB = (BN * BK) / NT;
-  T ra_r[RA], ra_i[RA], rb_r[RB], rb_i[RB];
+  float ra_r[RA], ra_i[RA], rb_r[RB], rb_i[RB];
   auto load = [&](int64_t k0) {
 #pragma unroll
     for (int r = 0; r < RA; ++r) {
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(NT) void cgemm_simt_kernel(GemmArgs g) {
         kk = tid / BM + r * (NT / BM);
       }
       const int64_t gm = m0 + mm, gk = k0 + kk;
-      T vr = T(0), vi = T(0);
+      float vr = 0.f, vi = 0.f;
       if (gm < g.M && gk < Kd) {
         const int64_t off = g.op_a == 0 ? gm * g.lda + gk : gk * g.lda + gm;
         vr = are[off];
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(NT) void cgemm_simt_kernel(GemmArgs g) {
         nn = tid / BK + r * (NT / BK);
       }
       const int64_t gn = n0 + nn, gk = k0 + kk;
-      T vr = T(0), vi = T(0);
+      float vr = 0.f, vi = 0.f;
       if (gn < g.N && gk < Kd) {
         const int64_t off = g.op_b == 0 ? gk * g.ldb + gn : gn * g.ldb + gk;
         vr = bre[off];
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(NT) void cgemm_simt_kernel(GemmArgs g) {
     if (real) {
 #pragma unroll
       for (int kk = 0; kk < BK; ++kk) {
-        T a[4], b[4];
+        float a[4], b[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) a[i] = As_re[kk][ty + TY * i];
 #pragma unroll
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(NT) void cgemm_simt_kernel(GemmArgs g) {
     } else {
 #pragma unroll
       for (int kk = 0; kk < BK; ++kk) {
-        T ar[4], ai[4], br[4], bi[4];
+        float ar[4], ai[4], br[4], bi[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           ar[i] = As_re[kk][ty + TY * i];
@@ -185,8 +185,8 @@ __global__ __launch_bounds__(NT) void cgemm_simt_kernel(GemmArgs g) {
     }
     __syncthreads();
   }
-  T* cre = (T*)g.cre + k * g.sc;
-  T* cim = (T*)g.cim + k * g.sc;
+  float* cre = g.cre + k * g.sc;
+  float* cim = g.cim + k * g.sc;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int64_t gm = m0 + ty + TY * i;
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(NT) void cgemm_simt_kernel(GemmArgs g) {
       const int64_t gn = n0 + tx + TX * j;
       if (gn >= g.N) continue;
       cre[gm * g.ldc + gn] = cr[i][j];
-      cim[gm * g.ldc + gn] = real ? T(0) : ci[i][j];
+      cim[gm * g.ldc + gn] = real ? 0.f : ci[i][j];
     }
   }
 }
@@ -256,16 +256,17 @@ int cgemm(const CGemm& p, int dtype, int prec, hipStream_t st) {
     if (int rc = cgemm_mfma(p, prec, st, &handled)) return rc;
     if (handled) return TP_OK;
   }
-  GemmArgs g{p.M, p.N, p.Kd, p.are, p.aim, p.bre, p.bim, p.cre, p.cim, p.lda, p.ldb, p.ldc,
-             p.sa, p.sb, p.sc, p.op_a, p.op_b, p.K, p.real_last ? 1 : 0, p.kdim_dev};
+  GemmArgs g{p.M, p.N, p.Kd, (const float*)p.are, (const float*)p.aim, (const float*)p.bre, (const float*)p.bim,
+             (float*)p.cre, (float*)p.cim, p.lda, p.ldb, p.ldc, p.sa, p.sb, p.sc, p.op_a, p.op_b, p.K,
+             p.real_last ? 1 : 0, p.kdim_dev};
   if (p.K > 65535) return fail(TP_EUNSUPPORTED, "more than 65535 Fourier slices");
   const bool narrow = p.N <= 32;
   const int64_t bm = narrow ? 128 : 64, bn = narrow ? 32 : 64;
   dim3 grid((unsigned)((p.N + bn - 1) / bn), (unsigned)((p.M + bm - 1) / bm), (unsigned)p.K);
   if (narrow)
-    hipLaunchKernelGGL((cgemm_simt_kernel<float, 128, 32>), grid, dim3(NT), 0, st, g);
+    hipLaunchKernelGGL((cgemm_simt_kernel<128, 32>), grid, dim3(NT), 0, st, g);
   else
-    hipLaunchKernelGGL((cgemm_simt_kernel<float, 64, 64>), grid, dim3(NT), 0, st, g);
+    hipLaunchKernelGGL((cgemm_simt_kernel<64, 64>), grid, dim3(NT), 0, st, g);
   TP_LAUNCH_CHECK();
   return TP_OK;
 }

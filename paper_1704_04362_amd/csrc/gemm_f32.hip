@@ -264,7 +264,6 @@ __global__ __launch_bounds__(FT, W == 4 ? 1 : 3) void cgemm_f32_kernel(FArgs g) 
     f32_body<false, W, OPA, OPB, Off>(g, k, part, lds);
 }
 
-// C[k] = sum over the parts, in part order
 }  // namespace
 
 // Parts of a split contraction for the float32 matrix-core product, at least

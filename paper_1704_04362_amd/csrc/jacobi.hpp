@@ -61,19 +61,6 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Row transform of pair (c, s, e) on a column (x = M_p, y = M_q):
-//   M_p = c x - s e y,  M_q = s x + c e y;
-// the column transform is the same with conj(e).
-__device__ __forceinline__ void jrot_apply(double c, double s, double er, double ei, double& xr, double& xi,
-                                           double& yr, double& yi) {
-  const double eyr = er * yr - ei * yi, eyi = er * yi + ei * yr;
-  const double nxr = c * xr - s * eyr, nxi = c * xi - s * eyi;
-  yr = s * xr + c * eyr;
-  yi = s * xi + c * eyi;
-  xr = nxr;
-  xi = nxi;
-}
-
 // Diagonalises the n x n Hermitian matrix in sh.H (n <= MAXN) in place,
 // accumulating the unitary in sh.V (initialised here to the identity).
 // Stops when the off-diagonal mass is below rel_tol^2 of the total or after

@@ -38,10 +38,14 @@ struct Rot32 {
   double c, s, er, ei;
 };
 
-// 1 / sqrt(x), sqrt(x) and y / x for values whose squares neither overflow nor
-// underflow: the hardware estimate (about 2^-24) and the refinement steps of
-// the library functions, without their scaling and special cases. Zeros,
-// infinities and NaN give NaN or infinity, which the caller's test rules out.
+// 1 / sqrt(x), sqrt(x) and y / x from the hardware estimates (about 2^-24), for
+// values whose squares neither overflow nor underflow. Zeros, infinities and NaN
+// give NaN or infinity, which the caller's test rules out.
+// 1 / sqrt: one step of third order, y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2.
+// sqrt: a step of Goldschmidt's iteration on g ~ sqrt(x) and h ~ 1 / (2 sqrt(x)),
+// then g + h (x - g^2), Newton's step in g, twice.
+// Quotient: two Newton steps r + r (1 - x r) of the reciprocal, and the product
+// y r corrected once by its residual.
 __device__ __forceinline__ double j32_rsqrt(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   const double e = fma(y * -x, y, 1.0);

@@ -73,8 +73,8 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // transposition over the lane groups hands it column 16 q + 4 kk + g for the
 // product kk. A 16 x 16 block's re = Xr Xr^T + Xi Xi^T and im = Xi Xr^T - Xr Xi^T
 // run over all columns in order. Of the eight only seven are formed, one per
-// wavefront (re of block (1,0) is that of (0,1) transposed). Two column groups'
-// loads are in flight during the products of a third.
+// wavefront (re of block (1,0) is that of (0,1) transposed). Four column groups'
+// loads are in flight at a time (kAhead).
 __device__ __forceinline__ void swap32(float& a, float& b) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   a = __uint_as_float(r[0]);
