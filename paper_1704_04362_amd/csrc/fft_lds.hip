@@ -187,29 +187,32 @@ __device__ void load_tubes(const T* x, const int64_t* src, const double* scl, co
       if (f >= pc.total || piece >= pc.nv) continue;
       const bool live = src[u] >= 0;
       const double s = scl[u];
-      // a scaled value is rounded to its type
-      double w[E];
+      T w[E];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const double t = (double)v[q].v[e], ts = t * s;
-        w[e] = !live ? 0.0 : (s == 1.0) ? t : (double)(T)ts;
-      }
+      for (int e = 0; e < E; ++e) w[e] = !live ? T(0) : (s == 1.0) ? v[q].v[e] : (T)((double)v[q].v[e] * s);
       constexpr int C = E > 1 ? E / 2 : 1;
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         const int m = piece * C + c;
-        const double zr = w[E > 1 ? 2 * c : 0], zi = E > 1 ? w[E > 1 ? 2 * c + 1 : 0] : 0.0;
+        const double zr = (double)w[E > 1 ? 2 * c : 0], zi = E > 1 ? (double)w[E > 1 ? 2 * c + 1 : 0] : 0.0;
         l.buf[(m << p.lg) + u] = Cx<S>{(S)zr, (S)zi};
       }
     }
   }
 }
 
+// Inverse transforms are divided by their length in float64: where they are read
+// if float32 values lie between the stages, which round the last stage's, else
+// where they are written
+template <typename S>
+constexpr bool kDivideFirst = sizeof(S) == 4;
+
 // Writes the tubes: element m of the transformed conjugate, conjugated, is the
 // tube's values 2m and 2m+1 (odd n: value m)
 template <typename T, typename S, int E>
 __device__ void store_tubes(T* y, int64_t t0, int64_t ntubes, const LdsPlan& p, const Layout<S>& l) {
   const Pieces pc(p.n / E, p.lg);
+  const double inv = kDivideFirst<S> ? 1.0 : 1.0 / (double)p.N;
   for (int f = threadIdx.x; f < pc.total; f += blockDim.x) {
     int piece, u;
     pc.at(f, p.lg, piece, u);
@@ -221,8 +224,8 @@ __device__ void store_tubes(T* y, int64_t t0, int64_t ntubes, const LdsPlan& p, 
     for (int c = 0; c < C; ++c) {
       const int m = piece * C + c;
       const Cx<S> w = l.buf[(m << p.lg) + u];
-      v.v[E > 1 ? 2 * c : 0] = (T)w.x;
-      if constexpr (E > 1) v.v[2 * c + 1] = (T)-w.y;
+      v.v[E > 1 ? 2 * c : 0] = (T)((double)w.x * inv);
+      if constexpr (E > 1) v.v[2 * c + 1] = (T)(-(double)w.y * inv);
     }
     store_run<T, E>(y + t * p.n + (int64_t)piece * E, v);
   }
@@ -324,12 +327,12 @@ __global__ __launch_bounds__(kMaxNT, 4) void irfft_lds_kernel(const T* __restric
   lfft::fill_roots(N, l.tab);
   lfft::fill_positions(p.pl, l.pos);
   __syncthreads();
-  const double inv = 1.0 / (double)N;
+  const double inv = kDivideFirst<S> ? 1.0 / (double)N : 1.0;
   XcdWalk walk((ks + TB - 1) >> p.lg);
   for (int64_t G; walk.next(G);) {
     const int64_t t0 = G << p.lg;
-    // conj Z / N into buf: the forward transform of the conjugate is the conjugate
-    // of the inverse (divided here, in float64, and not once more rounded at the end)
+    // conj Z into buf: the forward transform of the conjugate is the conjugate
+    // of the inverse
     auto put = [&](int k, int u, double zr, double zi) {
       l.buf[((int)l.pos[k] << p.lg) + u] = Cx<S>{(S)(zr * inv), (S)(zi * inv)};
     };
