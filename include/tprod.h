@@ -167,11 +167,11 @@ int tp_version(void);
  * ------------------------------------------------------------------------- */
 
 /* Forward transform of every tube: Xh = first K slices of fft(X, [], 3).
- * Xh must be K x n1 x n2 with X's dtype. n3 >= 1. Tube lengths: any; even
- * lengths beyond one workgroup's LDS (float32 above 8192, float64 above
- * 4096) up to 2^19 with no prime factor above 13 (e.g. 500000) run a
- * four-step transform that uses Xh itself as its intermediate storage;
- * other lengths without a fast kernel fall back to a direct O(n3^2)
+ * Xh must be K x n1 x n2 with X's dtype. n3 >= 1. Tube lengths: any up to
+ * one workgroup's LDS (8192 float32, 4096 float64 values) has a fast kernel;
+ * even lengths beyond, up to 2^19, whose half has no prime factor above 13
+ * (e.g. 500000) run a four-step transform that uses Xh itself as its
+ * intermediate storage; the other lengths fall back to a direct O(n3^2)
  * transform. The same holds for tp_tifft (which then uses X). */
 int tp_tfft(const tp_tensor* X, tp_spectrum* Xh, void* stream);
 

@@ -24,8 +24,8 @@
 // Bound: HBM up to n of about 150, then the float64 matrix cores (n^2 operations a
 // tube, half of that in two sequences; 58 TFLOP/s from registers, 34 here at n =
 // 997). 1.5e6 float64 values, us forward / inverse, direct sum and Bluestein /
-// here: n = 29 40 / 66 and 115 / 110 -> 13 / 14, 127 642 / 943 and 92 / 87 -> 16 / 14,
-// 254 1670 / 3542 and 66 / 64 -> 14 / 14, 1013 Bluestein 158 / 150 -> 65 / 57; 14640
+// here: n = 29 40 / 66 and 115 / 110 -> 14 / 13, 127 642 / 943 and 92 / 87 -> 14 / 14,
+// 254 1670 / 3542 and 66 / 64 -> 16 / 15, 1013 Bluestein 158 / 150 -> 58 / 56; 14640
 // float32 tubes of 997, Bluestein 912 / 887 -> 424 / 384, of 2039 1880 / 1893 -> 1532 /
 // 1375.
 #include <algorithm>

@@ -12,8 +12,8 @@
 // Bound by the matrix cores (64 cycles per instruction of 2,048 operations;
 // 58 TFLOP/s measured from registers). Measured against the vector kernel this
 // replaces (a float64 multiply-add per lane in 8 cycles, tiles padded to 64 x 64):
-// 31 slices of 257 x 380 x 201 411 -> 195 us, 33 of 512 x 512 x 512 1504 -> 800,
-// 65 of 300 x 1024 x 32 405 -> 188, 25 of 28 x 1732 x 39 528 -> 170.
+// 31 slices of 257 x 380 x 201 411 -> 180 us, 33 of 512 x 512 x 512 1504 -> 708,
+// 65 of 300 x 1024 x 32 405 -> 186, 25 of 28 x 1732 x 39 528 -> 171.
 #include <algorithm>
 
 #include "common.hpp"
